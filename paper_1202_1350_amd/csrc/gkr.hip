@@ -27,6 +27,7 @@
 
 #include "../../include/gkr.h"
 #include "fp61.hpp"
+#include "f2sc.hpp"
 #include "kernels.hpp"
 #include "steps.hpp"
 #include "nif2.hpp"
@@ -2845,70 +2846,57 @@ bool pow2(u64 n) { return n && !(n & (n - 1)); }
 }  // namespace
 
 // Scratch of one F2 sum-check proof at base (sized when base is NULL):
-// the two folded tables, two rounds' partial rows, the transcript and
-// challenges on the device, the challenge stream's state and, for host
+// the two alternating folded levels, two passes' rows, the transcript and
+// its challenges on the device, the challenge stream's states and, for host
 // inputs, their staging copy.
 struct F2scLayout {
-    u64 *A0, *A1, *partials, *msgs, *chals;
-    ProofState *ps;
+    u64 *A0, *A1, *rows, *msgs, *chals;
+    F2scState *ps;
     u32 *in;
 };
 static size_t f2sc_layout(char *base, u64 n, int on_device, F2scLayout &v) {
     const u32 l = log2ceil(n);
     Arena a;
     a.base = base;
-    v.A0 = a.take<u64>(std::max<u64>(n / 2, 2));
-    v.A1 = a.take<u64>(std::max<u64>(n / 4, 2));
-    v.partials = a.take<u64>((u64)MAX_BLOCKS * 6);  // two rounds' rows
+    v.A0 = a.take<u64>(std::max<u64>(n / 8, 2));
+    v.A1 = a.take<u64>(std::max<u64>(n / 64, 2));
+    v.rows = a.take<u64>(2ull * F2SC_MAX_ROWS * F2SC_ROW);
     v.msgs = a.take<u64>(1 + 3ull * l);
     v.chals = a.take<u64>(std::max<u32>(l, 1));
-    v.ps = a.take<ProofState>(1);
+    v.ps = a.take<F2scState>(1);
     v.in = a.take<u32>(on_device ? 1 : n);
     return a.used;
 }
 
 // Enqueue one F2 sum-check proof on st into the scratch v lays out (host
-// inputs are first copied into v.in); the transcript stays on the device.
+// inputs are first copied into v.in); the transcript goes to v.msgs, v.chals.
 static int f2sc_enqueue(const uint32_t *freq, u64 n, int on_device, u64 seed, const F2scLayout &v,
                         hipStream_t st) {
-    const u32 l = log2ceil(n);
+    const u32 l = log2ceil(n), np = f2sc_passes(l);
     const u32 *a32 = freq;
     if (!on_device) {
         HIP_TRY(hipMemcpyAsync(v.in, freq, n * 4, hipMemcpyHostToDevice, st));
         a32 = v.in;
     }
-    int nb = 0;
-    if (l == 0) {
-        LAUNCH(PC_MISC, 4, launch_f2sc_single(st, a32, v.msgs));
-        return GKR_OK;
-    }
-    LAUNCH(PC_MISC, 0, launch_f2sc_init(st, v.ps, seed));
+    F2scPass a;
+    memset(&a, 0, sizeof a);
+    a.seed = seed;
+    a.ps = v.ps;
+    a.msgs = v.msgs;
+    a.chals = v.chals;
     u64 *bufs[2] = {v.A0, v.A1};
     const u64 *src = nullptr;
-    // round j's launch also finishes round j - 1 (its message and
-    // challenge), so the challenge is drawn one launch after its sums
-    int prev = 0;
-    // rounds from j0 on run as one tail once level j0 fits it
-    u32 j0 = l;
-    if (l >= 3) j0 = std::max<u32>(2, l > 12 ? l - 12 : 2);
-    for (u32 j = 0; j < j0; j++) {
-        const u64 pairs = n >> (j + 1);
-        u64 *dst = j == 0 ? nullptr : bufs[(j + 1) & 1];
-        const double bytes = j == 0 ? pairs * 8.0 : (j == 1 ? pairs * 32.0 : pairs * 48.0);
-        u64 *pmsg = j ? v.msgs + 1 + 3 * (j - 1) : nullptr, *pchal = j ? v.chals + j - 1 : nullptr;
-        LAUNCH(PC_F2SC, bytes,
-               launch_f2sc_round(st, (int)j, pairs, a32, src, dst, v.ps, v.partials, prev, pmsg, pchal,
-                                 j == 1 ? v.msgs : nullptr, &nb));
-        prev = nb;
-        if (j > 0) src = dst;
+    for (a.p = 0; a.p < np; a.p++) {
+        u64 *dst = a.p ? bufs[(a.p - 1) & 1] : nullptr;
+        a.rows = v.rows + (u64)(a.p & 1) * F2SC_MAX_ROWS * F2SC_ROW;
+        const u64 lev = n >> (3 * a.p);  // entries stored (p >= 1), eight read for each
+        LAUNCH(PC_F2SC, a.p == 0 ? n * 4.0 : lev * ((a.p == 1 ? 32.0 : 64.0) + 8.0),
+               launch_f2sc_pass(st, a, l, a32, src, dst));
+        a.prev_rows = a.rows;
+        a.prev_nrows = f2sc_rows(l, a.p);
+        if (a.p) src = dst;
     }
-    if (j0 < l)
-        LAUNCH(PC_FINAL, (n >> (j0 - 1)) * 8.0,
-               launch_f2sc_tail(st, (int)j0, (int)l, src, prev, v.partials, v.ps, v.msgs, v.chals));
-    else
-        LAUNCH(PC_FINAL, prev * 24.0,
-               launch_f2sc_final(st, (int)(l - 1), prev, v.partials, v.ps, v.msgs + 1 + 3 * (l - 1),
-                                 v.chals + l - 1, l == 1 ? v.msgs : nullptr));
+    LAUNCH(PC_FINAL, (double)(n >> (3 * np)) * (np > 1 ? 64.0 : np ? 32.0 : 4.0), launch_f2sc_tail(st, a, l, a32, src));
     return GKR_OK;
 }
 
@@ -2931,10 +2919,12 @@ extern "C" int f2_sumcheck_prove(const uint32_t *freq, uint64_t n, int on_device
     rc = f2_reserve(f2sc_layout(nullptr, n, on_device, v), nm + l + 1);
     if (rc) return rc;
     f2sc_layout((char *)g_f2.mem, n, on_device, v);
+    // the kernels write the transcript's few words straight into pinned host
+    // memory (complete once the stream is waited for): no copies behind them
+    v.msgs = g_f2.h;
+    v.chals = g_f2.h + nm;
     rc = f2sc_enqueue(freq, n, on_device, seed, v, st);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(g_f2.h, v.msgs, nm * 8, hipMemcpyDeviceToHost, st));
-    if (chals && l) HIP_TRY(hipMemcpyAsync(g_f2.h + nm, v.chals, l * 8ull, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     memcpy(msgs, g_f2.h, nm * 8);
     if (chals && l) memcpy(chals, g_f2.h + nm, l * 8ull);

@@ -1,6 +1,5 @@
 // kernels.hip -- HIP kernels (gfx950) of the GKR prover's per-layer
-// sum-check over F_p, p = 2^61 - 1, of its verifier, and of the F2
-// sum-check.
+// sum-check over F_p, p = 2^61 - 1, and of its verifier.
 //
 // Sec. 4.1.1: each gate contributes independently to the prover's message;
 // a workgroup sums its gates' contributions (wave64 shuffles, then LDS),
@@ -17,20 +16,6 @@ using fp::add;
 using fp::mul;
 using fp::P;
 using fp::sub;
-
-struct alignas(16) u64x2 {
-    u64 x, y;
-};
-
-__device__ __forceinline__ u64x2 ld2(const u64 *p, u64 i) {
-    return *reinterpret_cast<const u64x2 *>(p + i);
-}
-__device__ __forceinline__ void st2(u64 *p, u64 i, u64 a, u64 b) {
-    u64x2 v;
-    v.x = a;
-    v.y = b;
-    *reinterpret_cast<u64x2 *>(p + i) = v;
-}
 
 #define GTID ((u64)blockIdx.x * blockDim.x + threadIdx.x)
 #define GSTRIDE ((u64)gridDim.x * blockDim.x)
@@ -62,48 +47,6 @@ __device__ __forceinline__ void block_store(u64 (&v)[K], u64 *out) {
 #pragma unroll
         for (int w = 0; w < BLOCK / 64; w++) a = add(a, sm[threadIdx.x][w]);
         out[threadIdx.x] = a;
-    }
-}
-
-// One workgroup: fold nparts rows of K values; totals land in tot[] for
-// thread 0 (and every thread, through LDS).
-template <int K>
-__device__ __forceinline__ void rows_total(int nparts, const u64 *partials, u64 (&tot)[K]) {
-    __shared__ u64 res[K];
-    u64 v[K];
-#pragma unroll
-    for (int k = 0; k < K; k++) v[k] = 0;
-    for (int r = threadIdx.x; r < nparts; r += BLOCK) {
-#pragma unroll
-        for (int k = 0; k < K; k++) v[k] = add(v[k], partials[(u64)r * K + k]);
-    }
-    block_store<K>(v, res);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; k++) tot[k] = res[k];
-}
-
-// Challenge d of the F2 sum-check, drawn from the state before it; the
-// state after it goes to *next when not NULL.
-__device__ __forceinline__ u64 draw(const ProofState *ps, int d, u64 *next) {
-    u64 s = ps->rng[d & 1];
-    const u64 r = fp::sm_field(s);
-    if (next) *next = s;
-    return r;
-}
-
-// Message of F2 sum-check round d from its partial rows, challenge r_d, and
-// the state after it (one workgroup).
-__device__ __forceinline__ void f2sc_finish(int d, int nparts, const u64 *part, ProofState *ps, u64 *msg,
-                                            u64 *chal, u64 *f2) {
-    u64 t[3];
-    rows_total<3>(nparts, part, t);
-    if (threadIdx.x == 0) {
-        msg[0] = t[0];
-        msg[1] = t[1];
-        msg[2] = t[2];
-        if (f2) *f2 = add(t[0], t[1]);
-        *chal = draw(ps, d, &ps->rng[(d + 1) & 1]);
     }
 }
 
@@ -257,154 +200,6 @@ __global__ void __launch_bounds__(BLOCK) k_reduce_rows(int nparts, int K, const 
 
 hipError_t launch_reduce_rows(hipStream_t st, int nparts, int K, const u64 *partials, u64 *out) {
     hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(BLOCK), 0, st, nparts, K, partials, out);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------- F2 sum-check (a11)
-
-template <int J>  // 0: first round, 1: second round (u32 source), 2: later rounds
-__global__ void __launch_bounds__(BLOCK) k_f2sc_round(int j, u64 nm, const u32 *a32, const u64 *Asrc,
-                                                      u64 *Aout, ProofState *ps, u64 *part, int prev_parts,
-                                                      u64 *prev_msg, u64 *prev_chal, u64 *f2) {
-    const u32 nb = gridDim.x - (J > 0 ? 1 : 0);  // body workgroups
-    if (J > 0 && blockIdx.x == nb) {  // finishes round j - 1 beside the body
-        f2sc_finish(j - 1, prev_parts, part + 3ull * MAX_BLOCKS * ((j - 1) & 1), ps, prev_msg, prev_chal, f2);
-        return;
-    }
-    u64 r = 0;
-    if (J > 0) r = draw(ps, j - 1, nullptr);  // r_{j-1}: round j-1's sums are complete
-    const u64 stride = (u64)nb * BLOCK;
-    u64 acc[3] = {0, 0, 0};
-    if (J == 0) {
-        // u32 pairs (a, b): a^2, b^2 and ab are exact in 64 bits; their sums
-        // stay exact in 128 bits (a thread adds far fewer than 2^64 terms), and
-        // (2b - a)^2 = a^2 + 4 b^2 - 4 ab, so the thread reduces mod p once
-        fp::u128 saa = 0, sbb = 0, sab = 0;
-        for (u64 m = GTID; m < nm; m += stride) {
-            const uint2 p = *reinterpret_cast<const uint2 *>(a32 + 2 * m);
-            const u64 a = p.x, b = p.y;
-            saa += a * a;
-            sbb += b * b;
-            sab += a * b;
-        }
-        const u64 ra = fp::red128(saa), rb = fp::red128(sbb), rab = fp::red128(sab);
-        const u64 rb4 = add(add(rb, rb), add(rb, rb)), rab4 = add(add(rab, rab), add(rab, rab));
-        acc[0] = ra;
-        acc[1] = rb;
-        acc[2] = sub(add(ra, rb4), rab4);
-    }
-    for (u64 m = GTID; J > 0 && m < nm; m += stride) {
-        u64 v0, v1;
-        if (J == 1) {
-            const uint4 p = *reinterpret_cast<const uint4 *>(a32 + 4 * m);
-            v0 = add(p.x, mul(r, sub(p.y, p.x)));
-            v1 = add(p.z, mul(r, sub(p.w, p.z)));
-            st2(Aout, 2 * m, v0, v1);
-        } else {
-            const u64x2 p = ld2(Asrc, 4 * m), q = ld2(Asrc, 4 * m + 2);
-            v0 = add(p.x, mul(r, sub(p.y, p.x)));
-            v1 = add(q.x, mul(r, sub(q.y, q.x)));
-            st2(Aout, 2 * m, v0, v1);
-        }
-        const u64 d = sub(add(v1, v1), v0);
-        acc[0] = add(acc[0], mul(v0, v0));
-        acc[1] = add(acc[1], mul(v1, v1));
-        acc[2] = add(acc[2], mul(d, d));
-    }
-    block_store<3>(acc, part + 3ull * MAX_BLOCKS * (j & 1) + 3 * (u64)blockIdx.x);
-}
-
-hipError_t launch_f2sc_round(hipStream_t st, int j, u64 nm, const u32 *a32, const u64 *Asrc,
-                             u64 *Aout, ProofState *ps, u64 *part, int prev_parts, u64 *prev_msg,
-                             u64 *prev_chal, u64 *f2, int *nblocks) {
-    const int nb = blocks_for(nm, 4);
-    *nblocks = nb;
-    const dim3 b(BLOCK);
-    if (j == 0)
-        hipLaunchKernelGGL(k_f2sc_round<0>, dim3(nb), b, 0, st, j, nm, a32, Asrc, Aout, ps, part, prev_parts,
-                           prev_msg, prev_chal, f2);
-    else if (j == 1)
-        hipLaunchKernelGGL(k_f2sc_round<1>, dim3(nb + 1), b, 0, st, j, nm, a32, Asrc, Aout, ps, part,
-                           prev_parts, prev_msg, prev_chal, f2);
-    else
-        hipLaunchKernelGGL(k_f2sc_round<2>, dim3(nb + 1), b, 0, st, j, nm, a32, Asrc, Aout, ps, part,
-                           prev_parts, prev_msg, prev_chal, f2);
-    return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(BLOCK) k_f2sc_final(int j, int nparts, const u64 *part, ProofState *ps,
-                                                      u64 *msg, u64 *chal, u64 *f2) {
-    f2sc_finish(j, nparts, part + 3ull * MAX_BLOCKS * (j & 1), ps, msg, chal, f2);
-}
-
-__global__ void __launch_bounds__(BLOCK) k_f2sc_tail(int j0, int l, const u64 *Asrc, int prev_parts,
-                                                     const u64 *part, ProofState *ps, u64 *msgs, u64 *chals) {
-    __shared__ __align__(16) u64 T[2][F2SC_TAIL];
-    __shared__ u64 tot[3];
-    const int d = j0 - 1;
-    f2sc_finish(d, prev_parts, part + 3ull * MAX_BLOCKS * (d & 1), ps, msgs + 1 + 3 * d, chals + d, nullptr);
-    u64 st = ps->rng[d & 1];
-    const u64 r0 = fp::sm_field(st);  // r_{j0-1}: round j0-1's sums are complete
-    u32 nt = 1u << (l - j0);          // entries of level j0
-    for (u32 e = threadIdx.x; e < nt; e += BLOCK) {
-        const u64x2 p = ld2(Asrc, 2 * e);
-        T[0][e] = add(p.x, mul(r0, sub(p.y, p.x)));
-    }
-    __syncthreads();
-    for (int j = j0, b = 0; j < l; j++, b ^= 1, nt >>= 1) {
-        const u32 half = nt >> 1;
-        u64 acc[3] = {0, 0, 0};
-        for (u32 m = threadIdx.x; m < half; m += BLOCK) {
-            const u64 v0 = T[b][2 * m], v1 = T[b][2 * m + 1], dd = sub(add(v1, v1), v0);
-            acc[0] = add(acc[0], mul(v0, v0));
-            acc[1] = add(acc[1], mul(v1, v1));
-            acc[2] = add(acc[2], mul(dd, dd));
-        }
-        block_store<3>(acc, tot);
-        __syncthreads();  // round j's message is complete
-        if (threadIdx.x < 3) msgs[1 + 3 * j + threadIdx.x] = tot[threadIdx.x];
-        const u64 r = fp::sm_field(st);
-        if (threadIdx.x == 0) chals[j] = r;
-        for (u32 m = threadIdx.x; m < half; m += BLOCK) {
-            const u64 v0 = T[b][2 * m], v1 = T[b][2 * m + 1];
-            T[b ^ 1][m] = add(v0, mul(r, sub(v1, v0)));
-        }
-        __syncthreads();  // the next level is complete (and tot is read)
-    }
-}
-
-hipError_t launch_f2sc_tail(hipStream_t st, int j0, int l, const u64 *Asrc, int prev_parts, const u64 *part,
-                            ProofState *ps, u64 *msgs, u64 *chals) {
-    hipLaunchKernelGGL(k_f2sc_tail, dim3(1), dim3(BLOCK), 0, st, j0, l, Asrc, prev_parts, part, ps, msgs, chals);
-    return hipGetLastError();
-}
-
-hipError_t launch_f2sc_final(hipStream_t st, int j, int nparts, const u64 *part, ProofState *ps,
-                             u64 *msg, u64 *chal, u64 *f2) {
-    hipLaunchKernelGGL(k_f2sc_final, dim3(1), dim3(BLOCK), 0, st, j, nparts, part, ps, msg, chal, f2);
-    return hipGetLastError();
-}
-
-__global__ void k_f2sc_init(ProofState *ps, u64 seed) {
-    if (threadIdx.x == 0) {
-        ps->rng[0] = fp::sm_state(seed, fp::PURPOSE_F2SC);
-    }
-}
-
-hipError_t launch_f2sc_init(hipStream_t st, ProofState *ps, u64 seed) {
-    hipLaunchKernelGGL(k_f2sc_init, dim3(1), dim3(64), 0, st, ps, seed);
-    return hipGetLastError();
-}
-
-__global__ void k_f2sc_single(const u32 *a32, u64 *msg) {
-    if (threadIdx.x == 0) {
-        const u64 v = a32[0];
-        msg[0] = mul(v, v);
-    }
-}
-
-hipError_t launch_f2sc_single(hipStream_t st, const u32 *a32, u64 *msg) {
-    hipLaunchKernelGGL(k_f2sc_single, dim3(1), dim3(64), 0, st, a32, msg);
     return hipGetLastError();
 }
 

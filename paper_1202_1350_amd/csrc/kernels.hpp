@@ -18,15 +18,6 @@ typedef uint8_t u8;
 // Layer gate mix: the kernels drop the type array when a layer is uniform.
 enum Kind { KIND_ADD = 0, KIND_MUL = 1, KIND_MIXED = 2 };
 
-// Device state of an F2 sum-check.
-struct ProofState {
-    // SplitMix64 states of the challenge stream: the state before draw d
-    // sits in rng[d & 1], so a launch reads one slot while its recorder
-    // writes the other
-    u64 rng[2];
-    u64 pad[2];
-};
-
 // Workgroup size of every reduction kernel, and the cap on workgroups per
 // launch (8 per CU on 256 CUs).
 constexpr int BLOCK = 256;
@@ -77,33 +68,6 @@ hipError_t launch_mle(hipStream_t st, u64 n, const u64 *T64, const u32 *T32, con
                       int nb_fixed = 0);
 // Fold nparts rows of K partial sums into out[0..K).
 hipError_t launch_reduce_rows(hipStream_t st, int nparts, int K, const u64 *partials, u64 *out);
-
-// ---- F2 sum-check (a11) -------------------------------------------------------
-// Round j over nm = n / 2^{j+1} pairs.  j = 0: pairs from the u32 vector.
-// j = 1: fold the u32 vector by r_0 into Aout; j >= 2: fold Asrc (u64) by
-// r_{j-1}, which every workgroup draws from the state round j-1 completed.
-// Partials of round j: rows (sum A0^2, sum A1^2, sum (2 A1 - A0)^2) at
-// part + 3 MAX_BLOCKS (j & 1).  For j >= 1 one more workgroup finishes round
-// j-1: its message (G(0), G(1), G(2)) into prev_msg (and F2 = G(0) + G(1)
-// into *f2 when not NULL), r_{j-1} into *prev_chal, and the state after it.
-hipError_t launch_f2sc_round(hipStream_t st, int j, u64 nm, const u32 *a32, const u64 *Asrc,
-                             u64 *Aout, ProofState *ps, u64 *part, int prev_parts, u64 *prev_msg,
-                             u64 *prev_chal, u64 *f2, int *nblocks);
-// The last rounds j0..l-1 in one workgroup, from level j0-1 of the table
-// (u64, 2 F2SC_TAIL entries at most, stored by round j0-1's launch): it
-// finishes round j0-1 (prev_parts rows), folds that level by r_{j0-1} into
-// LDS, then per round sums the message, and only after a barrier that
-// completes it draws the round's challenge and folds.  msgs and chals are
-// the transcript's bases.  j0 >= 2.
-constexpr int F2SC_TAIL = 4096;
-hipError_t launch_f2sc_tail(hipStream_t st, int j0, int l, const u64 *Asrc, int prev_parts, const u64 *part,
-                            ProofState *ps, u64 *msgs, u64 *chals);
-// Finish of the last round j over its nparts partial rows, as above.
-hipError_t launch_f2sc_final(hipStream_t st, int j, int nparts, const u64 *part, ProofState *ps,
-                             u64 *msg, u64 *chal, u64 *f2);
-hipError_t launch_f2sc_init(hipStream_t st, ProofState *ps, u64 seed);
-// n == 1: the transcript is just F2 = a[0]^2.
-hipError_t launch_f2sc_single(hipStream_t st, const u32 *a32, u64 *msg);
 
 // ---- field check ----------------------------------------------------------
 hipError_t launch_field_op(hipStream_t st, int op, const u64 *a, const u64 *b, u64 *out, u64 n);

@@ -58,3 +58,16 @@ def test_c2_f2sc_2p26_full_bit_exact():
     assert np.array_equal(got_m, want_m) and np.array_equal(got_c, want_c)
     assert int(got_m[0]) == int((a.astype(np.int64) ** 2).sum()) % P
     assert G().f2_sumcheck_verify(ta, seed, got_m)[0]
+
+
+@pytest.mark.parametrize("logn", [5, 6, 7, 8, 12, 13, 14, 15, 18, 21])
+def test_full_values_where_the_passes_change(logn):
+    """Full 32-bit counts at each residue of the rounds a pass takes, at the
+    tail's largest level (2^11) and on both sides of a further pass; the first
+    oct at the ends of the range.  Exact."""
+    a = (W.splitmix64(logn, 3, 1 << logn) >> np.uint64(32)).astype(np.uint32)
+    a[:8] = np.array([0xFFFFFFFF, 0, 0xFFFFFFFF, 0xFFFFFFFF, 0, 0, 1, 0xFFFFFFFF], np.uint32)
+    say("f2sc full values logn", logn)
+    want_m, want_c = O.f2sc_prove(a, 60 + logn)
+    got_m, got_c = G().f2_sumcheck_prove(device_tensor(a), 60 + logn)
+    assert np.array_equal(got_m, want_m) and np.array_equal(got_c, want_c)
