@@ -3513,12 +3513,12 @@ int nif2_plan(u32 h, PfaPlan &pl) {
 }
 
 // Host inputs below p (checked here) copied to dst, or device inputs
-// range-checked into *flag.
+// range-checked into *flag (cleared here; check 0: by the caller's kernel).
 int nif2_inputs(const uint64_t *a, u64 n, int on_device, u64 *dst, u32 *flag, hipStream_t st,
-                const u64 **src) {
+                const u64 **src, bool check) {
     HIP_TRY(hipMemsetAsync(flag, 0, 4, st));
     if (on_device) {
-        LAUNCH(PC_NIF2, n * 8.0, launch_nif2_range(st, a, n, flag));
+        if (check) LAUNCH(PC_NIF2, n * 8.0, launch_nif2_range(st, a, n, flag));
         *src = a;
         return GKR_OK;
     }
@@ -3540,15 +3540,17 @@ extern "C" int nif2_prove(const uint64_t *a, uint64_t n, uint32_t h, int on_devi
     hipStream_t st = pick_stream(hip_stream);
     if (!st) return fail(GKR_ERR_DEVICE, "no stream");
     const u64 v = (n + h - 1) / h;
+    const bool lds = h <= NIF2_LDS_H;  // rows transformed in LDS, else a launch a pass over the grid in memory
     std::lock_guard<std::mutex> lk(g_nif2.mu);
     struct {
         u64 *W, *tw, *in, *msgs, *part;
-        u32 *flag;
+        u32 *flag, *pos;
     } b;
     auto lay = [&](Arena &ar) {
-        b.W = ar.take<u64>((u64)h * v);
-        b.part = ar.take<u64>(2ull * h * nif2_colsum_split(h, v));
+        b.W = ar.take<u64>(lds ? 1 : (u64)h * v);
+        b.part = ar.take<u64>(2ull * h * (lds ? nif2_lds_groups(h, v) : nif2_colsum_split(h, v)));
         b.tw = ar.take<u64>(h);
+        b.pos = ar.take<u32>(h);
         b.in = ar.take<u64>(on_device ? 1 : n);
         b.msgs = ar.take<u64>(2ull * h);
         b.flag = ar.take<u32>(1);
@@ -3561,12 +3563,17 @@ extern "C" int nif2_prove(const uint64_t *a, uint64_t n, uint32_t h, int on_devi
     ar.base = (char *)g_nif2.mem;
     lay(ar);
     const u64 *src = nullptr;
-    rc = nif2_inputs(a, n, on_device, b.in, b.flag, st, &src);
+    rc = nif2_inputs(a, n, on_device, b.in, b.flag, st, &src, !lds);
     if (rc) return rc;
     const u64 xi = fp::pow(NIF2_ROOT, (fp::P - 1) / (2ull * h));
-    LAUNCH(PC_NIF2, h * 8.0, launch_nif2_twist(st, h, xi, b.tw));
-    LAUNCH(PC_NIF2, (double)h * v * 8 * 2 * 2 * pl.nf, launch_nif2_transform(st, pl, src, n, v, b.tw, b.W));
-    LAUNCH(PC_NIF2, (double)h * v * 16, launch_nif2_colsum(st, pl, src, n, v, b.W, b.part, b.msgs));
+    if (lds) {
+        LAUNCH(PC_NIF2, n * 8.0 + 16.0 * h * nif2_lds_groups(h, v),
+               launch_nif2_rows_lds(st, pl, src, n, v, xi, b.pos, b.tw, b.part, b.msgs, b.flag));
+    } else {
+        LAUNCH(PC_NIF2, h * 8.0, launch_nif2_twist(st, h, xi, b.tw));
+        LAUNCH(PC_NIF2, (double)h * v * 8 * 2 * 2 * pl.nf, launch_nif2_transform(st, pl, src, n, v, b.tw, b.W));
+        LAUNCH(PC_NIF2, (double)h * v * 16, launch_nif2_colsum(st, pl, src, n, v, b.W, b.part, b.msgs));
+    }
     HIP_TRY(hipMemcpyAsync(g_nif2.h, b.msgs, 2ull * h * 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(g_nif2.h + 2ull * h, b.flag, 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -3614,7 +3621,7 @@ extern "C" int nif2_verify(const uint64_t *a, uint64_t n, uint32_t h, int on_dev
     ar.base = (char *)g_nif2.mem;
     lay(ar);
     const u64 *src = nullptr;
-    rc = nif2_inputs(a, n, on_device, b.in, b.flag, st, &src);
+    rc = nif2_inputs(a, n, on_device, b.in, b.flag, st, &src, true);
     if (rc) return rc;
     // the secret point, drawn before the stream is read
     u64 rs = fp::sm_state(seed, NIF2_PURPOSE);

@@ -153,6 +153,359 @@ hipError_t launch_nif2_transform(hipStream_t st, const PfaPlan &pl, const u64 *a
     return hipSuccess;
 }
 
+// ------------------------------------------------------- rows kept in LDS
+//
+// Rows of up to NIF2_LDS_H values (every row length of Table 3) go through
+// both transforms without leaving the chip: a workgroup takes a tile of TY
+// adjacent rows (their elements of a column are adjacent words), reads it
+// once, adds its squares into the even points' sums, runs the passes of both
+// transforms in LDS, and adds the squares of what is left into the odd
+// points' sums, kept in registers over all of the workgroup's tiles.  Against
+// a launch a pass with the grid in memory (six reads and six writes of 200 MB
+// for h = 2475, the columns read once more and the range check once before)
+// the grid is read once, and the time is the transforms' arithmetic: h = 2475
+// over 25 million values 795 -> 413 us a proof, this kernel 380 us with the
+// VALU issuing 82% of it (172 million wave instructions, 440 a value).
+//
+// A DFT of odd length F pairs x_m with x_{F-m}: with s = x_m + x_{F-m},
+// d = x_m - x_{F-m}, c_j = (w^j + w^-j) / 2 and t_j = (w^j - w^-j) / 2,
+//   X_k, X_{F-k} = (x_0 + sum_m s_m c_{mk}) +- sum_m d_m t_{mk},
+// (F-1)^2 / 2 products instead of F^2 (50 for 121 at F = 11); 25 is 5 x 5
+// with twiddles.  X_0 is a sum.
+constexpr int RB = 512;  // threads per workgroup of the row kernel
+
+struct Half {
+    u32 l, h;
+};
+struct RowArgs {
+    u32 h, nf, logty, ntiles;
+    u32 full;         // columns all of whose v rows hold values
+    u64 rem;          // rows of the next column that do
+    u32 F[NIF2_LDS_NF], stride[NIF2_LDS_NF];
+    u64 v;
+    const u64 *a;
+    const u32 *pos;   // column j's position (Good order)
+    const u64 *tw;    // by position: xi^k / h of coefficient k there (CRT order)
+    u64 *part;        // [workgroup][2][h], by position: even, odd points
+    u32 *flag;        // set when a value is not below p
+    u32 root_at[2 * NIF2_LDS_NF];  // per pass: its roots in `roots`
+    Half roots[NIF2_LDS_ROOTS];
+};
+
+//
+// The passes are bound by VALU instructions, so the products are sums over
+// halves: x = xh 2^31 + xl (xl < 2^31) makes a product the three sums
+// xl yl, xl yh + xh yl, xh yh of weights 1, 2^31, 2^62 = 2, four multiply-adds
+// and no carries while at most four terms are summed; a u128 sum takes 12
+// instructions a term.  Values between passes are congruent, not canonical,
+// and below 3 2^61 + 16; a folded value is below 2^61 + 8, its high half at
+// most 2^30.
+
+__device__ __forceinline__ Half halves(u64 x) { return {(u32)x & 0x7fffffffu, (u32)(x >> 31)}; }
+// (x mod 2^61) + (x >> 61) in three instructions (a multiply-add by 1 takes
+// the high bits without widening them).
+__device__ __forceinline__ u64 fold(u64 x) {
+    u32 t = (u32)(x >> 61);
+    x &= P;
+    asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(x) : "v"(t) : "vcc");
+    return x;
+}
+struct Sums {
+    u64 ll = 0, mm = 0, hh = 0;
+};
+// (a term is at most 2^62, 2^62, 2^60 + 2^31)
+__device__ __forceinline__ void mac(Sums &a, Half x, Half y) {
+    a.ll += (u64)x.l * y.l;
+    a.mm += (u64)x.l * y.h;
+    a.mm += (u64)x.h * y.l;
+    a.hh += (u64)x.h * y.h;
+}
+// The value of N <= 7 terms' sums plus x0 (below 2^62 + 32), below 2^61 + 8:
+// ll + mm 2^31 + 2 hh with 2^31 mm = (mm >> 30) + (mm mod 2^30) 2^31.  Before
+// the last fold: ll folded 2^61, x0 2^62, 2^34, 2^61 and 2 hh 2^63 for four
+// terms (folded first for more), below 2^64 together.
+template <int N>
+__device__ __forceinline__ u64 total(const Sums &a, u64 x0 = 0) {
+    const u64 t = fold(a.ll) + x0 + (a.mm >> 30) + (u64)((u32)a.mm & 0x3fffffffu) * 0x80000000u;
+    return fold(t + 2 * (N <= 4 ? a.hh : fold(a.hh)));
+}
+__device__ __forceinline__ u64 mul_lz(u64 x, Half y) {
+    Sums a;
+    mac(a, halves(fold(x)), y);
+    return total<1>(a);
+}
+
+// x := its DFT, c_j at rt[j - 1] for j <= M = (F-1)/2, t_j at rt[M + j - 1] for j < F.
+template <int F>
+__device__ __forceinline__ void dft_odd(u64 (&x)[F], const Half *rt) {
+    constexpr int M = (F - 1) / 2;
+    Half s[M], d[M];
+    const u64 x0 = fold(x[0]);
+    u64 tot = x0;
+#pragma unroll
+    for (int m = 1; m <= M; m++) {
+        const u64 sm = fold(x[m] + x[F - m]);  // (below 3 2^62 + 32 before)
+        s[m - 1] = halves(sm);
+        d[m - 1] = halves(fold(x[m] + (4 * P - x[F - m])));  // (below 3 2^61 + 2^63 + 16)
+        tot += sm;  // (M + 1 <= 7 values below 2^61 + 8: no overflow)
+    }
+#pragma unroll
+    for (int k = 1; k <= M; k++) {
+        Sums A, B;
+        u64 extra = x0;
+        int ta = 0;
+#pragma unroll
+        for (int m = 1; m <= M; m++) {
+            const int j = (m * k) % F;
+            if (j == 0) {  // (F = 9: c_0 = 1, t_0 = 0)
+                extra += ((u64)s[m - 1].h << 31) + s[m - 1].l;
+                continue;
+            }
+            if (ta++ == 4) {  // room for three more terms
+                A.ll = fold(A.ll);
+                A.mm = fold(A.mm);
+                B.ll = fold(B.ll);
+                B.mm = fold(B.mm);
+            }
+            mac(A, s[m - 1], rt[(j <= M ? j : F - j) - 1]);
+            mac(B, d[m - 1], rt[M + j - 1]);
+        }
+        const u64 p = total<M>(A, extra), q = total<M>(B);
+        x[k] = p + q;
+        x[F - k] = p + (2 * P - q);
+    }
+    x[0] = fold(tot);
+}
+
+// 25 = 5 x 5: n = 5 n1 + n2, k = k1 + 5 k2; the 5-point roots at rt, the
+// twiddles w^{n2 k1} (n2, k1 = 1..4) at rt + 6.  out(k, X_k) takes the results.
+template <typename Out>
+__device__ __forceinline__ void dft25(u64 (&x)[25], const Half *rt, Out out) {
+#pragma unroll
+    for (int n2 = 0; n2 < 5; n2++) {
+        u64 t[5] = {x[n2], x[5 + n2], x[10 + n2], x[15 + n2], x[20 + n2]};
+        dft_odd<5>(t, rt);
+        x[n2] = t[0];
+#pragma unroll
+        for (int k1 = 1; k1 < 5; k1++) x[5 * k1 + n2] = n2 ? mul_lz(t[k1], rt[6 + 4 * (n2 - 1) + k1 - 1]) : t[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 5; k1++) {
+        u64 t[5] = {x[5 * k1], x[5 * k1 + 1], x[5 * k1 + 2], x[5 * k1 + 3], x[5 * k1 + 4]};
+        dft_odd<5>(t, rt);
+#pragma unroll
+        for (int k2 = 0; k2 < 5; k2++) out(k1 + 5 * k2, t[k2]);
+    }
+}
+
+// One pass over the tile in LDS: the F-point DFT along a digit of stride s.
+template <int F>
+__device__ __forceinline__ void row_pass(u64 *W, u32 h, u32 s, u32 logty, const Half *rt, const u64 *tw) {
+    const u32 ty = 1u << logty, items = (h / F) << logty;
+    for (u32 it = threadIdx.x; it < items; it += RB) {
+        const u32 y = it & (ty - 1), l = it >> logty;
+        const u32 q = l / s, base = l - q * s + q * s * F;
+        const u32 step = s << logty;
+        u32 at = (base << logty) + y;
+        u64 x[F];
+#pragma unroll
+        for (int m = 0; m < F; m++) x[m] = W[at + m * step];
+        if (tw) {  // (uniform)
+#pragma unroll
+            for (int m = 0; m < F; m++) x[m] = mul_lz(x[m], halves(tw[base + m * s]));
+        }
+        asm("" : "+v"(at));  // the stores' addresses are formed again: F of them would be held in registers
+        if constexpr (F == 25) {
+            dft25(x, rt, [&](int k, u64 X) { W[at + k * step] = X; });
+        } else {
+            dft_odd<F>(x, rt);
+#pragma unroll
+            for (int m = 0; m < F; m++) W[at + m * step] = x[m];
+        }
+    }
+}
+
+// Squares of the tile's TY values at each of the thread's positions.
+template <int NC>
+__device__ __forceinline__ void square_sums(const u64 *W, u32 h, u32 logty, u64 (&acc)[NC]) {
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+        const u32 p = threadIdx.x + c * RB;
+        if (p < h) {
+            u64 t = acc[c];
+            for (u32 y = 0; y < (1u << logty); y += 4) {
+                Sums s;
+#pragma unroll
+                for (u32 i = 0; i < 4; i++) {
+                    const Half x = halves(fold(W[(p << logty) + y + i]));
+                    s.ll += (u64)x.l * x.l;
+                    s.mm += (u64)x.l * (2 * x.h);
+                    s.hh += (u64)x.h * x.h;
+                }
+                t = fold(t + total<4>(s));
+            }
+            acc[c] = t;
+        }
+    }
+}
+
+// NC: positions a thread accumulates, ceil(h / RB).
+template <int NC>
+__global__ void __launch_bounds__(RB, NC <= 5 ? 4 : 2) k_nif2_rows_lds(const RowArgs a) {
+    extern __shared__ u64 W[];
+    const u32 tid = threadIdx.x, ty = 1u << a.logty;
+    u64 even[NC], odd[NC];
+#pragma unroll
+    for (int c = 0; c < NC; c++) even[c] = odd[c] = 0;
+    // Adjacent tiles share cache lines, so workgroups of one XCD (equal
+    // blockIdx mod 8) take adjacent tiles.
+    const u32 xcd = blockIdx.x & 7, per = (a.ntiles + 7) / 8;
+    u64 bad = 0;
+    for (u32 k = blockIdx.x >> 3; k < per; k += gridDim.x >> 3) {
+        const u32 tile = xcd * per + k;
+        if (tile >= a.ntiles) break;  // (uniform)
+        const u64 y0 = (u64)tile << a.logty;
+        __syncthreads();  // the previous tile's sums are done with W
+        {
+            // column j of row y0 + y is a value while j < cols; a thread keeps
+            // its row and takes every dj-th column, eight loads in flight
+            const u32 y = tid & (ty - 1), dj = RB >> a.logty;
+            const u64 row = y0 + y;
+            const u32 cols = row < a.v ? a.full + (row < a.rem ? 1u : 0u) : 0u;
+            u32 j = tid >> a.logty;
+            const u64 *src = a.a + (u64)j * a.v + row;
+            const u64 step = (u64)dj * a.v;
+            constexpr u32 U = 8;
+            for (; j < a.h; j += U * dj, src += U * step) {
+                u64 x[U];
+                u32 p[U];
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    p[i] = j + i * dj < a.h ? a.pos[j + i * dj] : 0;
+                    x[i] = j + i * dj < cols ? src[i * step] : 0;
+                }
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    bad |= x[i] >= P;
+                    if (j + i * dj < a.h) W[(p[i] << a.logty) + y] = x[i];
+                }
+            }
+        }
+        __syncthreads();
+        square_sums<NC>(W, a.h, a.logty, even);
+        for (u32 q = 0; q < 2 * a.nf; q++) {
+            const u32 d = q < a.nf ? q : q - a.nf;
+            const Half *rt = a.roots + a.root_at[q];
+            const u64 *tw = q == a.nf ? a.tw : nullptr;
+            __syncthreads();
+            switch (a.F[d]) {
+#define RP(N) case N: row_pass<N>(W, a.h, a.stride[d], a.logty, rt, tw); break;
+                RP(3) RP(5) RP(7) RP(9) RP(11) RP(13) RP(25)
+#undef RP
+                default: break;
+            }
+        }
+        __syncthreads();
+        square_sums<NC>(W, a.h, a.logty, odd);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+        const u32 p = tid + c * RB;
+        if (p < a.h) {
+            a.part[(u64)blockIdx.x * 2 * a.h + p] = fp::canon(even[c]);
+            a.part[((u64)blockIdx.x * 2 + 1) * a.h + p] = fp::canon(odd[c]);
+        }
+    }
+    if (bad) a.flag[0] = 1;
+}
+
+// By position p: pos[Good(p)] = p and tw[p] = xi^CRT(p) / h.
+__global__ void k_nif2_tables(const PfaPlan pl, u64 xi, u64 hinv, u32 *pos, u64 *tw) {
+    const u32 p = blockIdx.x * NT + threadIdx.x;
+    if (p >= pl.h) return;
+    pos[good_index(pl, p)] = p;
+    tw[p] = mul(fp::pow(xi, crt_index(pl, p)), hinv);
+}
+
+// msgs[2j + o] = the sum over the workgroups of the parts at column j's
+// position (o: even or odd points); 32 threads share a position, 32 adjacent
+// positions a workgroup.
+__global__ void __launch_bounds__(1024) k_nif2_parts(const PfaPlan pl, const u64 *__restrict__ part, u32 nwg, u64 *msgs) {
+    __shared__ u64 sm[32][32];
+    const u32 t = threadIdx.x & 31, g = threadIdx.x >> 5, c = blockIdx.x * 32 + t;  // c = o h + position
+    u64 s = 0;
+    if (c < 2 * pl.h) {
+#pragma unroll 16
+        for (u32 w = g; w < nwg; w += 32) s = add(s, part[(u64)w * 2 * pl.h + c]);
+    }
+    sm[g][t] = s;
+    __syncthreads();
+    if (g == 0 && c < 2 * pl.h) {
+        for (u32 k = 1; k < 32; k++) s = add(s, sm[k][t]);
+        const u32 o = c >= pl.h;
+        msgs[2 * good_index(pl, o ? c - pl.h : c) + o] = s;
+    }
+}
+
+// Rows a tile holds: a power of two, 4 to 64, at most 80 KB of LDS (two
+// workgroups a CU: one loads while the other transforms), except that rows of
+// more than 2560 values take 160 KB with 4.
+static u32 tile_log(u32 h) {
+    u32 l = 2;
+    while (l < 6 && (u64)h * 8 * (2u << l) <= 80 * 1024) l++;
+    return l;
+}
+u32 nif2_lds_groups(u32 h, u64 v) {
+    const u64 tiles = (v + (1ull << tile_log(h)) - 1) >> tile_log(h);
+    const u64 lds = (u64)h * 8 << tile_log(h), most = 256 * std::min<u64>(4, 160 * 1024 / lds);
+    return (u32)((std::min<u64>(tiles, most) + 7) / 8 * 8);
+}
+
+hipError_t launch_nif2_rows_lds(hipStream_t st, const PfaPlan &pl, const u64 *a, u64 n, u64 v, u64 xi, u32 *pos,
+                                u64 *tw, u64 *part, u64 *msgs, u32 *flag) {
+    RowArgs r;
+    r.h = pl.h;
+    r.nf = pl.nf;
+    r.logty = tile_log(pl.h);
+    r.ntiles = (u32)((v + (1ull << r.logty) - 1) >> r.logty);
+    r.full = (u32)(n / v);
+    r.rem = n % v;
+    r.v = v;
+    r.a = a;
+    r.pos = pos;
+    r.tw = tw;
+    r.part = part;
+    r.flag = flag;
+    u32 at = 0;
+    const u64 half = 1ull << 60;  // 1/2
+    for (u32 q = 0; q < 2 * pl.nf; q++) {
+        const u32 d = q < pl.nf ? q : q - pl.nf, F = pl.F[d], f = F == 25 ? 5 : F, M = (f - 1) / 2;
+        const u64 w = q < pl.nf ? pl.winv[d] : pl.wfwd[d], wi = q < pl.nf ? pl.wfwd[d] : pl.winv[d];
+        const u64 u = F == 25 ? fp::pow(w, 5) : w, ui = F == 25 ? fp::pow(wi, 5) : wi;
+        r.F[d] = F;
+        r.stride[d] = pl.stride[d];
+        r.root_at[q] = at;
+        if (at + M + f - 1 + 16 > NIF2_LDS_ROOTS) return hipErrorInvalidValue;
+        auto put = [&](u64 c) { r.roots[at++] = Half{(u32)c & 0x7fffffffu, (u32)(c >> 31)}; };
+        for (u32 j = 1; j <= M; j++) put(mul(add(fp::pow(u, j), fp::pow(ui, j)), half));
+        for (u32 j = 1; j < f; j++) put(mul(sub(fp::pow(u, j), fp::pow(ui, j)), half));
+        if (F == 25)
+            for (u32 n2 = 1; n2 < 5; n2++)
+                for (u32 k1 = 1; k1 < 5; k1++) put(fp::pow(w, n2 * k1));
+    }
+    const u32 nwg = nif2_lds_groups(pl.h, v), lds = pl.h * 8u << r.logty;
+    hipLaunchKernelGGL(k_nif2_tables, dim3((pl.h + NT - 1) / NT), dim3(NT), 0, st, pl, xi, fp::inv(pl.h), pos, tw);
+    const u32 nc = (pl.h + RB - 1) / RB;
+#define RK(N) hipLaunchKernelGGL(k_nif2_rows_lds<N>, dim3(nwg), dim3(RB), lds, st, r)
+    if (nc <= 1) RK(1);
+    else if (nc <= 3) RK(3);
+    else if (nc <= 5) RK(5);
+    else RK(10);
+#undef RK
+    hipLaunchKernelGGL(k_nif2_parts, dim3((2 * pl.h + 31) / 32), dim3(1024), 0, st, pl, part, nwg, msgs);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------ reductions
 
 // Workgroup sum of one value per thread, returned to thread 0.

@@ -28,6 +28,16 @@ struct PfaPlan {
 // input a_i at i = j v + y for row y, column j (zero for i >= n).
 hipError_t launch_nif2_transform(hipStream_t st, const PfaPlan &pl, const u64 *a, u64 n, u64 v,
                                  const u64 *tw, u64 *W);
+// Rows of at most NIF2_LDS_H values: the whole proof msgs[0 .. 2h) with each
+// row transformed in LDS (no transform buffer), the range check included
+// (flag[0] = 1 if some a_i >= p).  pos: h, tw: h, part: nif2_lds_groups(h, v)
+// 2h words of scratch.
+constexpr u32 NIF2_LDS_H = 5120;
+constexpr int NIF2_LDS_NF = 4;      // factors of such an h (3 5 7 11 13 = 15015 is longer)
+constexpr int NIF2_LDS_ROOTS = 160; // words of roots: at most 22 a pass
+u32 nif2_lds_groups(u32 h, u64 v);
+hipError_t launch_nif2_rows_lds(hipStream_t st, const PfaPlan &pl, const u64 *a, u64 n, u64 v, u64 xi, u32 *pos,
+                                u64 *tw, u64 *part, u64 *msgs, u32 *flag);
 // msgs[k] = sum_y (value k of row y)^2, k < 2h: even k from a, odd from W;
 // each column is split over nif2_colsum_split(h, v) workgroups whose sums
 // go through part (2h times that many words).

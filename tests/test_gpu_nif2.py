@@ -94,3 +94,21 @@ def test_table3_size_properties(h):
     for seed in (1, 2):
         assert O.nif2_verify(a, h, seed, m) == (True, f2)
         assert G().nif2_verify(at, h, seed, m) == (True, f2)
+
+
+@pytest.mark.parametrize("n,h", [(17, 5), (7 * 100 + 3, 7), (11 * 70, 11), (13 * 64 + 1, 13), (63 * 65, 63),
+                                 (25 * 257 + 9, 25), (693 * 33 + 2, 693), (4095 * 5 + 17, 4095),
+                                 (5005 * 4 - 1, 5005), (17325 * 2 + 5, 17325)])
+def test_row_lengths_and_tile_edges(n, h):
+    """Every DFT length alone, rows of each tile height (64 down to 4) with
+    tiles one row short and one over, the longest row kept in LDS and one
+    beyond it; values over the whole field.  Exact."""
+    rng = np.random.default_rng(h)
+    a = rng.integers(0, P, n).astype(np.uint64)
+    a[: min(n, 4)] = np.array([P - 1, 0, P - 1, 1], np.uint64)[: min(n, 4)]
+    say("nif2 row lengths", "n", n, "h", h)
+    O.set_threads(oracle_threads())
+    want = O.nif2_prove(a, h)
+    got = G().nif2_prove(device_tensor(a), h)
+    bad = np.nonzero(got != want)[0]
+    assert len(bad) == 0, f"first differing values {bad[:5]} of {2 * h}"
