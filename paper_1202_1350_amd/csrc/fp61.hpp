@@ -72,7 +72,21 @@ __host__ __device__ __forceinline__ u64 pow(u64 a, u64 e) {
     return r;
 }
 
-__host__ __device__ __forceinline__ u64 inv(u64 a) { return pow(a, P - 2); }
+// a^(2^k), then times b
+__host__ __device__ __forceinline__ u64 sq_mul(u64 a, int k, u64 b) {
+    for (; k; k--) a = mul(a, a);
+    return mul(a, b);
+}
+
+// a^(p - 2), p - 2 = 4 (2^59 - 1) + 1: exponents 2^e - 1 for e = 2, 3, 6, 7,
+// 14, 28, 29, 58, 59, each from the last (70 products in a chain; square and
+// multiply takes 121).
+__host__ __device__ __forceinline__ u64 inv(u64 a) {
+    const u64 e2 = sq_mul(a, 1, a), e3 = sq_mul(e2, 1, a), e6 = sq_mul(e3, 3, e3), e7 = sq_mul(e6, 1, a);
+    const u64 e14 = sq_mul(e7, 7, e7), e28 = sq_mul(e14, 14, e14), e29 = sq_mul(e28, 1, a);
+    const u64 e58 = sq_mul(e29, 29, e29);
+    return sq_mul(sq_mul(e58, 1, a), 2, a);
+}
 
 // ---------------------------------------------------------------------------
 // SplitMix64 (Steele, Lea, Flood, OOPSLA 2014): the verifier's coin stream.

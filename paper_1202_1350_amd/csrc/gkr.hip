@@ -2583,10 +2583,9 @@ int vs_reserve(size_t bytes, size_t host_words) {
 // VCHUNK values are copied from the
 // caller's memory into two device buffers on a copy stream, chunk k into
 // buffer k & 1 once the kernels that read that buffer before have finished;
-// the caller's stream checks the chunk against p (u64 values, into *bad_dev)
-// and adds its extension terms into the same per-workgroup rows while chunk
-// k + 1 is copied.  Chunks start at multiples of VCHUNK, a multiple of 2^L
-// for every table here (L <= 16).
+// the caller's stream checks the chunk against p (u64 values, into *bad)
+// and adds its extension terms into the same per-workgroup sums while chunk
+// k + 1 is copied.
 constexpr u64 VCHUNK = 1ull << 23;
 
 struct InputStream {  // one per device, created on first use, kept until exit
@@ -2599,8 +2598,8 @@ InputStream g_is[IS_DEVICES];
 
 // dbuf: device room for 2 min(n, VCHUNK) values.
 template <typename T>
-static int stream_mle(hipStream_t st, const T *in, u64 n, T *dbuf, const u64 *lo, const u64 *hi, u32 L,
-                      u64 *partials, int *nb, u32 *bad_dev) {
+static int stream_mle(hipStream_t st, const T *in, u64 n, T *dbuf, const MlePoint &pt, u64 *partials, int *nb,
+                      u32 *bad) {
     std::lock_guard<std::mutex> lk(g_is_mu);
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -2614,7 +2613,7 @@ static int stream_mle(hipStream_t st, const T *in, u64 n, T *dbuf, const u64 *lo
         }
     }
     const u64 C = std::min<u64>(n, VCHUNK);
-    const int nbf = blocks_for(C, 8);
+    *nb = mle_blocks(C);
     u64 k = 0;
     for (u64 x0 = 0; x0 < n; x0 += C, k++) {
         const int b = (int)(k & 1);
@@ -2625,8 +2624,7 @@ static int stream_mle(hipStream_t st, const T *in, u64 n, T *dbuf, const u64 *lo
         HIP_TRY(hipStreamWaitEvent(st, is.copied[b], 0));
         const u64 *t64 = sizeof(T) == 8 ? (const u64 *)(dbuf + b * C) : nullptr;
         const u32 *t32 = sizeof(T) == 4 ? (const u32 *)(dbuf + b * C) : nullptr;
-        if (t64) HIP_TRY(launch_check_range(st, t64, m, bad_dev));
-        HIP_TRY(launch_mle(st, m, t64, t32, lo, hi + (x0 >> L), L, partials, nb, k > 0, nbf));
+        HIP_TRY(launch_mle(st, m, t64, t32, pt, x0, partials, *nb, k > 0, bad));
         HIP_TRY(hipEventRecord(is.used[b], st));
     }
     return GKR_OK;
@@ -2705,7 +2703,6 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
     std::copy(z[d].begin(), z[d].end(), pts.begin() + c->n_chals);
     HIP_TRY(hipMemcpyAsync(v.pts, pts.data(), npts * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemsetAsync(v.flag, 0, 4, st));
-    if (inputs_on_device) LAUNCH(PC_MISC, Sd * 8.0, launch_check_range(st, inputs, Sd, v.flag));
     u64 *T = v.tab;
     int nb = 0;
     const bool closed = g_closed_forms.load() != 0;
@@ -2740,14 +2737,15 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
         LAUNCH(PC_MISC, 0, launch_reduce_rows(st, nb, 2, v.partials, v.res + 2 * i));
     }
     {
-        const u32 sd = c->s[d];
-        u32 Ld;
-        split_half(sd, &Ld);
-        LAUNCH(PC_TABLES, 0, launch_eq_halves(st, v.pts + c->n_chals, sd, Ld, T, T + HALF_MAX));
+        MlePoint pt;
+        memset(&pt, 0, sizeof pt);
+        pt.s = c->s[d];
+        for (u32 k = 0; k < pt.s; k++) pt.r[k] = z[d][k];
+        nb = mle_blocks(Sd);
         if (inputs_on_device) {
-            LAUNCH(PC_MLE, Sd * 8.0, launch_mle(st, Sd, inputs, nullptr, T, T + HALF_MAX, Ld, v.partials, &nb));
+            LAUNCH(PC_MLE, Sd * 8.0, launch_mle(st, Sd, inputs, nullptr, pt, 0, v.partials, nb, 0, v.flag));
         } else {
-            rc = stream_mle<u64>(st, inputs, Sd, v.in, T, T + HALF_MAX, Ld, v.partials, &nb, v.flag);
+            rc = stream_mle<u64>(st, inputs, Sd, v.in, pt, v.partials, &nb, v.flag);
             if (rc) return rc;
         }
         LAUNCH(PC_MISC, 0, launch_reduce_rows(st, nb, 1, v.partials, v.res + 2 * d));
@@ -3012,39 +3010,32 @@ extern "C" int f2_sumcheck_verify(const uint32_t *freq, uint64_t n, int on_devic
     // ~a(r) on the device, one pass over the vector (the verifier's secret,
     // Sec. 4.1.2; its pass parallel over the input symbols, Sec. 4.2.2)
     std::lock_guard<std::mutex> lk(g_f2.mu);
-    struct {
-        u64 *pts, *tab, *partials, *res;
-        u32 *in;
-    } v;
-    auto lay = [&](Arena &a) {
-        v.pts = a.take<u64>(l + 1);
-        v.tab = a.take<u64>(2ull * HALF_MAX);
-        v.partials = a.take<u64>((u64)MAX_BLOCKS);
-        v.res = a.take<u64>(1);
-        v.in = a.take<u32>(on_device ? 1 : 2 * std::min<u64>(n, VCHUNK));
-    };
-    Arena sz;
+    // the workgroups' sums go straight to pinned host memory, added up here
+    Arena sz, a;
+    auto lay = [&](Arena &x) { return x.take<u32>(on_device ? 1 : 2 * std::min<u64>(n, VCHUNK)); };
+    auto layp = [&](Arena &x) { return x.take<u64>(MLE_BLOCKS); };
     lay(sz);
-    int rc = f2_reserve(sz.used, 2);
+    layp(sz);
+    int rc = f2_reserve(sz.used, MLE_BLOCKS);
     if (rc) return rc;
-    Arena a;
     a.base = (char *)g_f2.mem;
-    lay(a);
-    if (l) HIP_TRY(hipMemcpyAsync(v.pts, r.data(), l * 8ull, hipMemcpyHostToDevice, st));
-    u32 L;
-    split_half(l, &L);
-    int nb = 0;
-    LAUNCH(PC_TABLES, 0, launch_eq_halves(st, v.pts, l, L, v.tab, v.tab + HALF_MAX));
+    u32 *in = lay(a);
+    u64 *dpart = layp(a);
+    MlePoint pt;
+    memset(&pt, 0, sizeof pt);
+    pt.s = l;
+    for (u32 k = 0; k < l; k++) pt.r[k] = r[k];
+    int nb = mle_blocks(n);
     if (on_device) {
-        LAUNCH(PC_MLE, n * 4.0, launch_mle(st, n, nullptr, freq, v.tab, v.tab + HALF_MAX, L, v.partials, &nb));
+        LAUNCH(PC_MLE, n * 4.0, launch_mle(st, n, nullptr, freq, pt, 0, g_f2.h, nb, 0, nullptr));
     } else {
-        rc = stream_mle<u32>(st, freq, n, v.in, v.tab, v.tab + HALF_MAX, L, v.partials, &nb, nullptr);
+        rc = stream_mle<u32>(st, freq, n, in, pt, dpart, &nb, nullptr);
         if (rc) return rc;
+        HIP_TRY(hipMemcpyAsync(g_f2.h, dpart, nb * 8ull, hipMemcpyDeviceToHost, st));
     }
-    LAUNCH(PC_MISC, 0, launch_reduce_rows(st, nb, 1, v.partials, v.res));
-    HIP_TRY(hipMemcpyAsync(g_f2.h, v.res, 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    const u64 ar = g_f2.h[0];
+    u64 ar = 0;
+    for (int k = 0; k < nb; k++) ar = add(ar, g_f2.h[k]);
     if (mul(ar, ar) != claim) {
         reject(accepted, why, -1, -1, GKR_CHECK_INPUT);
         return GKR_OK;
@@ -3597,47 +3588,43 @@ extern "C" int nif2_verify(const uint64_t *a, uint64_t n, uint32_t h, int on_dev
     hipStream_t st = pick_stream(hip_stream);
     if (!st) return fail(GKR_ERR_DEVICE, "no stream");
     const u64 v = (n + h - 1) / h;
-    const u32 nch = (h + 31) / 32;
+    const u32 nb = nif2_rowsum_blocks(v);
     std::lock_guard<std::mutex> lk(g_nif2.mu);
     struct {
-        u64 *L, *L2, *part, *blk, *out, *in, *msgs;
-        u32 *flag;
+        u64 *L, *in;
     } b;
     auto lay = [&](Arena &ar) {
-        b.L = ar.take<u64>(h);
-        b.L2 = ar.take<u64>(2ull * h);
-        b.part = ar.take<u64>((u64)nch * v);
-        b.blk = ar.take<u64>(1024);
-        b.out = ar.take<u64>(2);
+        b.L = ar.take<u64>(3ull * h);
         b.in = ar.take<u64>(on_device ? 1 : n);
-        b.msgs = ar.take<u64>(2ull * h);
-        b.flag = ar.take<u32>(1);
     };
     Arena sz;
     lay(sz);
-    rc = nif2_reserve(sz.used, 2ull * h + 3);
+    // pinned host words: the proof (read by the kernel), the sums and the
+    // range flag (written by it)
+    rc = nif2_reserve(sz.used, 2ull * h + NIF2_ROW_BLOCKS + 1);
     if (rc) return rc;
     Arena ar;
     ar.base = (char *)g_nif2.mem;
     lay(ar);
-    const u64 *src = nullptr;
-    rc = nif2_inputs(a, n, on_device, b.in, b.flag, st, &src, true);
-    if (rc) return rc;
+    u64 *hmsgs = g_nif2.h, *out = hmsgs + 2ull * h, *hflag = out + NIF2_ROW_BLOCKS;
+    const u64 *src = a;
+    if (!on_device) {
+        for (u64 i = 0; i < n; i++)
+            if (a[i] >= fp::P) return fail(GKR_ERR_RANGE, "input value not below p");
+        HIP_TRY(hipMemcpyAsync(b.in, a, n * 8, hipMemcpyHostToDevice, st));
+        src = b.in;
+    }
     // the secret point, drawn before the stream is read
     u64 rs = fp::sm_state(seed, NIF2_PURPOSE);
     const u64 r = fp::sm_field(rs);
     const u64 w = fp::pow(NIF2_ROOT, (fp::P - 1) / h), xi = fp::pow(NIF2_ROOT, (fp::P - 1) / (2ull * h));
-    memcpy(g_nif2.h, msgs, 2ull * h * 8);
-    HIP_TRY(hipMemcpyAsync(b.msgs, g_nif2.h, 2ull * h * 8, hipMemcpyHostToDevice, st));
-    LAUNCH(PC_NIF2, h * 8.0, launch_nif2_basis(st, w, h, r, b.L));
-    LAUNCH(PC_NIF2, n * 8.0 + (double)nch * v * 16, launch_nif2_rows(st, src, n, v, h, b.L, b.part, b.blk, b.out));
-    LAUNCH(PC_NIF2, 2.0 * h * 8, launch_nif2_basis(st, xi, 2ull * h, r, b.L2));
-    LAUNCH(PC_NIF2, 2.0 * h * 16, launch_nif2_dot(st, b.msgs, b.L2, 2ull * h, b.blk, b.out + 1));
-    HIP_TRY(hipMemcpyAsync(g_nif2.h, b.out, 16, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(g_nif2.h + 2, b.flag, 4, hipMemcpyDeviceToHost, st));
+    memcpy(hmsgs, msgs, 2ull * h * 8);
+    LAUNCH(PC_NIF2, n * 8.0 + 5.0 * h * 8, launch_nif2_verify(st, src, n, v, h, w, xi, r, b.L, hmsgs, out, (u32 *)hflag));
     HIP_TRY(hipStreamSynchronize(st));
-    if (*(const u32 *)(g_nif2.h + 2)) return fail(GKR_ERR_RANGE, "input value not below p");
-    *accepted = g_nif2.h[0] == g_nif2.h[1];
+    if (*(const u32 *)hflag) return fail(GKR_ERR_RANGE, "input value not below p");
+    u64 rows = 0;
+    for (u32 k = 1; k < nb; k++) rows = fp::add(rows, out[k]);
+    *accepted = rows == out[0];
     if (f2) {
         u64 s = 0;
         for (u64 j = 0; j < h; j++) s = fp::add(s, msgs[2 * j]);

@@ -32,11 +32,6 @@ inline int blocks_for(u64 n, u64 per = 1) {
     return (int)b;
 }
 
-// ---- evaluation (a3) ------------------------------------------------------
-hipError_t launch_load_inputs(hipStream_t st, const u64 *src, u32 S, u64 npad, u64 *V,
-                              u32 *bad_flag);
-// *bad_flag |= 1 if some src[g] >= p, g < n.
-hipError_t launch_check_range(hipStream_t st, const u64 *src, u64 n, u32 *bad_flag);
 // ---- proof bookkeeping ----------------------------------------------------
 // eq half tables of a point pt[0..s): lo[x] = chi_x(pt[0..L)) for x < 2^L,
 // hi[y] = chi_y(pt[L..s)) for y < 2^{s-L}; chi_x(pt) = lo[x & (2^L-1)] * hi[x >> L].
@@ -58,14 +53,18 @@ struct WiringArgs {
     u64 *partials;
 };
 hipError_t launch_wiring(hipStream_t st, const WiringArgs &a, int *nblocks);
-// Multilinear extension of T (n values, u64 or u32) at the point with half
-// tables lo / hi (entry x weighs lo[x mod 2^L] hi[x >> L]): per-workgroup
-// partial sums, stored, or added to the rows already there (accumulate), on
-// nb_fixed workgroups (0: sized for n).  A chunk of a longer table starting
-// at a multiple of 2^L passes hi advanced by its start >> L.
-hipError_t launch_mle(hipStream_t st, u64 n, const u64 *T64, const u32 *T32, const u64 *lo,
-                      const u64 *hi, u32 L, u64 *partials, int *nblocks, int accumulate = 0,
-                      int nb_fixed = 0);
+// Multilinear extension of T (n values, u64 or u32) at the point pt (s
+// coordinates, the others 0): partial sums of nb workgroups, stored, or added
+// to the sums already there (accumulate).  A chunk of a longer table starts
+// at x0, a multiple of 2^12.  *bad = 1 if a u64 value is not below p.
+struct MlePoint {
+    u32 s;
+    u64 r[36];
+};
+constexpr int MLE_BLOCKS = 2048;
+int mle_blocks(u64 n);
+hipError_t launch_mle(hipStream_t st, u64 n, const u64 *T64, const u32 *T32, const MlePoint &pt, u64 x0, u64 *partials,
+                      int nb, int accumulate, u32 *bad);
 // Fold nparts rows of K partial sums into out[0..K).
 hipError_t launch_reduce_rows(hipStream_t st, int nparts, int K, const u64 *partials, u64 *out);
 

@@ -508,14 +508,14 @@ hipError_t launch_nif2_rows_lds(hipStream_t st, const PfaPlan &pl, const u64 *a,
 
 // ------------------------------------------------------------ reductions
 
-// Workgroup sum of one value per thread, returned to thread 0.
+// Sum of one value per thread over the first NT threads, returned to thread 0.
 __device__ __forceinline__ u64 group_sum(u64 v) {
     __shared__ u64 sm[NT / 64];
     for (int o = 32; o > 0; o >>= 1) {
         const int lo = __shfl_down((int)(u32)v, o), hi = __shfl_down((int)(u32)(v >> 32), o);
         v = add(v, ((u64)(u32)hi << 32) | (u32)lo);
     }
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < NT) sm[threadIdx.x >> 6] = v;
     __syncthreads();
     u64 t = 0;
     if (threadIdx.x == 0)
@@ -596,82 +596,96 @@ hipError_t launch_nif2_twist(hipStream_t st, u32 h, u64 xi, u64 *tw) {
 
 // ------------------------------------------------------------- verifier
 
-// L[j] = w^j (r^N - 1) / (N (r - w^j)), or [w^j == r] when r^N = 1.
-__global__ void k_nif2_basis(u64 w, u64 N, u64 r, u64 rN1, u64 *L) {
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
-    if (j >= N) return;
-    const u64 wj = fp::pow(w, j);
-    if (rN1 == 0) {
-        L[j] = wj == r ? 1 : 0;
-        return;
-    }
-    L[j] = mul(mul(wj, rN1), fp::inv(mul(N % P, sub(r, wj))));
+// The Lagrange bases at r of the order-h subgroup <w> (L[j], j < h) and the
+// order-2h subgroup <xi> (L[h + k], k < 2h): w^j (r^N - 1) / (N (r - w^j)), or
+// [w^j == r] when r^N = 1.  Clears the flag as well.
+__global__ void k_nif2_bases(u64 w, u64 xi, u64 h, u64 r, u64 rh1, u64 r2h1, u64 *L, u32 *flag) {
+    const u64 t = (u64)blockIdx.x * NT + threadIdx.x;
+    if (t == 0) *flag = 0;
+    if (t >= 3 * h) return;
+    const u64 N = t < h ? h : 2 * h, rN1 = t < h ? rh1 : r2h1;
+    const u64 wj = t < h ? fp::pow(w, t) : fp::pow(xi, t - h);
+    if (rN1 == 0)
+        L[t] = wj == r ? 1 : 0;
+    else
+        L[t] = mul(mul(wj, rN1), fp::inv(mul(N % P, sub(r, wj))));
 }
 
-hipError_t launch_nif2_basis(hipStream_t st, u64 w, u64 N, u64 r, u64 *L) {
-    const u64 rN1 = sub(fp::pow(r, N), 1);
-    hipLaunchKernelGGL(k_nif2_basis, dim3((u32)((N + NT - 1) / NT)), dim3(NT), 0, st, w, N, r, rN1, L);
-    return hipGetLastError();
-}
-
-constexpr u32 RCH = 32;  // columns per partial row evaluation (32 products < 2^127)
-
-// part[c v + y] = sum_{j in chunk c} a(j, y) L[j]
-__global__ void __launch_bounds__(NT) k_nif2_rowpart(const u64 *__restrict__ a, u64 n, u64 v, u32 h,
-                                                     const u64 *__restrict__ L, u64 *part) {
-    const u64 nch = (h + RCH - 1) / RCH, total = nch * v;
-    for (u64 gid = (u64)blockIdx.x * NT + threadIdx.x; gid < total; gid += (u64)gridDim.x * NT) {
-        const u64 y = gid % v, c = gid / v;
-        u128 acc = 0;
-        for (u64 j = c * RCH; j < std::min<u64>(h, (c + 1) * RCH); j++) {
-            const u64 i = j * v + y;
-            acc += fp::wide(i < n ? a[i] : 0, L[j]);
+// Verifier's pass over the grid: out[1 + b] = the sum over workgroup b's rows
+// y of (sum_j a(j, y) L[j])^2, and out[0] = sum_k msgs[k] L[h + k] (workgroup
+// 0).  RW adjacent rows at a time, RB / RW threads a row taking every
+// (RB / RW)-th column, eight loads in flight; values are checked against p as
+// they pass.  One read of the grid: 200 MB in 37 us at h = 585 (a range check,
+// a pass of 32-column parts and their squares before: 72 us in three).
+template <int RW>
+__global__ void __launch_bounds__(RB) k_nif2_rowsum(const u64 *__restrict__ a, u32 h, u32 full, u64 rem, u64 v,
+                                                    const u64 *__restrict__ L, const u64 *__restrict__ msgs, u64 *out,
+                                                    u32 *flag) {
+    constexpr u32 G = RB / RW, U = 8;
+    __shared__ u64 sm[G][RW];
+    const u32 tid = threadIdx.x, y = tid % RW, g = tid / RW;
+    u64 s = 0;
+    if (blockIdx.x == 0) {
+        for (u32 k = tid; k < 2 * h; k += RB) s = add(s, mul(msgs[k], L[h + k]));
+    } else {
+        u64 bad = 0;
+        for (u64 y0 = (u64)(blockIdx.x - 1) * RW; y0 < v; y0 += (u64)(gridDim.x - 1) * RW) {
+            const u64 row = y0 + y;
+            const u32 cols = row < v ? full + (row < rem ? 1u : 0u) : 0u;
+            u64 t = 0;
+            for (u32 j0 = g; j0 < cols; j0 += G * U) {
+                u64 x[U], w[U];
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    const u32 j = j0 + i * G;
+                    x[i] = j < cols ? a[(u64)j * v + row] : 0;
+                    w[i] = j < cols ? L[j] : 0;
+                }
+                u128 acc = 0;
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    bad |= x[i] >= P;
+                    acc += fp::wide(x[i], w[i]);
+                }
+                t = add(t, fp::red128(acc));
+            }
+            __syncthreads();  // the previous rows' sums are read
+            sm[g][y] = t;
+            __syncthreads();
+            if (tid < RW) {
+                for (u32 k = 1; k < G; k++) t = add(t, sm[k][y]);
+                s = add(s, mul(t, t));
+            }
         }
-        part[c * v + y] = fp::red128(acc);
+        if (bad) *flag = 1;
     }
-}
-
-// blk[b] = sum over this workgroup's rows y of (sum_c part[c v + y])^2
-__global__ void __launch_bounds__(NT) k_nif2_rowsq(const u64 *__restrict__ part, u64 v, u32 nch, u64 *blk) {
-    u64 s = 0;
-    for (u64 y = (u64)blockIdx.x * NT + threadIdx.x; y < v; y += (u64)gridDim.x * NT) {
-        u64 t = 0;
-        for (u32 c = 0; c < nch; c++) t = add(t, part[(u64)c * v + y]);
-        s = add(s, mul(t, t));
-    }
+    // (RB threads; NT of them hold a group_sum)
+    __shared__ u64 half[RB - NT];
+    __syncthreads();
+    if (tid >= NT) half[tid - NT] = s;
+    __syncthreads();
+    if (tid < RB - NT) s = add(s, half[tid]);
     s = group_sum(s);
-    if (threadIdx.x == 0) blk[blockIdx.x] = s;
+    if (tid == 0) out[blockIdx.x] = s;
 }
 
-__global__ void __launch_bounds__(NT) k_nif2_sum(const u64 *__restrict__ x, u64 cnt, u64 *out) {
-    u64 s = 0;
-    for (u64 i = threadIdx.x; i < cnt; i += NT) s = add(s, x[i]);
-    s = group_sum(s);
-    if (threadIdx.x == 0) out[0] = s;
+u32 nif2_rowsum_blocks(u64 v) {
+    const u64 rw = v >= 64 * 512 ? 64 : 16, b = (v + rw - 1) / rw;
+    return 1 + (u32)std::min<u64>(b, NIF2_ROW_BLOCKS - 1);
 }
 
-hipError_t launch_nif2_rows(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, const u64 *L, u64 *part,
-                            u64 *blk, u64 *out) {
-    const u32 nch = (h + RCH - 1) / RCH;
-    hipLaunchKernelGGL(k_nif2_rowpart, dim3(grid_of((u64)nch * v)), dim3(NT), 0, st, a, n, v, h, L, part);
-    const u32 nb = (u32)std::min<u64>(1024, (v + NT - 1) / NT);
-    hipLaunchKernelGGL(k_nif2_rowsq, dim3(nb), dim3(NT), 0, st, part, v, nch, blk);
-    hipLaunchKernelGGL(k_nif2_sum, dim3(1), dim3(NT), 0, st, blk, (u64)nb, out);
-    return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(NT) k_nif2_dot(const u64 *__restrict__ x, const u64 *__restrict__ y, u64 N,
-                                                 u64 *blk) {
-    u64 s = 0;
-    for (u64 k = (u64)blockIdx.x * NT + threadIdx.x; k < N; k += (u64)gridDim.x * NT) s = add(s, mul(x[k], y[k]));
-    s = group_sum(s);
-    if (threadIdx.x == 0) blk[blockIdx.x] = s;
-}
-
-hipError_t launch_nif2_dot(hipStream_t st, const u64 *msgs, const u64 *L2, u64 N, u64 *blk, u64 *out) {
-    const u32 nb = (u32)std::min<u64>(1024, (N + NT - 1) / NT);
-    hipLaunchKernelGGL(k_nif2_dot, dim3(nb), dim3(NT), 0, st, msgs, L2, N, blk);
-    hipLaunchKernelGGL(k_nif2_sum, dim3(1), dim3(NT), 0, st, blk, (u64)nb, out);
+hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, u64 w, u64 xi, u64 r, u64 *L,
+                              const u64 *msgs, u64 *out, u32 *flag) {
+    const u64 rh = fp::pow(r, h);
+    hipLaunchKernelGGL(k_nif2_bases, dim3((3 * h + NT - 1) / NT), dim3(NT), 0, st, w, xi, (u64)h, r, sub(rh, 1),
+                       sub(mul(rh, rh), 1), L, flag);
+    const dim3 g(nif2_rowsum_blocks(v));
+    const u32 full = (u32)(n / v);
+    const u64 rem = n % v;
+    if (v >= 64 * 512)
+        hipLaunchKernelGGL(k_nif2_rowsum<64>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
+    else
+        hipLaunchKernelGGL(k_nif2_rowsum<16>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
     return hipGetLastError();
 }
 

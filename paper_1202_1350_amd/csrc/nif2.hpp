@@ -46,14 +46,14 @@ hipError_t launch_nif2_colsum(hipStream_t st, const PfaPlan &pl, const u64 *a, u
                               const u64 *W, u64 *part, u64 *msgs);
 // tw[k] = xi^k / h, k < h.
 hipError_t launch_nif2_twist(hipStream_t st, u32 h, u64 xi, u64 *tw);
-// L[j] = Lagrange basis of the order-N subgroup generated by w, at r.
-hipError_t launch_nif2_basis(hipStream_t st, u64 w, u64 N, u64 r, u64 *L);
-// out[0] = sum_y (sum_j a(j, y) L[j])^2 (part: ceil(h / 32) v scratch words,
-// blk: scratch of 1024 words).
-hipError_t launch_nif2_rows(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, const u64 *L, u64 *part,
-                            u64 *blk, u64 *out);
-// out[0] = sum_k msgs[k] L2[k], k < N.
-hipError_t launch_nif2_dot(hipStream_t st, const u64 *msgs, const u64 *L2, u64 N, u64 *blk, u64 *out);
+// The verifier at the secret r: out[0] = the value at r of the polynomial
+// through the 2h proof values msgs (device-visible), and out[1 ..
+// nif2_rowsum_blocks(v)) add up to sum_y f_y(r)^2; *flag = 1 if some a_i >= p
+// (cleared first).  L: 3h scratch words.
+constexpr u32 NIF2_ROW_BLOCKS = 1024;
+u32 nif2_rowsum_blocks(u64 v);
+hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, u64 w, u64 xi, u64 r, u64 *L,
+                              const u64 *msgs, u64 *out, u32 *flag);
 // flag[0] = 1 if some a_i >= p.
 hipError_t launch_nif2_range(hipStream_t st, const u64 *a, u64 n, u32 *flag);
 

@@ -1,0 +1,70 @@
+"""The verifiers' one pass over device inputs: sizes at the edges of its
+tiles, and inputs that do not start on a 16-byte boundary.  The verdicts are
+exact: the honest transcript is accepted, one changed input is rejected."""
+import numpy as np
+import pytest
+
+from gpu_util import say, device_tensor
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+P = (1 << 61) - 1
+
+
+def G():
+    import paper_1202_1350_amd as mod
+    return mod
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 3, 1023, 1025, 2047, 2049, 70001])
+def test_circuit_inputs(n, offset):
+    c = G().Circuit.from_workload(W.f2_circuit(n))
+    x = W.splitmix64(n, 1, n) % np.uint64(P)
+    x[-1] = P - 1
+    # (out-of-range words around the values must not be read; offset 1 starts
+    # them one word past a 16-byte boundary)
+    bad = np.full(4, 2 ** 64 - 1, np.uint64)
+    t = device_tensor(np.concatenate([bad[:2 + offset], x, bad]))[2 + offset:2 + offset + n]
+    say("verify inputs n", n, "offset", offset)
+    msgs, _ = G().gkr_prove(c, x, 5)
+    assert G().gkr_verify(c, t, 5, msgs)[0]
+    y = x.copy()
+    y[n // 2] = (int(y[n // 2]) + 1) % P
+    assert not G().gkr_verify(c, device_tensor(y), 5, msgs)[0]
+    y[n // 2] = P
+    with pytest.raises(G().GkrError) as e:
+        G().gkr_verify(c, device_tensor(y), 5, msgs)
+    assert e.value.code == G().GKR_ERR_RANGE
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("logn", [0, 1, 10, 11, 12, 17])
+def test_counts(logn, offset):
+    n = 1 << logn
+    a = (W.splitmix64(logn, 3, n) >> np.uint64(32)).astype(np.uint32)
+    buf = device_tensor(np.concatenate([np.zeros(offset, np.uint32), a]))
+    say("verify counts log n", logn, "offset", offset)
+    msgs, _ = G().f2_sumcheck_prove(a, 6)
+    assert G().f2_sumcheck_verify(buf[offset:], 6, msgs) == (True, -1, 0)
+    b = a.copy()
+    b[n // 3] ^= 1
+    assert not G().f2_sumcheck_verify(device_tensor(b), 6, msgs)[0]
+
+
+@pytest.mark.parametrize("n,h", [(64 * 512 * 9 - 1, 9), (64 * 512 * 9 + 10, 9), (2475 * 17, 2475)])
+def test_rows(n, h):
+    """Rows on both sides of the change of rows a workgroup takes at a time."""
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, P, n).astype(np.uint64)
+    say("verify rows n", n, "h", h)
+    t = device_tensor(a)
+    m = G().nif2_prove(t, h)
+    f2 = sum(int(m[2 * j]) for j in range(h)) % P
+    assert G().nif2_verify(t, h, 3, m) == (True, f2)
+    a[n // 2] = (int(a[n // 2]) + 1) % P
+    assert not G().nif2_verify(device_tensor(a), h, 3, m)[0]
+    a[n - 1] = P
+    with pytest.raises(G().GkrError) as e:
+        G().nif2_verify(device_tensor(a), h, 3, m)
+    assert e.value.code == G().GKR_ERR_RANGE
