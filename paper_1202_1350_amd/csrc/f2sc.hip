@@ -15,7 +15,7 @@
 // 1.6 GB, in 6 launches instead of 16 (proof 412 -> 180 us; 2^10 counts,
 // one launch instead of four and no copies, 42 -> 25 us).
 #include "f2sc.hpp"
-#include "fp61.hpp"
+#include "lanes.hpp"
 
 namespace gkr {
 
@@ -32,38 +32,6 @@ constexpr int FW = FB / 64;       // waves
 constexpr int OCT = 8;            // lanes sharing an oct, one entry each
 constexpr int SLOTS = 5;          // Gram sums a lane keeps
 static_assert(OCT * SLOTS == F2SC_ROW, "a row holds every lane's slots");
-
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ u64 dppx(u64 v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(u32)v, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u32)(v >> 32), CTRL, ROWS, 0xf, true);
-    return ((u64)(u32)hi << 32) | (u64)(u32)lo;
-}
-__device__ __forceinline__ u64 from1(u64 v) { return dppx<0xB1>(v); }   // lane ^ 1
-__device__ __forceinline__ u64 from2(u64 v) { return dppx<0x4E>(v); }   // lane ^ 2
-__device__ __forceinline__ u64 from3(u64 v) { return dppx<0x1B>(v); }   // lane ^ 3
-__device__ __forceinline__ u64 from7(u64 v) { return dppx<0x141>(v); }  // lane ^ 7 (row_half_mirror)
-__device__ __forceinline__ u64 from8(u64 v) { return dppx<0x128>(v); }  // lane ^ 8 (row_ror:8)
-
-// v + its value in lane ^ 16 or ^ 32 (the swaps leave the two halves' values
-// of every lane pair in both results).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u64 plus16(u64 v) {
-    const u32x2 a = __builtin_amdgcn_permlane16_swap((u32)v, (u32)v, false, false);
-    const u32x2 b = __builtin_amdgcn_permlane16_swap((u32)(v >> 32), (u32)(v >> 32), false, false);
-    return (((u64)b.x << 32) | a.x) + (((u64)b.y << 32) | a.y);
-}
-__device__ __forceinline__ u64 plus32(u64 v) {
-    const u32x2 a = __builtin_amdgcn_permlane32_swap((u32)v, (u32)v, false, false);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap((u32)(v >> 32), (u32)(v >> 32), false, false);
-    return (((u64)b.x << 32) | a.x) + (((u64)b.y << 32) | a.y);
-}
-__device__ __forceinline__ u64 reduced(u64 v) { return fp::canon(fp::fold64(v)); }
-__device__ __forceinline__ u64 uniform(u64 v) {
-    const u32 lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)v);
-    const u32 hi = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(v >> 32));
-    return ((u64)hi << 32) | lo;
-}
 
 // The 36 products of an oct over its eight lanes: lane j takes the partners
 // j, j ^ (1 or 3), j ^ (2 or 6), j ^ (4 or 5), j ^ 7, the first of each pair
@@ -152,36 +120,6 @@ __device__ __forceinline__ void wave_gram(u64 (&s)[SLOTS], u64 (*part)[F2SC_ROW]
 #pragma unroll
         for (int k = 0; k < SLOTS; k++) part[wid][lane * SLOTS + k] = reduced(s[k]);
     }
-}
-
-// Sum over the wave, in every lane: DPP prefix steps (eight values below p
-// stay below 2^64, so three steps go unreduced), then lane 63's total.
-__device__ __forceinline__ u64 wave_total(u64 v) {
-    v += dppx<0x111>(v);  // row_shr:1, 2, 4
-    v += dppx<0x112>(v);
-    v += dppx<0x114>(v);
-    v = fp::canon(fp::fold64(v));
-    v += dppx<0x118>(v);         // row_shr:8
-    v += dppx<0x142, 0xa>(v);    // row_bcast:15 into rows 1, 3
-    v += dppx<0x143, 0xc>(v);    // row_bcast:31 into rows 2, 3
-    v = fp::canon(fp::fold64(v));
-    const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)v, 63);
-    const u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(v >> 32), 63);
-    return ((u64)hi << 32) | lo;
-}
-// Lane l ^ (1 << b), b < 4 uniform.
-__device__ __forceinline__ u64 from_bit(u64 v, u32 b) {
-    switch (b) {
-        case 0: return from1(v);
-        case 1: return from2(v);
-        case 2: return from3(from7(v));
-        default: return from8(v);
-    }
-}
-// v + lane ^ (1 << b)'s value, canonical, b uniform.
-__device__ __forceinline__ u64 plus_bit(u64 v, u32 b) {
-    if (b < 4) return add(v, from_bit(v, b));
-    return reduced(b == 4 ? plus16(v) : plus32(v));
 }
 
 // Message k < 3 of three rounds from their Gram matrix, lane x + 8 y of the
@@ -436,19 +374,13 @@ __global__ void __launch_bounds__(FB) k_f2sc_tail(const F2scPass a, u32 L, const
 #pragma unroll
             for (int i = 0; i < PER; i++) {
                 if (i * FB < (int)n0) {
-                    u64 v = mul(w, x[i]);
-                    v += from1(v);
-                    v += from2(v);
-                    v += from7(v);
+                    const u64 v = oct_total(mul(w, x[i]));
                     if (j == 0 && tid + i * FB < n) tab[(tid + i * FB) >> 3] = reduced(v);
                 }
             }
         } else {  // (at most F2SC_TAIL / 8 entries, in tab[0 .. n))
             if ((tid & ~63u) < n) {
-                u64 v = mul(w, tid < n ? x[0] : 0);
-                v += from1(v);
-                v += from2(v);
-                v += from7(v);
+                const u64 v = oct_total(mul(w, tid < n ? x[0] : 0));
                 if (j == 0 && tid < n) tab[tid >> 3] = reduced(v);
             }
         }

@@ -306,7 +306,7 @@ struct TuneInit {
 
 bool tunable(u32 kind) {
     switch (kind) {
-        case ST_LOAD: case ST_EVAL: case ST_EQ: case ST_P: case ST_W: case ST_FOLD:
+        case ST_LOAD: case ST_EVAL: case ST_EQ: case ST_W: case ST_FOLD:
         case ST_LT: case ST_WAGG: case ST_WT0: case ST_WT: case ST_WA0:
             return true;
         default:
@@ -352,12 +352,12 @@ u32 grid_for(u32 kind, u64 units, u32 qdef) {
 struct Workspace {
     void *mem = nullptr;
     std::vector<u64 *> V;  // per layer, 2^{s_i} values
-    u64 *pA, *pB, *bA, *bB, *fA, *fB;
+    u64 *pA, *pB, *fA, *fB;
     u64 *w, *off;
-    u64 *zlo, *zhi, *alo, *ahi, *blo, *bhi;
+    u64 *alo, *ahi, *blo, *bhi;
     u64 *llo, *lhl, *lhh;
     u64 *rowpool;        // every reducing step's rows, each at its own offset
-    u64 *frec;           // records of p-phase finishes (C, z_j, z_{j+1})
+    u64 *frec;           // records of p-phase finishes (C, z_j, z_{j+1}, ..)
     FinItem *d_items;    // the finish step's items
     TopLayer *d_top;     // descriptors of the layers ST_TOP runs
     u64 *msgs, *chals, *rngst, *zbuf, *state;
@@ -831,15 +831,11 @@ static void carve(const gkr_circuit *c, Arena &a, Arena &h, Workspace &w, const 
     const u64 half = std::max<u64>(1ull << (c->smax ? c->smax - 1 : 0), 2);
     w.pA = rt.take<u64>(half);
     w.pB = rt.take<u64>(half);
-    w.bA = rt.take<u64>(half);
-    w.bB = rt.take<u64>(half);
     w.fA = rt.take<u64>(half);
     w.fB = rt.take<u64>(half);
     const bool gates = c->omega_algo == GKR_OMEGA_GATES;
     w.w = rt.take<u64>(gates ? c->gmax : 1);   // per-gate weights: per-gate rounds only
     w.off = rt.take<u64>(gates ? c->gmax : 1);
-    w.zlo = a.take<u64>(HALF_MAX);
-    w.zhi = a.take<u64>(HALF_MAX);
     w.alo = a.take<u64>(HALF_MAX);
     w.ahi = a.take<u64>(HALF_MAX);
     w.blo = a.take<u64>(HALF_MAX);
@@ -962,7 +958,7 @@ struct Planner {
         const u64 n = units.back();
         const u64 most = n ? std::min<u64>(CAP_MAX, std::max<u64>(1, (n + SBLOCK - 1) / SBLOCK)) : s.nblocks;
         s.rows = w ? w->rowpool + rows_used : nullptr;
-        rows_used += std::max<u64>(most, s.nblocks) * ROW_STRIDE;
+        rows_used += std::max<u64>(most, s.nblocks) * std::max<u32>(K, ROW_STRIDE);
     }
     // Finish info for a step that follows a reducing step (p-phase finishes
     // get a record slot).
@@ -974,30 +970,52 @@ struct Planner {
         const StepDesc &p = out.back();
         f.rows = p.rows;
         f.nrows = p.nblocks;
-        if (kind == FIN_P || kind == FIN_P2) {
-            f.rec = w ? w->frec + recs_used : nullptr;
-            recs_used += 3;
-        }
+        if (kind == FIN_P) f.rec = take_rec();
         return f;
     }
-    // The finish step: one item per message (per chunk of line values).
+    // Record and columns of a p-phase tail.
+    u64 *take_rec() {
+        u64 *r = w ? w->frec + recs_used : nullptr;
+        recs_used += P_REC;
+        return r;
+    }
+    u64 *take_cols() {
+        u64 *r = w ? w->rowpool + rows_used : nullptr;
+        rows_used += PT_COLS;
+        return r;
+    }
+    // The finish step: one item per message (per chunk of line values, per
+    // step's p-phase rounds).
     void add_finish() {
+        // a p-phase tail's messages: its first rounds' columns, then the last ones'
+        auto p_tail = [&](u32 L, u32 pre, i32 draw, u64 *msg, const u64 *rec, const u64 *cols) {
+            const u32 Ra = L > P_LAST ? L - P_LAST : 0;
+            if (Ra) items.push_back(FinItem{FIN_P, 1, cols, msg, rec, draw, Ra, pre});
+            items.push_back(FinItem{FIN_P, 1, cols ? cols + 32 : nullptr, msg ? msg + 3 * Ra : nullptr, rec, draw,
+                                    L - Ra, pre + Ra});
+        };
+        for (const TopLayer &t : top)
+            if (t.s) p_tail(t.s, 0, (i32)t.co, t.msg, t.rec, t.cols);
         for (const StepDesc &sd : out) {
             const Fin &f = sd.fin;
+            if (sd.kind == ST_PTAIL) {
+                const PtailArgs &a = sd.u.ptail;
+                p_tail(a.s - a.j0, a.pend, (i32)(a.c0 - a.pend), a.msg, a.rec, a.cols);
+            }
             if (f.kind == FIN_NONE) continue;
             if (f.kind == FIN_LINE) {
                 for (u32 q = 0; q * f.ch < f.T; q++)
                     items.push_back(FinItem{FIN_LINE, f.chunk_blocks, f.rows ? f.rows + (u64)q * f.chunk_blocks * ROW_STRIDE : nullptr,
                                             f.msg ? f.msg + q * f.ch : nullptr, nullptr, -1,
-                                            std::min<u32>(f.ch, f.T - q * f.ch)});
+                                            std::min<u32>(f.ch, f.T - q * f.ch), 0});
                 continue;
             }
-            items.push_back(FinItem{f.kind, f.nrows, f.rows, f.msg, f.rec, f.draw + 0, 0});
+            items.push_back(FinItem{f.kind, f.nrows, f.rows, f.msg, f.rec, f.draw + 0, f.R, 0});
         }
         if (items.empty()) return;
         double nbytes = 0;
         for (const FinItem &it : items)
-            nbytes += it.nrows * 8.0 * (it.kind == FIN_P ? 2 : it.kind == FIN_P2 ? 6 : it.kind == FIN_W ? 4
+            nbytes += it.nrows * 8.0 * (it.kind == FIN_P ? 1 << it.nvals : it.kind == FIN_W ? 4
                                         : it.kind == FIN_T ? 3 : it.kind == FIN_T2 ? 12 : LINE_CHUNK);
         StepDesc &s = add(ST_FINISH, (u32)items.size(), nbytes);
         s.u.finish = FinishArgs{w ? w->d_items : nullptr, w ? w->chals : nullptr};
@@ -1068,6 +1086,8 @@ struct Planner {
                     t.oths[ph - 1] = g.oths;
                     t.types[ph - 1] = g.types;
                 }
+                t.rec = take_rec();
+                t.cols = take_cols();
                 top.push_back(t);
                 sc_first[i] = sc_last[i] = (int)out.size();
                 // V_{i+1} 8 per entry; per phase: row pointers 4 per wire, sorted
@@ -1101,112 +1121,86 @@ struct Planner {
             u64 *msg = w ? w->msgs + c->mo[i] : nullptr;
             u64 *chals = w ? w->chals : nullptr;
             u64 *vslot = w ? msg + 3ull * n : nullptr;  // v1, v2, then h(2..s')
-            // A p-phase whose table fits a tail runs whole in one workgroup:
-            // the tail starts at round 0 from V_i, forms the suffix weights
-            // B_0 from z itself and carries the previous layer's finish.
-            const bool ptail_only = s > 0 && (1ull << s) <= (u64)TAIL_LIM;
-            if (ptail_only) {
-                StepDesc &st = add(ST_PTAIL, 1, 8.0 * (1ull << s));
-                st.fin = layer_end;
-                PtailArgs pt;
-                memset(&pt, 0, sizeof pt);
-                pt.j0 = 0;
-                pt.s = s;
-                pt.pend = 0;
-                pt.V = V(i);
-                pt.B = nullptr;  // B_0 from z
-                pt.live = 1u << s;
-                pt.c0 = co;
-                pt.msg = msg;
-                st.u.ptail = pt;
-            }
-            // ---- eq tables of z_i[1..s) for the p-phase's first round
-            if (!ptail_only) {
-                const u32 nz = s ? s - 1 : 0;
-                const u64 ne = (1ull << (nz / 2)) + (1ull << (nz - nz / 2));
-                StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
-                mods.back() = 0.5 * ne * nz;
-                e.fin = layer_end;
-                e.u.eq = EqArgs{PT_Z, nz, nz / 2, 1, P_(w ? w->zlo : nullptr), P_(w ? w->zhi : nullptr)};
-            }
-            // ---- p-phase (a5): grid steps of two rounds while the table is
-            // large, then the remaining rounds in one workgroup.  The first
-            // step does round 0 (and round 1's coefficients); a step reading
-            // V^(j) does rounds j+2, j+3; the tail starts at round j0.
-            if (s > 0 && !ptail_only) {
-                const bool look = s >= 2;
-                u32 j0 = 1;
-                if (look) j0 = s > 12 ? ((s - 10 + 1) & ~1u) : 2;  // even, 2^(s - j0) <= TAIL_LIM
-                // V_i is zero from S_i on, and so is every V^(j) from S_i >> j:
-                // the grid steps take the first NP entries of V_i (S_i rounded
-                // up to 2^j0, so every step's range is exact) and the tail
-                // zeroes V^(j0) from NP >> j0 on.  The suffix weights B are not
-                // zero there; the steps write them below the bound only, so a
-                // trimmed tail forms its B_{j0} from z.
-                const u64 NP = std::min<u64>(1ull << s, ((u64)c->S[i] + (1ull << j0) - 1) >> j0 << j0);
-                u64 *vbuf[2] = {w ? w->pA : nullptr, w ? w->pB : nullptr};
-                u64 *bbuf[2] = {w ? w->bA : nullptr, w ? w->bB : nullptr};
-                const u32 nz = s - 1;
-                int bw = 0;           // B buffer the last step wrote
+            // ---- p-phase (a5).  A table that fits a tail runs whole in one
+            // workgroup, which carries the previous layer's finish.  Larger
+            // ones: a step over V_i summing R1 rounds, a step folding them (and
+            // summing three more rounds) until three rounds separate the table
+            // from the tail's size, and the tail, which folds those.  R1 makes
+            // the second step's table 2^13 entries: one step at least (3), and
+            // at most 2^7 columns, which a workgroup's rows still hold cheaply.
+            if (s > 0) {
                 const u64 *vlast = V(i);
-                {
+                u32 lev = 0, pend = 0;  // rounds summed so far; those of the last step
+                u64 live = c->S[i];     // entries of V^(lev) that are not zero
+                u64 *vbuf[2] = {w ? w->pA : nullptr, w ? w->pB : nullptr};
+                u32 vb = 0;
+                auto p_fin = [&](Fin f) {  // the finish of the rounds [lev - pend, lev) just summed
+                    f.j = lev - pend;
+                    f.R = pend;
+                    f.draw = (i32)(co + lev - pend);
+                    f.msg = w ? msg + 3ull * (lev - pend) : nullptr;
+                    return f;
+                };
+                if ((1ull << s) > (u64)TAIL_LIM) {
+                    const u32 R1 = std::min<u32>(P_ROUNDS, std::max<u32>(3, s > 13 ? s - 13 : 0));
                     PArgs pa;
                     memset(&pa, 0, sizeof pa);
-                    pa.first = 1;
-                    pa.look = look;
-                    pa.nu = look ? NP >> 2 : 1;
-                    pa.Vsrc = V(i);
-                    pa.Bout = look ? bbuf[0] : nullptr;  // B_1
-                    pa.zlo = w ? w->zlo : nullptr;
-                    pa.zhi = w ? w->zhi : nullptr;
-                    pa.L = nz / 2;
-                    // V 8 per entry, eq halves 16 per pair, B_1 8 per quad
-                    StepDesc &st = addg(ST_P, look ? 4 * pa.nu : pa.nu, 1, look ? pa.nu * (32.0 + 32 + 8) : 32.0);
-                    // per quad: a suffix weight and two products in each lane; per pair: 3
-                    mods.back() = look ? pa.nu * 12.0 : pa.nu * 3.0;
-                    st.u.p = pa;
-                    reduces(look ? 6 : 2);
-                }
-                for (u32 j = 0; j + 2 < j0; j += 2) {
-                    Fin f = fin_of_prev(FIN_P2);
-                    f.j = j;
-                    f.draw = (i32)(co + j);
-                    f.msg = w ? msg + 3ull * j : nullptr;
-                    PArgs pa;
-                    memset(&pa, 0, sizeof pa);
-                    pa.nu = NP >> (j + 4);  // (j + 4 <= j0)
+                    pa.R = R1;
+                    pa.s = s;
+                    pa.nu = (live + SBLOCK - 1) / SBLOCK;
                     pa.Vsrc = vlast;
-                    pa.Vout = vbuf[(j / 2) & 1];
-                    pa.Bprev = bbuf[bw];
-                    pa.Bout = bbuf[bw ^ 1];
-                    // per unit: V^(j) 16 read, V^(j+2) 4 written, B 4 read and 1 written
-                    StepDesc &st = addg(ST_P, 4 * pa.nu, 1, pa.nu * 8.0 * (16 + 4 + 4 + 1));
-                    mods.back() = pa.nu * 20.0;  // per quad: four two-challenge folds (3 each), 8 products
-                    st.fin = f;
+                    // four runs a workgroup before another starts, at most 512
+                    StepDesc &st = add(ST_P, (u32)std::min<u64>(SMAX_BLOCKS, (pa.nu + 3) / 4), 8.0 * live);
+                    mods.back() = (double)live;
+                    st.fin = layer_end;
                     st.u.p = pa;
-                    reduces(6);
-                    vlast = pa.Vout;
-                    bw ^= 1;
+                    reduces(1u << R1);
+                    lev = pend = R1;
+                    live = (live + (1ull << R1) - 1) >> R1;
+                    while (s - lev > (u32)TAIL_LOG) {
+                        const Fin f = p_fin(fin_of_prev(FIN_P));
+                        memset(&pa, 0, sizeof pa);
+                        pa.pend = pend;
+                        pa.R = 3;
+                        pa.s = s;
+                        pa.j = lev;
+                        pa.nu = (live + 7) / 8;
+                        pa.live = live;
+                        pa.Vsrc = vlast;
+                        pa.Vout = vbuf[vb];
+                        // a wave a unit, at most 512 workgroups
+                        StepDesc &sn = add(ST_P, (u32)std::min<u64>(SMAX_BLOCKS, (pa.nu + 7) / 8),
+                                           8.0 * ((live << pend) + 8 * pa.nu));
+                        mods.back() = (double)(live << pend) + 8.0 * pa.nu;
+                        sn.fin = f;
+                        sn.u.p = pa;
+                        reduces(8);
+                        vlast = pa.Vout;
+                        vb ^= 1;
+                        pend = 3;
+                        lev += 3;
+                        live = pa.nu;
+                    }
                 }
-                const u32 pend = look ? 2 : 1;
-                Fin f = fin_of_prev(look ? FIN_P2 : FIN_P);
-                f.j = j0 - pend;
-                f.draw = (i32)(co + j0 - pend);
-                f.msg = w ? msg + 3ull * (j0 - pend) : nullptr;
-                StepDesc &st = add(ST_PTAIL, 1, 8.0 * (1ull << (s - j0 + pend)));
-                mods.back() = 4.0 * (1ull << (s - j0 + pend));
+                const Fin f = lev ? p_fin(fin_of_prev(FIN_P)) : layer_end;
+                StepDesc &st = add(ST_PTAIL, 1, 8.0 * (1ull << (s - lev + pend)));
+                mods.back() = 4.0 * (1ull << (s - lev + pend));
                 st.fin = f;
                 PtailArgs pt;
                 memset(&pt, 0, sizeof pt);
-                pt.j0 = j0;
+                pt.j0 = lev;
                 pt.s = s;
                 pt.pend = pend;
-                pt.V = vlast;       // V^(j0 - pend)
-                pt.B = NP == (1ull << s) ? bbuf[bw] : nullptr;  // B_{j0-1}, or B_{j0} from z
-                pt.live = (u32)(NP >> j0);
-                pt.c0 = co + j0;
-                pt.msg = w ? msg + 3ull * j0 : nullptr;
+                pt.V = vlast;
+                pt.live = (u32)live;
+                pt.c0 = co + lev;
+                pt.msg = w ? msg + 3ull * lev : nullptr;
+                pt.rec = lev ? f.rec : take_rec();
+                pt.cols = take_cols();
                 st.u.ptail = pt;
+            } else if (layer_end.kind != FIN_NONE) {  // no p-phase: a step for the previous layer's finish
+                StepDesc &e = add(ST_END, 1, 0);
+                e.fin = layer_end;
             }
             // A small layer whose wires each carry one chunk of gates runs each
             // omega phase in one workgroup (ST_WSMALL), which also forms the
@@ -1218,7 +1212,7 @@ struct Planner {
                 const u32 La = s / 2;
                 const u64 ne = (1ull << La) + (1ull << (s - La));
                 StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
-                e.u.eq = EqArgs{PT_CHAL, s, La, co, w ? w->alo : nullptr, w ? w->ahi : nullptr, 1};
+                e.u.eq = EqArgs{s, La, co, w ? w->alo : nullptr, w ? w->ahi : nullptr, 1};
             }
             if (sp == 0) {
                 StepDesc &e = add(ST_SGE, 1, 8);
@@ -1314,7 +1308,7 @@ struct Planner {
                     if (ph == 2) {
                         const u64 ne = (1ull << Lb) + (1ull << (sp - Lb));
                         StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
-                        e.u.eq = EqArgs{PT_CHAL, sp, Lb, co + s, w ? w->blo : nullptr, w ? w->bhi : nullptr};
+                        e.u.eq = EqArgs{sp, Lb, co + s, w ? w->blo : nullptr, w ? w->bhi : nullptr};
                     }
                     const gkr_circuit::Group gd = group(ph, i);
                         const gkr_circuit::Group *dg = &gd;
@@ -1493,7 +1487,7 @@ struct Planner {
                         const u64 ne = (1ull << Lb) + (1ull << (sp - Lb));
                         StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
                         e.fin = f;
-                        e.u.eq = EqArgs{PT_CHAL, sp, Lb, co + s, w ? w->blo : nullptr, w ? w->bhi : nullptr};
+                        e.u.eq = EqArgs{sp, Lb, co + s, w ? w->blo : nullptr, w ? w->bhi : nullptr};
                     }
                     const u64 *F = V(i + 1);
                     u64 *fbuf[2] = {w ? w->fA : nullptr, w ? w->fB : nullptr};

@@ -7,7 +7,7 @@
 // result does not depend on the summation order.
 #include <hip/hip_ext.h>
 
-#include "fp61.hpp"
+#include "lanes.hpp"
 #include "steps.hpp"
 
 namespace gkr {
@@ -30,13 +30,17 @@ __device__ __forceinline__ void st2(u64 *p, u64 i, u64 a, u64 b) {
 }
 
 constexpr int NWAVES = SBLOCK / 64;
+constexpr int TAIL_TAB = 2 * TAIL_LIM;  // LDS entries per table of an omega tail: all levels
 
-// Data-parallel primitives moving one u64 as two 32-bit halves.
+// Words for workgroup sums, beside the body's.
+__device__ __forceinline__ u64 *sum_lds() {
+    __shared__ __align__(16) u64 t[NWAVES * ROW_STRIDE + ROW_STRIDE];
+    return t;
+}
+
 template <int CTRL, int ROWS>
 __device__ __forceinline__ u64 dpp64(u64 v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(u32)v, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u32)(v >> 32), CTRL, ROWS, 0xf, true);
-    return ((u64)(u32)hi << 32) | (u64)(u32)lo;
+    return dppx<CTRL, ROWS>(v);
 }
 // Value of lane Q of this lane's quad (lanes 4m..4m+3).
 template <int Q>
@@ -58,22 +62,11 @@ __device__ __forceinline__ u64 wave_sum63(u64 v) {
     return v;
 }
 
-// A value every lane holds the same copy of, moved to scalar registers.
-__device__ __forceinline__ u64 uniform(u64 v) {
-    const u32 lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)v);
-    const u32 hi = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(v >> 32));
-    return ((u64)hi << 32) | lo;
-}
-__device__ __forceinline__ u64 lane_value(u64 v, u32 l) {  // l uniform
-    const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)v, l);
-    const u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(v >> 32), l);
-    return ((u64)hi << 32) | lo;
-}
-
 // Workgroup sum of v; thread k < K writes total k to out[k].
 template <int K>
 __device__ __forceinline__ void block_store(u64 (&v)[K], u64 *out) {
-    __shared__ u64 sm[K][NWAVES];
+    static_assert(K <= ROW_STRIDE, "sum_lds");
+    u64 (*sm)[NWAVES] = reinterpret_cast<u64 (*)[NWAVES]>(sum_lds());
 #pragma unroll
     for (int k = 0; k < K; k++) v[k] = wave_sum63(v[k]);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -106,8 +99,8 @@ __device__ __forceinline__ void rows_total(const u64 *rows, u32 first, u32 n, u6
     static_assert(K <= ROW_STRIDE, "a row holds at most ROW_STRIDE values");
     constexpr u32 STEP = NWAVES * 4;  // rows per pass of the workgroup
     constexpr u32 U = 16;             // passes per batch of loads
-    __shared__ u64 part[NWAVES][ROW_STRIDE];
-    __shared__ u64 res[K];
+    u64 (*part)[ROW_STRIDE] = reinterpret_cast<u64 (*)[ROW_STRIDE]>(sum_lds());
+    u64 *res = sum_lds() + NWAVES * ROW_STRIDE;
     const u32 lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const u32 r0 = wid * 4 + (lane >> 4);
     const u64 *p = rows + ((u64)first + wid * 4) * ROW_STRIDE + lane;  // row first + r0, column lane % 16
@@ -144,18 +137,19 @@ __device__ __forceinline__ u64 chi_bits(u64 x, const u64 *pt, u32 n) {
 }
 
 struct Ctx {
+    u64 *lds;        // lds_words(kind) words: every kind lays its arrays over the same ones
     u32 lb, nb;      // this workgroup within the step, workgroups of the step
     u64 gtid, gstride;
     u64 r;           // challenge drawn in the prologue
     u64 r2;          // the second one, after a two-round step
+    u64 rl;          // lane k: the k-th challenge drawn
 };
 
-// What a tail takes over from its launch's prologue and finish: the RNG
-// state after the drawn challenges (if the prologue drew any) and the beta
-// prefix C (if the finish computed it, p-phase rounds).
+// What a tail takes over from its launch's prologue: the RNG state after the
+// drawn challenges (if the prologue drew any).
 struct TailIn {
-    u64 st, C;
-    u32 drew, have_c;
+    u64 st;
+    u32 drew;
 };
 
 __device__ __forceinline__ u64 fold1(u64 x0, u64 x1, u64 r) {
@@ -190,34 +184,26 @@ __device__ __forceinline__ u64 pick(const u64 (&tot)[K], u32 k) {
 }
 
 // The part of a round's finish that later rounds need; it reads no rows.
-// Thread 0 records the beta prefix C and z of a p-phase round for its
-// message, advances C by the drawn challenge(s) (left in *s_c as well), and
+// The first wave records the beta prefix C and the z values of p-phase rounds
+// for their messages and advances C by the drawn challenges; thread 0,
 // at the end of an omega phase folds the last pair into v1 / v2; the line
 // finish stores z_{i+1}.
 template <u32 KIND>
-__device__ __forceinline__ void fin_inline(const StepDesc &sd, const Ctx &c, const u64 *s_pt, u64 *s_c) {
+__device__ __forceinline__ void fin_inline(const StepDesc &sd, const Ctx &c, const u64 *s_pt) {
     const Fin &f = sd.fin;
     const ProofPtrs &pp = sd.pp;
     constexpr u32 FM = fin_mask(KIND);
     const u32 tid = threadIdx.x;
     if ((FM & (1u << FIN_P)) && f.kind == FIN_P) {
-        if (tid == 0) {
-            const u64 z = pp.zbuf[f.j], C = pp.state[0];
-            f.rec[0] = C;
-            f.rec[1] = z;
-            const u64 Cn = mul(C, fp::eq(z, c.r));  // beta prefix over r_0..r_j
-            pp.state[0] = Cn;
-            *s_c = Cn;
-        }
-    } else if ((FM & (1u << FIN_P2)) && f.kind == FIN_P2) {
-        if (tid == 0) {
-            const u64 z0 = pp.zbuf[f.j], z1 = pp.zbuf[f.j + 1], C = pp.state[0];
-            f.rec[0] = C;
-            f.rec[1] = z0;
-            f.rec[2] = z1;
-            const u64 Cn = mul(mul(C, fp::eq(z0, c.r)), fp::eq(z1, c.r2));
-            pp.state[0] = Cn;
-            *s_c = Cn;
+        if (tid < 64) {  // lane k: round j + k
+            const bool on = tid < f.R;
+            const u64 z = on ? pp.zbuf[f.j + tid] : 0, C = pp.state[0];
+            if (on) f.rec[1 + tid] = z;
+            const u64 e = row_product(on ? fp::eq(z, c.rl) : 1);
+            if (tid == 0) {
+                f.rec[0] = C;
+                pp.state[0] = mul(C, e);  // beta prefix over r_0 .. r_{j+R-1}
+            }
         }
     } else if ((FM & (1u << FIN_W)) && f.kind == FIN_W) {
         if (f.last && tid == 0) {
@@ -232,6 +218,32 @@ __device__ __forceinline__ void fin_inline(const StepDesc &sd, const Ctx &c, con
     }
 }
 
+// Message of p-phase round k of the R summed in the columns T (2^R words of
+// LDS), z and r the rounds' coordinates and challenges, C the beta prefix
+// before round k; one wave.
+__device__ __forceinline__ void p_message(const u64 *T, u32 R, u32 k, const u64 *z, const u64 *r, u64 C, u64 *msg) {
+    const u32 lane = threadIdx.x & 63;
+    u64 S0 = 0, S1 = 0;
+    for (u32 x = lane; x < (1u << R); x += 64) {
+        u64 w = T[x];
+        for (u32 i = 0; i < R; i++)  // (uniform)
+            if (i != k) w = mul(w, fp::eqbit((x >> i) & 1, i < k ? r[i] : z[i]));
+        if ((x >> k) & 1)
+            S1 = add(S1, w);
+        else
+            S0 = add(S0, w);
+    }
+    S0 = wave_total(S0);
+    S1 = wave_total(S1);
+    if (lane < 3) msg[lane] = p_value(lane, C, z[k], S0, S1);
+}
+// The beta prefix after rounds 0 .. k-1 (k <= 16): C0 prod eq(z_i, r_i), in
+// every lane.
+__device__ __forceinline__ u64 beta_prefix(u64 C0, u32 k, const u64 *z, const u64 *r) {
+    const u32 lane = threadIdx.x & 63;
+    return uniform(mul(C0, row_product(lane < k ? fp::eq(z[lane], r[lane]) : 1)));
+}
+
 // One item of ST_FINISH: a round's rows into its message, lanes t < 3 (and
 // 3..5 for a second message) writing one value each; operands that do not
 // depend on the rows are loaded before the row sums.
@@ -239,21 +251,32 @@ __device__ __forceinline__ void step_finish(const FinishArgs &a, const Ctx &c) {
     const FinItem &it = a.items[c.lb];
     const u32 tid = threadIdx.x;
     switch (it.kind) {
-        case FIN_P: {
-            const u64 C = it.rec[0], z = it.rec[1];
-            u64 t[2];
-            rows_total<2>(it.rows, 0, it.nrows, t);
-            if (tid < 3) it.msg[tid] = p_value(tid, C, z, t[0], t[1]);
-            break;
-        }
-        case FIN_P2: {
-            const u64 C = it.rec[0], z0 = it.rec[1], z1 = it.rec[2], r = a.chals[it.draw];
-            u64 t[6];
-            rows_total<6>(it.rows, 0, it.nrows, t);
-            const u64 C1 = mul(C, fp::eq(z0, r));
-            if (tid < 3) it.msg[tid] = p_value(tid, C, z0, t[0], t[1]);
-            else if (tid < 6)
-                it.msg[tid] = p_value(tid - 3, C1, z1, add(t[2], mul(r, t[3])), add(t[4], mul(r, t[5])));
+        case FIN_P: {  // column sums, then a wave a message
+            u64 *s_col = c.lds;
+            const u32 R = it.nvals, x = tid & ((1u << R) - 1), G = SBLOCK >> R;
+            u64 t = 0;
+            constexpr u32 U = 16;  // loads in flight
+            for (u32 q0 = tid >> R; q0 < it.nrows; q0 += G * U) {
+                u64 v[U];
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    const u32 q = q0 + i * G;
+                    v[i] = q < it.nrows ? it.rows[((u64)q << R) + x] : 0;
+                }
+#pragma unroll
+                for (u32 i = 0; i < U; i++) t = add(t, v[i]);
+            }
+            s_col[tid] = t;
+            __syncthreads();
+            for (u32 h = SBLOCK / 2; h >= (1u << R); h >>= 1) {
+                if (tid < h) s_col[tid] = add(s_col[tid], s_col[tid + h]);
+                __syncthreads();
+            }
+            const u32 k = tid >> 6;
+            if (k < R) {
+                const u64 *z = it.rec + 1, *r = a.chals + it.draw;
+                p_message(s_col, R, k, z + it.pre, r + it.pre, beta_prefix(it.rec[0], it.pre + k, z, r), it.msg + 3 * k);
+            }
             break;
         }
         case FIN_W: {
@@ -368,83 +391,133 @@ __device__ __forceinline__ u64 red128_lz(u128 x) {
 // loads and stores stay coalesced, the quad's values are exchanged with DPP
 // quad permutes and the quad's products are split over its lanes.
 
-// p-phase quad v0..v3 of V^(j) with b0 = B_j[2u], b1 = B_j[2u+1]: round j's
-// sums S0 = b0 v0 + b1 v2, S1 = b0 v1 + b1 v3 and the coefficients of round
-// j+1's sums in r_j: U0 = bb v0, U1 = bb (v1 - v0), W0 = bb v2,
-// W1 = bb (v3 - v2), bb = b0 + b1.  Lane j of the quad takes S0 (j = 0), S1
-// (1), U0 and U1 (2), W0 and W1 (3): two products each, operands chosen by
-// j so that all lanes run the same instructions.  x: its first (or only)
-// sum, y: its second.
-// bb and the differences stay unreduced (below 2 p), each product is
-// reduced to below p + 4, and x, y are kept below p + 4 (canonical only
-// when the step stores them).
-__device__ __forceinline__ void p_quad(u32 j, u64 v0, u64 v1, u64 v2, u64 v3, u64 b0, u64 b1,
-                                       u64 &x, u64 &y) {
-    const u64 bb = b0 + b1;
-    const bool s = j < 2;
-    const u64 m1 = s ? b0 : bb, m2 = s ? b1 : bb;
-    const u64 o1 = j == 0 ? v0 : (j == 1 ? v1 : (j == 2 ? v0 : v2));
-    const u64 o2 = j == 0 ? v2 : (j == 1 ? v3 : (j == 2 ? diff_lz(v1, v0) : diff_lz(v3, v2)));
-    const u64 p1 = red128_lz(fp::wide(m1, o1)), p2 = red128_lz(fp::wide(m2, o2));
-    x = fp::fold64(x + (s ? p1 + p2 : p1));
-    y = fp::fold64(y + (s ? 0 : p2));
+// p-phase grid steps (see PArgs).  zp: z_i in LDS (first step) or memory.
+// FIRST: whether this is the phase's first step, compile-time (1, 0; one
+// kernel each) or -1 to take a.pend.
+//
+// First step: bound by the read of V_i and one product an entry.  A thread
+// keeps its place in the SBLOCK-entry runs, so its entry's weight is one
+// scalar a run times a factor of its own, applied once at the end.
+__device__ __forceinline__ void step_p_first(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row) {
+    u64 *s_w = c.lds, (*s_sum)[64] = reinterpret_cast<u64 (*)[64]>(s_w + 64);
+    constexpr u32 LB = 9;
+    static_assert((1 << LB) == SBLOCK, "SBLOCK");
+    const u32 tid = threadIdx.x, lane = tid & 63, R = a.R;
+    u64 t = 0;
+    for (u64 q0 = c.lb; q0 < a.nu; q0 += 64ull * c.nb) {  // 64 runs of this workgroup at a time
+        if (tid < 64) {
+            const u64 q = q0 + (u64)tid * c.nb;
+            u64 w = 1;
+            if (q < a.nu)
+                for (u32 k = LB; k < a.s; k++) w = mul(w, fp::eqbit((u32)(q >> (k - LB)) & 1, zp[k]));
+            s_w[tid] = w;
+        }
+        __syncthreads();
+        const u64 left = (a.nu - q0 + c.nb - 1) / c.nb;
+        const u32 n = left < 64 ? (u32)left : 64;
+        const u64 *src = a.Vsrc + q0 * SBLOCK + tid;
+        u128 acc = 0;
+        for (u32 i0 = 0; i0 < n; i0 += 4) {
+            u64 v[4];
+#pragma unroll
+            for (u32 i = 0; i < 4; i++) v[i] = i0 + i < n ? src[(u64)(i0 + i) * c.nb * SBLOCK] : 0;
+#pragma unroll
+            for (u32 i = 0; i < 4; i++) acc += fp::wide(s_w[(i0 + i) & 63], v[i]);  // (up to 64 products below 2^122)
+        }
+        t = add(t, fp::red128(acc));
+        __syncthreads();  // s_w is read
+    }
+    for (u32 k = R; k < LB; k++) t = mul(t, fp::eqbit((tid >> k) & 1, zp[k]));
+    // threads of equal column tid mod 2^R, over the wave and the waves
+    for (u32 b = R; b < 6; b++) t = plus_bit(t, b);
+    s_sum[tid >> 6][lane] = t;
+    __syncthreads();
+    if (tid < (1u << R)) {
+        const u32 w0 = tid >> 6, step = R > 6 ? 1u << (R - 6) : 1;
+        u64 s = 0;
+        for (u32 w = w0; w < (u32)NWAVES; w += step) s = add(s, s_sum[w][tid & 63]);
+        row[tid] = s;
+    }
 }
 
-// FIRST: whether this is the phase's first step, compile-time (1, 0; one
-// kernel each) or -1 to take a.first.
-template <int FIRST>
-__device__ __forceinline__ void step_p(const PArgs &a, const Ctx &c, u64 *row) {
-    const bool first = FIRST >= 0 ? FIRST != 0 : a.first != 0;
-    const u64 mask = (1ull << a.L) - 1;
-    auto beta0 = [&](u64 m) { return mul(a.zlo[m & mask], a.zhi[m >> a.L]); };  // B_0[m]
-    if (first && !a.look) {
-        // one round (s = 1)
-        u64 acc[2] = {0, 0};
-        for (u64 m = c.gtid; m < a.nu; m += c.gstride) {
-            const u64x2 p = ld2(a.Vsrc, 2 * m);
-            const u64 b = beta0(m);
-            acc[0] = add(acc[0], mul(b, p.x));
-            acc[1] = add(acc[1], mul(b, p.y));
-        }
-        block_store<2>(acc, row);
-        return;
+// Later steps: eight lanes form an entry of V^(j) from its 2^pend entries of
+// V^(j-pend) and a wave a unit of eight entries, lane group g holding column g.
+// The first unit's loads are issued before draw() waits for the challenge
+// state: a step this small is a chain of memory round trips.
+template <typename Draw>
+__device__ __forceinline__ void step_p_next(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row, Draw draw) {
+    u64 *s_chi = c.lds, (*s_sum)[8] = reinterpret_cast<u64 (*)[8]>(s_chi + (1 << P_ROUNDS));
+    const u32 tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l = lane & 7, g = lane >> 3, pend = a.pend;
+    const u64 ustep = (u64)c.nb * NWAVES;
+    u64 u = (u64)c.lb * NWAVES + wid;
+    // a lane's entries of unit u: one (pend = 3), or two of each 16
+    constexpr u32 MX = 1 << (P_ROUNDS - 4);
+    const u32 n = pend == 3 ? 0 : 1u << (pend - 4);
+    u64x2 x[MX];
+    auto load = [&](u64 uu) {
+        const u64 m = 8 * uu + g;
+        const bool on = uu < a.nu && m < a.live;
+        const u64 *src = a.Vsrc + (m << pend);
+        if (n == 0) x[0].x = on ? src[l] : 0;
+#pragma unroll
+        for (u32 i = 0; i < MX; i++)
+            if (i < n) {
+                x[i].x = x[i].y = 0;
+                if (on) x[i] = ld2(src, 16 * i + 2 * l);
+            }
+    };
+    load(u);
+    // lane k < nz of each row of 16: coordinate k of a unit's index (usually
+    // all s - j - 3 of them)
+    const u32 nz = a.s - a.j - 3, kz = lane & 15;
+    const u64 z1 = kz < nz ? zp[a.j + 3 + kz] : 0;
+    draw();
+    if (tid < (1u << pend)) {  // chi_tid of the drawn challenges
+        u64 w = 1;
+        for (u32 k = 0; k < pend; k++) w = mul(w, fp::eqbit((tid >> k) & 1, lane_value(c.rl, k)));
+        s_chi[tid] = w;
     }
-    u64 x = 0, y = 0;  // this lane's sums (see p_quad)
-    const u64 r0 = c.r, r1 = c.r2, r01 = mul(r0, r1);
-    // lanes g = 4u + j; the stride is a multiple of 4, so a quad's lanes
-    // leave the loop together
-    for (u64 g = c.gtid; (g >> 2) < a.nu; g += c.gstride) {
-        const u64 u = g >> 2;
-        const u32 j = (u32)(g & 3);
-        u64 v, bq;  // entry 4u + j of this step's level; B of that level at pair 2u + j/2
-        if (first) {
-            v = a.Vsrc[g];
-            bq = beta0(2 * u + (j >> 1));  // lanes 0, 1: B_0[2u]; lanes 2, 3: B_0[2u+1]
+    __syncthreads();
+    u64 sum = 0;
+    while (u < a.nu) {  // (wave-uniform)
+        const u64 m = 8 * u + g;
+        u64 v;
+        if (n == 0) {
+            v = mul(s_chi[l], x[0].x);
         } else {
-            const u64x2 p = ld2(a.Vsrc, 4 * g), q = ld2(a.Vsrc, 4 * g + 2);
-            v = fold2(p.x, p.y, q.x, q.y, r0, r1, r01);
-            if (a.Vout) a.Vout[g] = v;
-            bq = a.Bprev[g];  // B_{j+1}[4u + j]
+            u128 acc = 0;
+#pragma unroll
+            for (u32 i = 0; i < MX; i++)
+                if (i < n) {
+                    const u64x2 w = ld2(s_chi, 16 * i + 2 * l);
+                    acc += fp::wide(w.x, x[i].x) + fp::wide(w.y, x[i].y);
+                }
+            v = fp::red128(acc);
         }
-        const u64 v0 = quad_get<0>(v), v1 = quad_get<1>(v), v2 = quad_get<2>(v), v3 = quad_get<3>(v);
-        u64 b0, b1;
-        if (first) {
-            b0 = quad_get<0>(bq);
-            b1 = quad_get<2>(bq);
-        } else {
-            b0 = add(quad_get<0>(bq), quad_get<1>(bq));  // B_{j+2}[2u]
-            b1 = add(quad_get<2>(bq), quad_get<3>(bq));  // B_{j+2}[2u+1]
-        }
-        if (j == 0 && a.Bout) a.Bout[u] = add(b0, b1);
-        p_quad(j, v0, v1, v2, v3, b0, b1, x, y);
+        v = reduced(oct_total(v));
+        if (l == 0) a.Vout[m] = v;
+        u64 w = row_product(kz < nz ? fp::eqbit((u32)(u >> kz) & 1, z1) : 1);
+        for (u32 k = 16; k < nz; k++) w = mul(w, fp::eqbit((u32)(u >> k) & 1, zp[a.j + 3 + k]));
+        sum = add(sum, mul(w, v));
+        u += ustep;
+        load(u);
     }
-    // rows: S0, S1, U0, U1, W0, W1
-    x = fp::canon(x);
-    y = fp::canon(y);
-    const u32 j = (u32)(c.gtid & 3);
-    u64 acc[6] = {j == 0 ? x : 0, j == 1 ? x : 0, j == 2 ? x : 0, j == 2 ? y : 0, j == 3 ? x : 0,
-                  j == 3 ? y : 0};
-    block_store<6>(acc, row);
+    if (l == 0) s_sum[wid][g] = sum;
+    __syncthreads();
+    if (tid < 8) {
+        u64 s = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVES; w++) s = add(s, s_sum[w][tid]);
+        row[tid] = s;
+    }
+}
+
+template <int FIRST, typename Draw>
+__device__ __forceinline__ void step_p(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row, Draw draw) {
+    if (FIRST == 1 || (FIRST < 0 && a.pend == 0))
+        step_p_first(a, c, zp, row);
+    else
+        step_p_next(a, c, zp, row, draw);
 }
 
 // Gate g with bound-wire index idx, at round k of its phase:
@@ -574,7 +647,7 @@ __device__ __forceinline__ void step_lt(const LtArgs &a, const Ctx &c, const u64
 // reduced once per tile (<= 64 terms).
 template <int CH>
 __device__ void line_sums(const LineArgs &a, const Ctx &c, u64 *row) {
-    __shared__ u64 s_w[64][CH];
+    u64 (*s_w)[CH] = reinterpret_cast<u64 (*)[CH]>(c.lds);
     const u32 T = a.T, H = a.sp - a.L - a.M;
     const u64 nlo = 1ull << a.L, nhl = 1ull << a.M, nhh = 1ull << H;
     const u32 chunk = c.lb / a.chunk_blocks;
@@ -843,7 +916,7 @@ __device__ __forceinline__ void table_quad(u32 j, u64 A, u64 C, u64 F, bool hasC
 // shifts by 4 and 8 leave a row's sums in its lanes 12 + j, shuffles add the
 // four rows of the wave, LDS the waves.
 __device__ __forceinline__ void table_quad_store(u32 j, const QuadAcc &q, u64 *row) {
-    __shared__ u64 sm[NWAVES][12];
+    u64 (*sm)[12] = reinterpret_cast<u64 (*)[12]>(sum_lds());
     u64 v[4] = {fp::canon(q.g), fp::canon(q.q0), fp::canon(q.q1), fp::canon(q.q2)};  // (below p + 4)
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -1025,18 +1098,11 @@ __device__ __forceinline__ void step_wt(const WtArgs &a, const Ctx &c, u64 *row)
 // below that wave t sums value t of the message and then folds table t.
 // The partial sums of all rounds are added into the messages at the end.
 
-constexpr int TAIL_TAB = 2 * TAIL_LIM;              // LDS entries per table: all levels
-constexpr int TAIL_LOG = 10;                        // log2(TAIL_LIM): rounds of a tail
 constexpr int TAIL_CHUNKS = TAIL_LIM / 64;          // 64-pair chunks of a tail
 constexpr int TAIL_SLOTS = TAIL_CHUNKS + TAIL_LOG;  // chunk sums, then the small rounds' sums
 static_assert((1 << TAIL_LOG) == TAIL_LIM, "TAIL_LOG");
 static_assert(TAIL_LIM / 2 <= SBLOCK, "a wide round gives every pair a thread");
 static_assert(NWAVES >= 3, "one wave per message value");
-
-__device__ __forceinline__ u64 *tail_lds() {
-    __shared__ __align__(16) u64 t[3 * TAIL_TAB];
-    return t;
-}
 
 // Partial message sums of a tail, per value t: chunk c's sum in slot c
 // (rounds of at least 64 pairs), round k's sum in slot TAIL_CHUNKS + k
@@ -1210,7 +1276,7 @@ __device__ __forceinline__ u64 wtail_rounds(u64 *A, u64 *Ct, u64 *F, u32 n, bool
 // HC: whether the phase has a C table, compile-time (one kernel each) or -1.
 template <int HC>
 __device__ __forceinline__ void step_wtail(const WtailArgs &a, const ProofPtrs &pp, const Ctx c, u32 drew, u64 st0) {
-    u64 *tab = tail_lds();
+    u64 *tab = c.lds;
     const u32 tid = threadIdx.x;
     const bool hc = HC >= 0 ? HC != 0 : a.hasC != 0;
     const u32 n = 1u << (a.sp - a.k0);  // entries of level k0, at most TAIL_LIM
@@ -1230,7 +1296,7 @@ __device__ __forceinline__ void step_wtail(const WtailArgs &a, const ProofPtrs &
 // level-0 tables from the wiring (as ST_WA0 forms them) into LDS, then
 // every round as a tail.
 __device__ __forceinline__ void step_wsmall(const WsmallArgs &a, const ProofPtrs &pp, const Ctx c) {
-    u64 *tab = tail_lds();
+    u64 *tab = c.lds;
     const u32 tid = threadIdx.x;
     {
         const u64 *pt = pp.chals + a.eqbase;
@@ -1262,140 +1328,125 @@ __device__ __forceinline__ void step_wsmall(const WsmallArgs &a, const ProofPtrs
     (void)c;
 }
 
-// p-phase rounds in one workgroup.  B is the table of sums of the eq
-// weights of the a-coordinates not yet reached (beta over z's suffix); pair
-// m of V goes with B[m].  Round j's message is G(t) = C_j eq_t(z_j) S_t with
-// S_t = sum_m B[m] V_t over the pairs and eq_t(z) the line through
-// (0, 1 - z), (1, z): 1 - z, z, 3z - 1 at t = 0, 1, 2; C_{j+1} =
-// C_j eq(z_j, r_j).  V is a tree as the omega tables; B's level k sits at
-// the indexes q of the pairs it goes with, its entry q' of level k+1 being
-// the sum of entries 2q' - n and 2q' - n + 1.
-//
-// ptail_rounds: the rounds over V (level 0: n = 2^L entries) and B (the
-// weights of its pairs, level 0: n / 2 entries), both in LDS as trees of
-// TAIL_TAB entries.  Lane l holds z_l of the tail's rounds in zr; C is the
-// beta prefix before round 0.  Messages go to msg, challenges c0, c0 + 1, ...
-// are recorded with the RNG states after them (and into rec[k], in LDS, when
-// rec is not NULL).  Returns beta over every round; st becomes the state
-// after the last challenge.
-__device__ __forceinline__ u64 ptail_rounds(u64 *V, u64 *B, u32 L, u64 zr, u64 C, u64 &st, u32 c0, u64 *msg,
-                                            const ProofPtrs &pp, u64 *rec = nullptr) {
-    __shared__ u64 s_cz[2][TAIL_LOG];  // C_j and z_j of each round
+// p-phase rounds in one workgroup over v, the level's 2^L <= TAIL_LIM entries
+// (thread tid holds entries tid and tid + SBLOCK, 0 past the end).  The column
+// sums of the first L - 5 rounds (see FIN_P: weights of the other five
+// coordinates, one product an entry) are complete at a barrier; the entries
+// are then folded by those rounds' challenges at once, and the 32 (or fewer)
+// left are the last five rounds' column sums themselves.  Both go to cols;
+// ST_FINISH forms the messages from them.  Lane off + k of every wave holds
+// z of round k in zl and receives its challenge in rl; st becomes the state
+// after them.  lds: PT_LDS words.  A round at a time (sums, barrier, fold,
+// barrier, ten times) took 13.9 us a tail; this takes 5.
+constexpr u32 PT_LDS = 32 * (3 + NWAVES);
+__device__ __forceinline__ void ptail_rounds(const u64 (&v)[2], u32 L, u32 off, u64 zl, u64 &rl, u64 &st, u64 *cols,
+                                             u64 *lds) {
+    u64 *s_w = lds, *s_chi = lds + 32, *s_v = lds + 64, (*s_part)[32] = reinterpret_cast<u64 (*)[32]>(lds + 96);
     const u32 tid = threadIdx.x, lane = tid & 63;
     const u32 w = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));  // wave-uniform
-    const u32 n = 1u << L;
-    u64 (*mp)[TAIL_SLOTS] = tail_parts();
-    for (u32 k = 0, nk = n; nk > 1; nk >>= 1, k++) {
-        const u32 half = nk >> 1, qb = n - nk;
-        const u64 r = fp::sm_field(st);  // challenge k: used after message k's sums
-        const u64 z = lane_value(zr, k);
-        if (tid == 0) {
-            s_cz[0][k] = C;
-            s_cz[1][k] = z;
+    const u32 Ra = L > P_LAST ? L - P_LAST : 0, Rb = L - Ra, nc = 1u << Ra;
+    if (Ra) {
+        rl = draw_lanes(st, Ra, off, rl);  // used after the sums are complete
+        if (w == 0 && lane < 32) {  // weights of the last coordinates (Rb = P_LAST)
+            u64 f[P_LAST];
+#pragma unroll
+            for (u32 k = 0; k < P_LAST; k++) f[k] = fp::eqbit((lane >> k) & 1, lane_value(zl, off + Ra + k));
+            s_w[lane] = mul(mul(mul(f[0], f[1]), mul(f[2], f[3])), f[4]);
         }
-        if (half >= 64) {  // thread tid takes pair qb + tid (whole waves)
-            const u32 q = qb + tid;
-            u64x2 pv = {0, 0};
-            if (tid < half) {
-                pv = ld2(V, 2 * q);
-                const u64 b = B[q];
-                u64 t[3] = {mul(b, pv.x), mul(b, pv.y), fp::red128(fp::wide(b, 2 * pv.y + (fp::P - pv.x)))};
-                chunk_sums(t, q >> 6, lane);
-                if (tid < half / 2) {  // B at the pairs of the next level
-                    const u32 q2 = n - half + tid;
-                    const u64x2 pb = ld2(B, 2 * q2 - n);
-                    B[q2] = add(pb.x, pb.y);
-                }
-            }
-            __syncthreads();  // message k's sums are complete
-            if (tid < half) V[n + q] = fold1(pv.x, pv.y, r);
-        } else {  // wave t < 3 sums value t over the pairs, lane m < half taking pair qb + m
-            const u32 q = qb + lane;
-            const bool on = lane < half;
-            u64x2 pv = {0, 0};
-            if (w < 3) {
-                u64 b = 0;
-                if (on) {
-                    pv = ld2(V, 2 * q);
-                    b = B[q];
-                }
-                const u64 x = w == 0 ? pv.x : (w == 1 ? pv.y : 2 * pv.y + (fp::P - pv.x));  // (t = 2: below 3p)
-                const u64 v = wave_sum63_lazy(fp::red128(fp::wide(b, x)));
-                if (lane == 63) mp[w][TAIL_CHUNKS + k] = v;
-                if (w == 1 && lane < half / 2) {  // B at the pairs of the next level
-                    const u32 q2 = n - half + lane;
-                    const u64x2 pb = ld2(B, 2 * q2 - n);
-                    B[q2] = add(pb.x, pb.y);
-                }
-            }
-            __syncthreads();  // message k's sums are complete
-            if (w == 0 && on) V[n + q] = fold1(pv.x, pv.y, r);
+        if (w == NWAVES - 1 && lane < 32) {
+            u64 f[P_LAST];
+#pragma unroll
+            for (u32 k = 0; k < P_LAST; k++) f[k] = k < Ra ? fp::eqbit((lane >> k) & 1, lane_value(rl, off + k)) : 1;
+            s_chi[lane] = mul(mul(mul(f[0], f[1]), mul(f[2], f[3])), f[4]);
         }
-        C = mul(C, fp::eq(z, r));  // the beta prefix of round k + 1
-        if (tid == 0) {
-            pp.chals[c0 + k] = r;
-            pp.rngst[c0 + k + 1] = st;
-            if (rec) rec[k] = r;
+        __syncthreads();
+        u64 t = fp::red128(fp::wide(v[0], s_w[(tid >> Ra) & 31]) + fp::wide(v[1], s_w[((tid + SBLOCK) >> Ra) & 31]));
+        for (u32 b = Ra; b < 6; b++) t = plus_bit(t, b);
+        if (lane < nc) s_part[w][lane] = t;
+        __syncthreads();  // the column sums are complete
+        const u64 chi = s_chi[tid & (nc - 1)];
+        u64 x[2] = {mul(chi, v[0]), mul(chi, v[1])};
+        for (u32 b = 0; b < Ra; b++) {
+            x[0] = plus_bit(x[0], b);
+            x[1] = plus_bit(x[1], b);
         }
-        __syncthreads();  // level k + 1 is complete
+        if ((tid & (nc - 1)) == 0) {
+            if (tid < (1u << L)) s_v[tid >> Ra] = x[0];
+            if (tid + SBLOCK < (1u << L)) s_v[(tid + SBLOCK) >> Ra] = x[1];
+        }
+        if (tid < nc) {
+            u64 s = 0;
+#pragma unroll
+            for (int q = 0; q < NWAVES; q++) s = add(s, s_part[q][tid]);
+            cols[tid] = s;
+        }
+        __syncthreads();  // the last rounds' column sums are complete
+        if (tid < 32) cols[32 + tid] = s_v[tid];
+    } else if (tid < (1u << L)) {
+        cols[32 + tid] = v[0];
     }
-    if (tid < 3 * L) {
-        const u32 k = tid / 3, t = tid - 3 * k;
-        const u64 z = s_cz[1][k];
-        const u64 e = t == 0 ? sub(1, z) : (t == 1 ? z : sub(add(add(z, z), z), 1));
-        msg[3 * k + t] = mul(mul(s_cz[0][k], e), tail_sum(n, k, t));
-    }
-    return C;
+    rl = draw_lanes(st, Rb, off + Ra, rl);
 }
 
-// B_0[m] = prod_{k=1}^{s-1} eq(bit k-1 of m, z_k) for m < 2^{s-1}, the
-// weights of z's suffix (the p-phase's first round pairs V entries 2m,
-// 2m+1); lane l holds z_l in zr.
-// The s - 1 factors are multiplied as a balanced tree (a chain of at most
-// four products instead of s - 1); tree levels no factor reaches are
-// skipped.
-__device__ __forceinline__ void suffix_weights(u64 *B, u32 s, u64 zr) {
-    const u32 nf = s ? s - 1 : 0;
-    for (u32 m = threadIdx.x; m < (1u << s) / 2; m += SBLOCK) {
-        u64 f[TAIL_LOG];
+// Remaining p-phase rounds j0..s-1 (ST_PTAIL), after pend = 3 rounds whose
+// finish this step does itself (everything it reads is loaded before the first
+// wait), or from round 0 (pend = 0).
+__device__ __forceinline__ void step_ptail(const PtailArgs &a, const ProofPtrs &pp, Ctx c, u32 drew, u64 st0,
+                                           u64 st_raw) {
+    const u32 tid = threadIdx.x, lane = tid & 63, pend = a.pend;
+    const u32 L = a.s - a.j0;  // 2^L entries of V^(j0), at most TAIL_LIM
+    u64x2 p[2][4];
 #pragma unroll
-        for (u32 k = 0; k < TAIL_LOG; k++) f[k] = k < nf ? fp::eqbit((m >> k) & 1, lane_value(zr, k + 1)) : 1;
+    for (u32 i = 0; i < 2; i++) {
+        const u32 e = tid + i * SBLOCK;
 #pragma unroll
-        for (u32 w = 1; w < TAIL_LOG; w *= 2) {
-            if (w < nf) {  // (uniform)
-#pragma unroll
-                for (u32 k = 0; k + w < TAIL_LOG; k += 2 * w) f[k] = mul(f[k], f[k + w]);
+        for (u32 k = 0; k < 4; k++) {
+            p[i][k].x = p[i][k].y = 0;
+            if (e < a.live) {
+                if (pend)
+                    p[i][k] = ld2(a.V, 8 * e + 2 * k);
+                else if (k == 0)
+                    p[i][k].x = a.V[e];
             }
         }
-        B[m] = f[0];
     }
-}
-
-// Remaining p-phase rounds j0..s-1 (ST_PTAIL).  The prologue drew the
-// pending challenge(s) up to r_{j0-1} and its finish of round j0-1 computed
-// the beta prefix C.
-__device__ __forceinline__ void step_ptail(const PtailArgs &a, const ProofPtrs &pp, const Ctx c, u32 drew, u64 st0,
-                                           u32 have_c, u64 C0) {
-    __shared__ u64 s_c;
-    u64 *tab = tail_lds();
-    u64 *V = tab, *B = tab + TAIL_TAB;
-    const u32 tid = threadIdx.x, lane = tid & 63;
-    const u32 L = a.s - a.j0, n = 1u << L;  // entries of V^(j0), at most TAIL_LIM
-    for (u32 e = tid; e < n; e += SBLOCK) V[e] = e < a.live ? tail_entry(a.V, e, a.pend, c) : 0;
-    const u64 zr = lane < L ? pp.zbuf[a.j0 + lane] : 0;  // z_{j0 + l} in lane l
-    if (a.B) {
-        for (u32 m = tid; m < n / 2; m += SBLOCK) {  // B_{j0}[m] = B_{j0-1}[2m] + B_{j0-1}[2m+1]
-            const u64x2 pb = ld2(a.B, 2 * m);
-            B[m] = add(pb.x, pb.y);
+    const u64 zl = lane < pend + L ? pp.zbuf[a.j0 - pend + lane] : 0;  // z of the pending rounds, then the tail's
+    const u64 C0 = pp.state[0];
+    u64 rl = 0, st, v[2];
+    if (pend) {
+        st = uniform(st_raw);
+        rl = draw_lanes(st, 3);
+        const u64 x = mul(mul(fp::eqbit(lane & 1, lane_value(rl, 0)), fp::eqbit((lane >> 1) & 1, lane_value(rl, 1))),
+                          fp::eqbit((lane >> 2) & 1, lane_value(rl, 2)));
+        u64 chi[8];  // one weight a lane, then scalars
+#pragma unroll
+        for (u32 e = 0; e < 8; e++) chi[e] = lane_value(x, e);
+#pragma unroll
+        for (u32 i = 0; i < 2; i++) {
+            u128 t = 0;
+#pragma unroll
+            for (u32 k = 0; k < 4; k++) t += fp::wide(chi[2 * k], p[i][k].x) + fp::wide(chi[2 * k + 1], p[i][k].y);
+            v[i] = fp::red128(t);
         }
     } else {
-        suffix_weights(B, L, zr);  // B_{j0}[m] = prod_{k >= 1} eq(bit k-1 of m, z_{j0+k})
+        st = tail_state(pp, a.c0, drew, st0);
+        v[0] = p[0][0].x;
+        v[1] = p[1][0].x;
     }
-    if (!have_c && tid == 0) s_c = pp.state[0];
-    u64 st = tail_state(pp, a.c0, drew, st0);
-    __syncthreads();
-    const u64 C = ptail_rounds(V, B, L, zr, uniform(have_c ? C0 : s_c), st, a.c0, a.msg, pp);
-    if (tid == 0) pp.state[0] = C;  // beta(z, a*)
+    ptail_rounds(v, L, pend, zl, rl, st, a.cols, c.lds);
+    if (tid < 64) {
+        const bool on = lane < pend + L;
+        const u64 C = uniform(mul(C0, row_product(on ? fp::eq(zl, rl) : 1)));
+        if (on) {
+            pp.chals[a.c0 - pend + lane] = rl;
+            a.rec[1 + lane] = zl;
+        }
+        if (tid == 0) {
+            a.rec[0] = C0;
+            pp.state[0] = C;  // beta(z, a*)
+            pp.rngst[a.c0 + L] = st;
+        }
+    }
 }
 
 // ---------------------------------------------------------- line by folding
@@ -1482,7 +1533,7 @@ __device__ __forceinline__ void fold_regs(const u64 (&p)[N][D + 1], const u64 *b
 template <int TB>
 __device__ __forceinline__ void lfold_body(const LfoldArgs &a, const Ctx &c, i32 draw) {
     constexpr int E = 1 << TB;  // entries a thread folds
-    u64 *tab = tail_lds();
+    u64 *tab = c.lds;
     u64 *bk = tab, *dk = tab + 32;
     u64 *buf0 = tab + 64, *buf1 = buf0 + SBLOCK * (TB + 1);  // 512 x (TB+1), then 256 x (TB+2) words
     const u32 tid = threadIdx.x;
@@ -1627,10 +1678,10 @@ __device__ __forceinline__ void top_line(u32 sp, const u64 *bst, const u64 *cst,
     }
 }
 
-__device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp) {
+__device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp, const Ctx c) {
     __shared__ u64 s_r[3 * TAIL_LOG];  // the layer's challenges: a*, then b*, then c*
     __shared__ u64 s_st;
-    u64 *tab = tail_lds();
+    u64 *tab = c.lds;
     u64 *X = tab, *Y = tab + TAIL_TAB, *Z = tab + 2 * TAIL_TAB;
     u64 *eqa = Y + TAIL_TAB - 128, *eqb = eqa + 64;  // eq halves: lo in [0, 32), hi in [32, 64)
     const u32 tid = threadIdx.x, lane = tid & 63;
@@ -1690,14 +1741,21 @@ __device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp) 
         const TopLayer &Ld = a.L[i];
         const u32 s = Ld.s, sp = Ld.sp, n = s + 2 * sp, N = 1u << sp;
         const bool hc = Ld.kind != 1;  // a layer with ADD gates has a C table
-        // p-phase over V_i (level 0 of Z), B in X; beta starts at 1
+        // p-phase over V_i (level 0 of Z); beta starts at 1
         u64 beta = 1;
         if (s > 0) {
-            suffix_weights(X, s, zr);
-            __syncthreads();
-            beta = ptail_rounds(Z, X, s, zr, 1, st, Ld.co, Ld.msg, pp, s_r);
+            u64 v[2], rl = 0;
+#pragma unroll
+            for (u32 e = 0; e < 2; e++) v[e] = tid + e * SBLOCK < (1u << s) ? Z[tid + e * SBLOCK] : 0;
+            ptail_rounds(v, s, 0, zr, rl, st, Ld.cols, X);
+            beta = uniform(row_product(lane < s ? fp::eq(zr, rl) : 1));
+            if (tid < s) {
+                pp.chals[Ld.co + tid] = s_r[tid] = rl;
+                Ld.rec[1 + tid] = zr;
+            }
+            if (tid == 0) Ld.rec[0] = 1;
         }
-        __syncthreads();  // the p-phase's reads of Z and of its partial sums are done
+        __syncthreads();  // the p-phase's reads of Z are done
         // phase 1: F = V_{i+1} into Z, A and C from the gates on in1
         for (u32 e = tid; e < N; e += SBLOCK) Z[e] = Ld.Vn[e];
         eq_halves_lds(s_r, s, eqa, eqa + 32);
@@ -1743,8 +1801,7 @@ __device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp) 
 // which only folds the previous rows into the message (so that work runs
 // beside the body instead of ahead of it) and records the drawn challenge.
 template <u32 KIND, int GK, int PH>
-__device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
-    __shared__ u64 s_c;
+__device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
     __shared__ u64 s_pt[64];  // a point (EQ), or b* and c* (LT), or z_{i+1} (FIN_LINE)
     const Fin &f = sd.fin;
     const ProofPtrs &pp = sd.pp;
@@ -1756,6 +1813,7 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
     const bool fin_block = split && lb == sd.nblocks;
     const bool recorder = split ? fin_block : lb == 0;
     Ctx c;
+    c.lds = lds;
     c.lb = lb;
     c.nb = sd.nblocks;
     c.gtid = (u64)c.lb * SBLOCK + threadIdx.x;
@@ -1767,35 +1825,37 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
     u64 st_after = 0;
     c.r = 0;
     c.r2 = 0;
-    if (f.draw >= 0) {
-        u64 st = pp.rngst[f.draw];
-        c.r = fp::sm_field(st);
-        const u64 st1 = st;
-        const bool two = f.kind == FIN_P2 || f.kind == FIN_T2;  // two rounds finish here
-        if (two) c.r2 = fp::sm_field(st);
-        if (recorder && threadIdx.x == 0) {
-            pp.chals[f.draw] = c.r;
-            pp.rngst[f.draw + 1] = st1;
-            if (two) {
-                pp.chals[f.draw + 1] = c.r2;
-                pp.rngst[f.draw + 2] = st;
-            }
-        }
+    c.rl = 0;
+    const u64 st_raw = f.draw >= 0 ? pp.rngst[f.draw] : 0;
+    auto draw = [&]() {
+        if (f.draw < 0) return;
+        u64 st = uniform(st_raw);
+        const u32 nd = f.kind == FIN_T2 ? 2 : ((fin_mask(KIND) & (1u << FIN_P)) && f.kind == FIN_P ? f.R : 1);
+        c.rl = draw_lanes(st, nd);
+        c.r = lane_value(c.rl, 0);
+        c.r2 = lane_value(c.rl, 1);
+        if (recorder && threadIdx.x < nd) pp.chals[f.draw + threadIdx.x] = c.rl;
+        if (recorder && threadIdx.x == 0) pp.rngst[f.draw + nd] = st;
         st_after = st;  // the state after the drawn challenge(s)
-    }
-    TailIn ti = {st_after, 0, f.draw >= 0 ? 1u : 0u, 0u};
+    };
+    // a p-phase tail finishes the rounds before it itself; a later p-phase
+    // step's body draws after issuing its loads
+    const bool own_fin = (KIND == ST_PTAIL || KIND == KALL) && kind == ST_PTAIL && f.kind == FIN_P;
+    const bool pfirst = (KIND == ST_P || KIND == KALL) && kind == ST_P && sd.u.p.pend == 0;
+    const bool late = own_fin || ((KIND == ST_P || KIND == KALL) && kind == ST_P && !pfirst && !fin_block);
+    if (!late) draw();
+    TailIn ti = {st_after, f.draw >= 0 ? 1u : 0u};
     // points assembled in LDS (challenges drawn by earlier launches are in
     // chals; the one drawn just now is c.r)
     const bool line_fin = (fin_mask(KIND) & (1u << FIN_LINE)) && f.kind == FIN_LINE;
-    if (line_fin || kind == ST_EQ || kind == ST_LT) {  // (uniform)
+    if (line_fin || kind == ST_EQ || kind == ST_LT || pfirst) {  // (uniform)
         if (line_fin && threadIdx.x < f.sp) {
             const u64 bb = f.bstar[threadIdx.x], cc = f.cstar[threadIdx.x];
             s_pt[threadIdx.x] = add(bb, mul(c.r, sub(cc, bb)));  // z_{i+1} = l(tau)
         }
-        if (kind == ST_EQ && sd.u.eq.point == PT_Z && f.kind != FIN_LINE &&
-            threadIdx.x < sd.u.eq.base + sd.u.eq.n)
+        if (pfirst && !line_fin && threadIdx.x < sd.u.p.s)
             s_pt[threadIdx.x] = pp.zbuf[threadIdx.x];  // z of the layer, already recorded
-        if (kind == ST_EQ && sd.u.eq.point == PT_CHAL && threadIdx.x < sd.u.eq.n) {
+        if (kind == ST_EQ && threadIdx.x < sd.u.eq.n) {
             const i32 ci = (i32)(sd.u.eq.base + threadIdx.x);
             s_pt[threadIdx.x] = ci == f.draw ? c.r : pp.chals[ci];
         }
@@ -1807,16 +1867,11 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
         }
         __syncthreads();
     }
-    if (fin_block || (tail && has_fin)) {
-        fin_inline<KIND>(sd, c, s_pt, &s_c);
+    if (fin_block || (tail && has_fin && !own_fin)) {
+        fin_inline<KIND>(sd, c, s_pt);
         if (fin_block) return;
     }
     if (tail && has_fin) {
-        if (kind == ST_PTAIL && (f.kind == FIN_P || f.kind == FIN_P2)) {
-            __syncthreads();
-            ti.have_c = 1;
-            ti.C = s_c;
-        }
         if ((fin_mask(KIND) & (1u << FIN_LINE)) && f.kind == FIN_LINE) __syncthreads();  // z_{i+1} stored
     }
 
@@ -1827,9 +1882,12 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
         case ST_EVAL: step_eval(sd.u.eval, c); break;
         case ST_START: step_start(sd.u.start, pp, c); break;
         case ST_EQ:
-            step_eq(sd.u.eq, c, sd.u.eq.point == PT_Z ? s_pt + sd.u.eq.base : s_pt, pp);
+            step_eq(sd.u.eq, c, s_pt, pp);
             break;
-        case ST_P: step_p<KIND == ST_P ? GK : -1>(sd.u.p, c, row); break;
+        case ST_P:
+            step_p<KIND == ST_P ? GK : -1>(sd.u.p, c, pfirst ? s_pt : pp.zbuf,
+                                           sd.rows + ((u64)c.lb << sd.u.p.R), draw);
+            break;
         case ST_W: {
             const WArgs &a = sd.u.w;
             if (GK >= 0) {
@@ -1853,10 +1911,10 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
         case ST_WA0: step_wa0<KIND == ST_WA0 ? GK : -1, KIND == ST_WA0 ? PH : 0>(sd.u.wa0, pp, c, row); break;
         case ST_WT: step_wt<KIND == ST_WT ? GK : -1>(sd.u.wt, c, row); break;
         case ST_WTAIL: step_wtail<KIND == ST_WTAIL ? GK : -1>(sd.u.wtail, pp, c, ti.drew, ti.st); break;
-        case ST_PTAIL: step_ptail(sd.u.ptail, pp, c, ti.drew, ti.st, ti.have_c, ti.C); break;
+        case ST_PTAIL: step_ptail(sd.u.ptail, pp, c, ti.drew, ti.st, st_raw); break;
         case ST_FINISH: step_finish(sd.u.finish, c); break;
         case ST_WSMALL: step_wsmall(sd.u.wsmall, pp, c); break;
-        case ST_TOP: step_top(sd.u.top, pp); break;
+        case ST_TOP: step_top(sd.u.top, pp, c); break;
         case ST_LFOLD: step_lfold(sd.u.lfold, c, f.draw); break;
         case ST_SGE:
             if (c.lb == 0 && threadIdx.x == 0) {
@@ -1870,12 +1928,27 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb) {
     }
 }
 
+// LDS words of a kind's body (the kernel of mixed batches holds every kind's
+// code, and its LDS decides how many workgroups a CU takes).
+constexpr u32 lds_words(u32 kind) {
+    return kind == ST_P       ? 64 + NWAVES * 64
+           : kind == ST_PTAIL ? PT_LDS
+           : kind == ST_FINISH ? SBLOCK
+           : kind == ST_LINE   ? 64 * LINE_CHUNK
+           : kind == ST_LFOLD  ? 64 + SBLOCK * 6 + SBLOCK / 2 * 7
+           : kind == KALL || kind == ST_WTAIL || kind == ST_WSMALL || kind == ST_TOP ? 3 * TAIL_TAB
+                               : 2;
+}
+static_assert(64 + SBLOCK * 6 + SBLOCK / 2 * 7 <= 3 * TAIL_TAB && 64 + NWAVES * 64 >= (1 << P_ROUNDS) + NWAVES * 8,
+              "lds_words");
+
 // A single proof's step, its descriptor passed by value as kernel argument;
 // one instantiation per step kind (and per gate mix and phase for omega
 // rounds) keeps each kernel's code and registers to what the kind needs.
 template <u32 KIND, int GK, int PH>
 __global__ void __launch_bounds__(SBLOCK) k_step_one(const StepDesc sd) {
-    run_step<KIND, GK, PH>(sd, blockIdx.x);
+    __shared__ __align__(16) u64 lds[lds_words(KIND)];
+    run_step<KIND, GK, PH>(sd, blockIdx.x, lds);
 }
 
 // One step of each of several proofs.
@@ -1886,7 +1959,8 @@ __global__ void __launch_bounds__(SBLOCK) k_step_jobs(const JobEntry *__restrict
         const u32 mid = (lo + hi) >> 1;
         if (jobs[mid].block0 <= b) lo = mid; else hi = mid;
     }
-    run_step<KALL, -1, 0>(*jobs[lo].step, b - jobs[lo].block0);
+    __shared__ __align__(16) u64 lds[lds_words(KALL)];
+    run_step<KALL, -1, 0>(*jobs[lo].step, b - jobs[lo].block0, lds);
 }
 
 // One step of each of several proofs, the job table in the kernel arguments.
@@ -1897,7 +1971,8 @@ __global__ void __launch_bounds__(SBLOCK) k_step_table(const JobTable t) {
         const u32 mid = (lo + hi) >> 1;
         if (t.e[mid].block0 <= b) lo = mid; else hi = mid;
     }
-    run_step<KALL, -1, 0>(*t.e[lo].step, b - t.e[lo].block0);
+    __shared__ __align__(16) u64 lds[lds_words(KALL)];
+    run_step<KALL, -1, 0>(*t.e[lo].step, b - t.e[lo].block0, lds);
 }
 
 hipError_t launch_step_table(hipStream_t st, const JobTable &t) {
@@ -1922,7 +1997,7 @@ hipError_t launch_step(hipStream_t st, const StepDesc &sd, hipEvent_t ev0, hipEv
         case ST_START: L1(ST_START); break;
         case ST_EQ: L1(ST_EQ); break;
         case ST_P:  // one kernel for the phase's first step, one for the others
-            if (sd.u.p.first) LK(ST_P, 1, 0); else LK(ST_P, 0, 0);
+            if (sd.u.p.pend == 0) LK(ST_P, 1, 0); else LK(ST_P, 0, 0);
             break;
         case ST_W:
             if (sd.u.w.ph == 1) {

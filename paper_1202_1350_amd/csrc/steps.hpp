@@ -64,21 +64,22 @@ enum StepKind : u32 {
 
 enum FinKind : u32 {
     FIN_NONE = 0,
-    FIN_P,     // p-phase message from rows of (S0, S1)
+    FIN_P,     // R p-phase messages from rows of 2^R column sums
     FIN_W,     // omega message from rows of (E0, E1, O0, O1)
     FIN_LINE,  // h(t) values from rows of line sums; then tau and z_{i+1}
     FIN_T,     // message (G(0), G(1), G(2)) from rows of three sums
-    FIN_P2,    // two p-phase messages from rows of (S0, S1, U0, U1, W0, W1)
     FIN_T2,    // two table-round messages from rows of (G(0..2), Q0(0..2), Q1(0..2), Q2(0..2))
 };
 
-// Two rounds per launch.  The sums of round k+1 are, before r_k is known,
-// polynomials in r_k with coefficients that are sums over the level-k
-// tables: a step that reaches round k also sums those coefficients, and the
-// finish of its rows writes message k, draws r_k, evaluates message k+1 at
-// r_k, writes it and draws r_{k+1}.
-//   p-phase: S0' = U0 + r_k U1, S1' = W0 + r_k W1.
-//   table rounds: G'(t) = Q0(t) + r_k Q1(t) + r_k^2 Q2(t).
+// Several rounds per launch.  The sums of a later round are, before the
+// challenges between are known, polynomials in them with coefficients that are
+// sums over the present tables: a step also sums those coefficients, and the
+// messages follow from its rows and the challenges.
+//   p-phase, R rounds: V_j's entries with equal low R index bits x, weighted
+//     by eq(z, their other bits), add up to 2^R column sums T[x]; round k's
+//     S_t = sum over x with bit k = t of T[x] prod_{i<k} eq(x_i, r_i)
+//     prod_{i>k} eq(x_i, z_i), at one product an entry.
+//   table rounds, two: G'(t) = Q0(t) + r_k Q1(t) + r_k^2 Q2(t).
 
 constexpr u32 KALL = 0xFFFF;  // kind resolved at run time (mixed batches)
 
@@ -86,8 +87,8 @@ constexpr u32 KALL = 0xFFFF;  // kind resolved at run time (mixed batches)
 // each kernel instantiation compiles only these.
 __host__ __device__ constexpr u32 fin_mask(u32 kind) {
     return kind == KALL                              ? 0xFFu
-           : kind == ST_P                            ? 1u << FIN_P2
-           : kind == ST_PTAIL                        ? (1u << FIN_P) | (1u << FIN_P2) | (1u << FIN_LINE)
+           : kind == ST_P                            ? (1u << FIN_P) | (1u << FIN_LINE)
+           : kind == ST_PTAIL                        ? (1u << FIN_P) | (1u << FIN_LINE)
            : kind == ST_WT                           ? (1u << FIN_T) | (1u << FIN_T2)
            : kind == ST_WTAIL                        ? (1u << FIN_T) | (1u << FIN_T2)
            : kind == ST_EQ                           ? (1u << FIN_LINE) | (1u << FIN_W)
@@ -99,12 +100,7 @@ __host__ __device__ constexpr u32 fin_mask(u32 kind) {
 // Largest table (entries at the level a tail starts from, after its fold)
 // that a one-workgroup tail keeps in LDS.
 constexpr int TAIL_LIM = 1024;
-
-// The point the ST_EQ step expands, assembled in LDS by each workgroup.
-enum PointKind : u32 {
-    PT_Z = 0,  // z_i[1..s): computed from the previous layer's line and tau
-    PT_CHAL,   // challenges chals[base .. base+n) (the last may be drawn now)
-};
+constexpr int TAIL_LOG = 10;  // log2(TAIL_LIM): rounds of a tail
 
 // Per-proof device state shared by all steps of a proof.
 struct ProofPtrs {
@@ -118,14 +114,19 @@ struct ProofPtrs {
 
 // Prologue: finish the previous round and/or draw challenge `draw`.  The
 // message values themselves are written by ST_FINISH from `rows` (and, for
-// p-phase rounds, the beta prefix and z values recorded in `rec`).
+// p-phase rounds, the beta prefix and z values recorded in `rec`, P_REC words).
+constexpr u32 P_ROUNDS = 7;  // most p-phase rounds a step sums (2^7 columns)
+constexpr u32 P_REC = 16;    // C and up to 15 z values
+constexpr u32 P_LAST = 5;    // a tail's last rounds, summed together
+constexpr u32 PT_COLS = 64;  // words of a tail's columns: its first rounds' at 0, the last ones' at 32
 struct Fin {
     u32 kind;          // FinKind
     i32 draw;          // challenge index drawn here (-1: none)
     const u64 *rows;   // partial rows of the previous step
     u32 nrows;
-    u64 *rec;          // FIN_P / FIN_P2: C, z_j (, z_{j+1}) at the time of the round
-    u32 j;             // FIN_P: round index (z_j)
+    u64 *rec;          // FIN_P: C, z_j .. z_{j+R-1} at the time of the rounds
+    u32 j;             // FIN_P: first round's index (z_j)
+    u32 R;             // FIN_P: rounds finished (challenges draw .. draw + R - 1)
     u32 last;          // FIN_W: 1 / 2 = end of phase 1 / 2 (v1 / v2)
     u32 T;             // FIN_LINE: number of line values
     u32 sp;            // FIN_LINE: coordinates of z_{i+1}
@@ -143,9 +144,10 @@ struct FinItem {
     u32 nrows;
     const u64 *rows;
     u64 *msg;
-    const u64 *rec;    // FIN_P / FIN_P2
-    i32 draw;          // FIN_P2 / FIN_T2: the challenge drawn after the first message
-    u32 nvals;         // FIN_LINE: values of this chunk
+    const u64 *rec;    // FIN_P
+    i32 draw;          // FIN_T2: the challenge drawn after the first message; FIN_P: of rec's first z
+    u32 nvals;         // FIN_LINE: values of this chunk; FIN_P: rounds
+    u32 pre;           // FIN_P: rounds between rec's C and the first of these
 };
 struct FinishArgs {
     const FinItem *items;  // one per workgroup
@@ -170,28 +172,23 @@ struct StartArgs {
     const u64 *V0;
 };
 struct EqArgs {
-    u32 point;  // PointKind
-    u32 n;      // coordinates
+    u32 n;      // coordinates: challenges chals[base .. base+n) (the last may be drawn now)
     u32 L;      // lo table covers coordinates [0, L)
-    u32 base;   // PT_CHAL: first challenge index; PT_Z: first coordinate of z
+    u32 base;
     u64 *lo, *hi;
     u32 beta_lo;  // a*: lo entries times beta(z, a*) (state[0]), so that a gate's
                   // weight beta chi_g(a*) is lo[g mod 2^L] hi[g >> L]
 };
-// p-phase grid step.  first: round 0 (and 1) on V_i and the eq tables of
-// z_i[1..s); a unit is a quad of V_i (look) or a pair (s = 1); writes
-// B_1 (look).  Otherwise: rounds j+2, j+3 from V^(j) and B_{j+1} folded by
-// r_j, r_{j+1}; a unit is a quad of V^(j+2) (16 entries of V^(j), 4 of
-// B_{j+1}); writes V^(j+2) and B_{j+3}.
+// p-phase grid step.  pend = 0: rounds 0 .. R-1 of V_i, its column sums
+// weighted by eq over z_i[R..s), in runs of SBLOCK entries (nu of them).
+// pend >= 3: V^(j) from V^(j-pend) folded by the pend challenges just drawn,
+// stored, and its 2^3 column sums (R = 3); a unit is eight entries of V^(j),
+// of which live are not zero.
 struct PArgs {
-    u32 first, look;
-    u64 nu;        // units
+    u32 pend, R, s, j;
+    u64 nu, live;
     const u64 *Vsrc;
     u64 *Vout;
-    const u64 *Bprev;
-    u64 *Bout;
-    const u64 *zlo, *zhi;
-    u32 L;
 };
 struct WArgs {
     u32 kind, ph, init, write_w, inline_fold;
@@ -328,13 +325,13 @@ struct WtailArgs {
 };
 struct PtailArgs {
     u32 j0, s;
-    u32 pend;                // challenges the prologue drew (1 or 2; 0 when j0 = 0)
+    u32 pend;                // challenges the prologue drew (3; 0 when j0 = 0)
     u32 live;                // entries [live, 2^{s-j0}) of V^(j0) are zero (not read)
-    const u64 *V, *B;        // V^(j0-pend) (2^{s-j0+pend}) and B_{j0-1} (2^{s-j0});
-                             // B NULL: B_{j0} is formed from z (j0 = 0, or the grid
-                             // steps wrote B below the live entries only)
+    const u64 *V;            // V^(j0-pend)
     u32 c0;                  // challenge index of round j0
     u64 *msg;                // message slot of round j0
+    u64 *rec;                // C and z of the pending and the tail's rounds
+    u64 *cols;               // PT_COLS words
 };
 
 // A small layer's whole omega phase in one workgroup: w as for ST_WA0
@@ -363,6 +360,7 @@ struct TopLayer {
     const u32 *in1, *in2;      // its wiring (evaluation)
     const u8 *type;            // its gate types (mixed layers)
     u64 *V;                    // V_i, written by the evaluation
+    u64 *rec, *cols;           // the p-phase's record and columns (as PtailArgs)
 };
 // ST_TOP also evaluates its layers, nl - 1 down to 0, from V_nl (the layer
 // below them, evaluated by ST_EVAL launches), and starts the proof as
