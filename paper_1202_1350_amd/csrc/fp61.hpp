@@ -29,6 +29,15 @@ __host__ __device__ __forceinline__ u64 sub(u64 a, u64 b) {
 // result apply canon() afterwards.
 __host__ __device__ __forceinline__ u64 fold64(u64 x) { return (x & P) + (x >> 61); }
 
+// fold64 in three instructions: a multiply-add by 1 takes the high bits
+// without widening them to a register pair.
+__device__ __forceinline__ u64 fold64_mad(u64 x) {
+    const u32 t = (u32)(x >> 61);
+    x &= P;
+    asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(x) : "v"(t) : "vcc");
+    return x;
+}
+
 __host__ __device__ __forceinline__ u64 canon(u64 x) { return x >= P ? x - P : x; }
 
 __host__ __device__ __forceinline__ u64 mul(u64 a, u64 b) {

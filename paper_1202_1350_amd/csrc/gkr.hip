@@ -979,10 +979,17 @@ struct Planner {
         recs_used += P_REC;
         return r;
     }
-    u64 *take_cols() {
+    u64 *take_cols(u32 words) {
         u64 *r = w ? w->rowpool + rows_used : nullptr;
-        rows_used += PT_COLS;
+        rows_used += words;
         return r;
+    }
+    // Message slot of the round whose challenge has index ci.
+    u64 *msg_at(u32 ci) const {
+        if (!w) return nullptr;
+        u32 i = 0;
+        while (i + 1 < c->co.size() && c->co[i + 1] <= ci) i++;
+        return w->msgs + c->mo[i] + 3ull * (ci - c->co[i]);
     }
     // The finish step: one item per message (per chunk of line values, per
     // step's p-phase rounds).
@@ -994,14 +1001,30 @@ struct Planner {
             items.push_back(FinItem{FIN_P, 1, cols ? cols + 32 : nullptr, msg ? msg + 3 * Ra : nullptr, rec, draw,
                                     L - Ra, pre + Ra});
         };
-        for (const TopLayer &t : top)
+        // an omega tail's: three rounds a step
+        auto w_tail = [&](u32 L, i32 draw, u64 *msg, const u64 *cols) {
+            for (u32 k = 0; k < L; k += 3)
+                items.push_back(FinItem{FIN_T, 1, cols ? cols + k / 3 * T_ROW : nullptr, msg ? msg + 3 * k : nullptr,
+                                        nullptr, draw + (i32)k, std::min<u32>(3, L - k), 0});
+        };
+        for (const TopLayer &t : top) {
             if (t.s) p_tail(t.s, 0, (i32)t.co, t.msg, t.rec, t.cols);
+            for (u32 ph = 0; ph < 2; ph++) {
+                const u32 at = t.s + ph * t.sp;
+                w_tail(t.sp, (i32)(t.co + at), t.msg ? t.msg + 3 * at : nullptr, t.wcols[ph]);
+            }
+        }
         for (const StepDesc &sd : out) {
             const Fin &f = sd.fin;
             if (sd.kind == ST_PTAIL) {
                 const PtailArgs &a = sd.u.ptail;
                 p_tail(a.s - a.j0, a.pend, (i32)(a.c0 - a.pend), a.msg, a.rec, a.cols);
             }
+            if (sd.kind == ST_WTAIL) {
+                const WtailArgs &a = sd.u.wtail;
+                w_tail(a.sp - a.k0, (i32)a.c0, msg_at(a.c0), a.cols);
+            }
+            if (sd.kind == ST_WSMALL) w_tail(sd.u.wsmall.sp, (i32)sd.u.wsmall.c0, msg_at(sd.u.wsmall.c0), sd.u.wsmall.cols);
             if (f.kind == FIN_NONE) continue;
             if (f.kind == FIN_LINE) {
                 for (u32 q = 0; q * f.ch < f.T; q++)
@@ -1016,7 +1039,7 @@ struct Planner {
         double nbytes = 0;
         for (const FinItem &it : items)
             nbytes += it.nrows * 8.0 * (it.kind == FIN_P ? 1 << it.nvals : it.kind == FIN_W ? 4
-                                        : it.kind == FIN_T ? 3 : it.kind == FIN_T2 ? 12 : LINE_CHUNK);
+                                        : it.kind == FIN_T ? (int)T_ROW : LINE_CHUNK);
         StepDesc &s = add(ST_FINISH, (u32)items.size(), nbytes);
         s.u.finish = FinishArgs{w ? w->d_items : nullptr, w ? w->chals : nullptr};
     }
@@ -1087,7 +1110,8 @@ struct Planner {
                     t.types[ph - 1] = g.types;
                 }
                 t.rec = take_rec();
-                t.cols = take_cols();
+                t.cols = take_cols(PT_COLS);
+                for (u32 ph = 0; ph < 2; ph++) t.wcols[ph] = take_cols(WT_COLS);
                 top.push_back(t);
                 sc_first[i] = sc_last[i] = (int)out.size();
                 // V_{i+1} 8 per entry; per phase: row pointers 4 per wire, sorted
@@ -1196,7 +1220,7 @@ struct Planner {
                 pt.c0 = co + lev;
                 pt.msg = w ? msg + 3ull * lev : nullptr;
                 pt.rec = lev ? f.rec : take_rec();
-                pt.cols = take_cols();
+                pt.cols = take_cols(PT_COLS);
                 st.u.ptail = pt;
             } else if (layer_end.kind != FIN_NONE) {  // no p-phase: a step for the previous layer's finish
                 StepDesc &e = add(ST_END, 1, 0);
@@ -1246,14 +1270,11 @@ struct Planner {
             };
             const u64 ntab = sp >= 2 ? (u64)(sp - 1) * ((1ull << Ll) + (1ull << M) + (1ull << H)) : 1;
             if (c->omega_algo != GKR_OMEGA_GATES) {
-                // ---- omega-phases over tables (a6, a7, a8): round 0 (and
-                // round 1's coefficients) with the level-0 tables, then grid
-                // steps of two rounds while the tables are large, then the
-                // remaining rounds in one workgroup from round k0
-                // Round 0 with the level-0 tables.  If level 1 fits a tail it
-                // starts at round 1; otherwise a step folding once gives round 1
-                // and round 2's coefficients, steps folding twice follow, and
-                // the tail starts at an odd round k0 >= 3 (2^(s' - k0) <= TAIL_LIM).
+                // ---- omega-phases over tables (a6, a7, a8): rounds 0..2 with
+                // the level-0 tables, then grid steps of three rounds while the
+                // tables are large, then the remaining rounds in one workgroup
+                // from round k0, a multiple of 3 (2^(s' - k0) <= TAIL_LIM; 0
+                // where level 0 fits it: the first step only forms the tables)
                 if (wsmall) {
                     for (u32 ph = 1; ph <= 2; ph++) {
                         const u32 rbase = s + (ph == 2 ? sp : 0);
@@ -1264,7 +1285,7 @@ struct Planner {
                         a.w.kind = kind;
                         a.w.ph = ph;
                         a.w.hasC = kind != KIND_MUL;
-                        a.w.npairs = (1ull << sp) / 2;
+                        a.w.nw = 1ull << sp;
                         a.w.perm = dg->perm;
                         a.w.rowptr = dg->rowptr;
                         a.w.oths = dg->oths;
@@ -1284,7 +1305,7 @@ struct Planner {
                         a.sp = sp;
                         a.last = ph;
                         a.c0 = co + rbase;
-                        a.msg = w ? msg + 3ull * rbase : nullptr;
+                        a.cols = take_cols(WT_COLS);
                         a.vout = vslot ? vslot + (ph - 1) : nullptr;
                         // eq entries 8, per gate sorted index 4 + other 4 + operand 8, per wire F 8
                         const u64 ne = (1ull << (a.eqn / 2)) + (1ull << (a.eqn - a.eqn / 2));
@@ -1294,8 +1315,7 @@ struct Planner {
                     }
                 } else {
                 const u64 N = 1ull << sp;
-                u32 k0 = 1;
-                if (sp > 11) k0 = std::max<u32>(3, (sp - 10) | 1u);
+                const u32 k0 = sp > (u32)TAIL_LOG ? (sp - TAIL_LOG + 2) / 3 * 3 : 0;
                 // Entries above c->wlive[i] stay zero at every level, so the
                 // grid steps take only the first NL entries of level 0 (NL
                 // a multiple of 2^k0: every step's range is then exact) and
@@ -1321,7 +1341,8 @@ struct Planner {
                         a.kind = kind;
                         a.ph = ph;
                         a.hasC = hasC;
-                        a.npairs = NL / 2;
+                        a.sum = k0 > 0;
+                        a.nw = NL;
                         a.perm = dg->perm;
                         a.rowptr = dg->rowptr;
                         a.oths = dg->oths;
@@ -1337,14 +1358,14 @@ struct Planner {
                         a.C = w ? w->tC0 : nullptr;
                         // per gate: perm 4, other wire 4, operand gather 8 (ph 1), type 1;
                         // per table entry: chunk index 4, F 8, A 8 (+ C 8)
-                        StepDesc &st = addg(ST_WA0, NL / 2, 1,
+                        StepDesc &st = addg(ST_WA0, NL, 1,
                                            S * (8.0 + (ph == 1 ? 8 : 0) + (kind == KIND_MIXED)) +
                                                NL * (4.0 + 8 + 8 + (hasC ? 8 : 0)) + 8.0 * nch);
                         // per gate: chi_g(a*) (1), beta (1), the operand or chi_in1(b*) (1 or 2);
-                        // per wire (phase 2) v1 twice; per pair three term products
-                        mods.back() = S * (ph == 1 ? 3.0 : 4.0) + NL * (ph == 2 ? 2.0 : 0.0) + 1.5 * NL;
+                        // per wire (phase 2) v1 twice; per entry four of an oct's products
+                        mods.back() = S * (ph == 1 ? 3.0 : 4.0) + NL * (ph == 2 ? 2.0 : 0.0) + (k0 ? 4.0 : 0.0) * NL;
                         st.u.wa0 = a;
-                        reduces(3);
+                        if (k0) reduces(T_ROW);
                     } else {
                         // gate sums per chunk, then level-0 tables and round 0
                         {
@@ -1381,69 +1402,67 @@ struct Planner {
                             memset(&a, 0, sizeof a);
                             a.ph = ph;
                             a.hasC = hasC;
-                            a.npairs = NL / 2;
+                            a.sum = k0 > 0;
+                            a.nw = NL;
                             a.xch = dg->xch;
                             a.partA = w ? w->partA : nullptr;
                             a.partC = w ? w->partC : nullptr;
                             a.F = V(i + 1);
                             a.A = w ? w->tA0 : nullptr;
                             a.C = w ? w->tC0 : nullptr;
-                            StepDesc &st = addg(ST_WT0, NL / 2, 1,
+                            StepDesc &st = addg(ST_WT0, NL, 1,
                                                NL * (4.0 + 8 + 8 + (hasC ? 8 : 0)) + 16.0 * nch);
-                            mods.back() = NL * (ph == 2 ? 2.0 : 0.0) + 1.5 * NL;
+                            mods.back() = NL * (ph == 2 ? 2.0 : 0.0) + (k0 ? 4.0 : 0.0) * NL;
                             st.u.wt0 = a;
-                            reduces(3);
+                            if (k0) reduces(T_ROW);
                         }
                     }
-                    // tables of level k (0, or odd k: two buffers alternate)
+                    // tables of level k (0, or a multiple of 3: two buffers alternate)
                     auto level = [&](u32 k, const u64 **A, const u64 **C, const u64 **F) {
                         if (k == 0) {
                             *A = w ? w->tA0 : nullptr;
                             *C = w ? w->tC0 : nullptr;
                             *F = V(i + 1);
                         } else {
-                            const u32 b = ((k - 1) / 2) & 1;
+                            const u32 b = (k / 3 - 1) & 1;
                             *A = w ? w->tA[b] : nullptr;
                             *C = w ? w->tC[b] : nullptr;
                             *F = w ? (b ? w->fB : w->fA) : nullptr;
                         }
                     };
-                    // a table step reading level k with pend pending challenges
-                    auto table_step = [&](u32 k, u32 pend) {
-                        Fin f = fin_of_prev(pend == 1 ? FIN_T : FIN_T2);
+                    auto t_fin = [&](u32 k) {  // the finish of rounds k .. k + 2
+                        Fin f = fin_of_prev(FIN_T);
+                        f.R = 3;
                         f.draw = (i32)(co + rbase + k);
                         f.msg = w ? msg + 3ull * (rbase + k) : nullptr;
+                        return f;
+                    };
+                    for (u32 k = 0; k + 3 < k0; k += 3) {  // the table step forming level k + 3
+                        const Fin f = t_fin(k);
                         WtArgs a;
                         memset(&a, 0, sizeof a);
                         a.hasC = hasC;
-                        a.pend = pend;
-                        a.nu = NL >> (k + pend + 2);  // quads of level k + pend (k + pend + 2 <= k0)
+                        a.nu = NL >> (k + 3);
                         const u64 *A, *C, *F;
                         level(k, &A, &C, &F);
                         a.A = A;
                         a.C = C;
                         a.F = F;
-                        level(k + pend, &A, &C, &F);
+                        level(k + 3, &A, &C, &F);
                         a.An = const_cast<u64 *>(A);
                         a.Cn = const_cast<u64 *>(C);
                         a.Fn = const_cast<u64 *>(F);
-                        // per unit and table: 4 << pend entries read, 4 written
+                        // per unit and table: 8 entries read, one written
                         const double tabs = hasC ? 3.0 : 2.0;
-                        StepDesc &st = addg(ST_WT, 4 * a.nu, 1, a.nu * tabs * 8.0 * ((4u << pend) + 4));
-                        // per quad: each table's four entries folded (one product, or three for two
-                        // challenges), then six products in each of the three value lanes
-                        mods.back() = a.nu * (4.0 * tabs * (pend == 1 ? 1 : 3) + 18.0);
+                        StepDesc &st = addg(ST_WT, a.nu, 1, a.nu * tabs * 8.0 * 9);
+                        // per unit: eight products a table, then four of an oct's
+                        mods.back() = a.nu * (8.0 * tabs + 4.0);
                         st.fin = f;
                         st.u.wt = a;
-                        reduces(12);
-                    };
-                    if (k0 > 1) table_step(0, 1);
-                    for (u32 k = 1; k + 4 <= k0; k += 2) table_step(k, 2);
+                        reduces(T_ROW);
+                    }
                     {
-                        const u32 pend = k0 == 1 ? 1 : 2;
-                        Fin f = fin_of_prev(pend == 1 ? FIN_T : FIN_T2);
-                        f.draw = (i32)(co + rbase + k0 - pend);
-                        f.msg = w ? msg + 3ull * (rbase + k0 - pend) : nullptr;
+                        const u32 pend = k0 ? 3 : 0;
                         WtailArgs a;
                         memset(&a, 0, sizeof a);
                         a.k0 = k0;
@@ -1454,8 +1473,13 @@ struct Planner {
                         a.live = (u32)(NL >> k0);
                         level(k0 - pend, &a.A, &a.C, &a.F);
                         a.c0 = co + rbase + k0;
-                        a.msg = w ? msg + 3ull * (rbase + k0) : nullptr;
+                        a.cols = take_cols(WT_COLS);
                         a.vout = vslot ? vslot + (ph - 1) : nullptr;
+                        Fin f;
+                        memset(&f, 0, sizeof f);
+                        f.kind = FIN_NONE;
+                        f.draw = -1;
+                        if (pend) f = t_fin(k0 - 3);
                         StepDesc &st = add(ST_WTAIL, 1, 24.0 * (1ull << (sp - k0 + pend)));
                         mods.back() = 8.0 * (1ull << (sp - k0 + pend));
                         st.fin = f;

@@ -202,14 +202,7 @@ struct RowArgs {
 // most 2^30.
 
 __device__ __forceinline__ Half halves(u64 x) { return {(u32)x & 0x7fffffffu, (u32)(x >> 31)}; }
-// (x mod 2^61) + (x >> 61) in three instructions (a multiply-add by 1 takes
-// the high bits without widening them).
-__device__ __forceinline__ u64 fold(u64 x) {
-    u32 t = (u32)(x >> 61);
-    x &= P;
-    asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(x) : "v"(t) : "vcc");
-    return x;
-}
+__device__ __forceinline__ u64 fold(u64 x) { return fp::fold64_mad(x); }
 struct Sums {
     u64 ll = 0, mm = 0, hh = 0;
 };

@@ -30,7 +30,10 @@ __device__ __forceinline__ void st2(u64 *p, u64 i, u64 a, u64 b) {
 }
 
 constexpr int NWAVES = SBLOCK / 64;
-constexpr int TAIL_TAB = 2 * TAIL_LIM;  // LDS entries per table of an omega tail: all levels
+// LDS entries per table of an omega tail: 2^10 and the levels of an eighth, a
+// 64th and a 512th after it (and room below for eq halves).
+constexpr int TAIL_TAB = TAIL_LIM + TAIL_LIM / 4;
+constexpr int TAIL_EXTRA = 8 + 2 * T_ROW + 16;  // weights, partial sums, challenges and RNG state after the three tables
 
 // Words for workgroup sums, beside the body's.
 __device__ __forceinline__ u64 *sum_lds() {
@@ -38,27 +41,17 @@ __device__ __forceinline__ u64 *sum_lds() {
     return t;
 }
 
-template <int CTRL, int ROWS>
-__device__ __forceinline__ u64 dpp64(u64 v) {
-    return dppx<CTRL, ROWS>(v);
-}
-// Value of lane Q of this lane's quad (lanes 4m..4m+3).
-template <int Q>
-__device__ __forceinline__ u64 quad_get(u64 v) {
-    return dpp64<Q | (Q << 2) | (Q << 4) | (Q << 6), 0xf>(v);
-}
-
 // Sum over the wave, left in lane 63: prefix sums within each row of 16
 // lanes (shifts 1, 2, 4, 8), then row 0's total into row 1 and row 2's into
 // row 3, then lane 31's into rows 2 and 3.  Lanes a shift leaves without a
 // source read 0.
 __device__ __forceinline__ u64 wave_sum63(u64 v) {
-    v = add(v, dpp64<0x111, 0xf>(v));  // row_shr:1
-    v = add(v, dpp64<0x112, 0xf>(v));  // row_shr:2
-    v = add(v, dpp64<0x114, 0xf>(v));  // row_shr:4
-    v = add(v, dpp64<0x118, 0xf>(v));  // row_shr:8
-    v = add(v, dpp64<0x142, 0xa>(v));  // row_bcast:15 into rows 1, 3
-    v = add(v, dpp64<0x143, 0xc>(v));  // row_bcast:31 into rows 2, 3
+    v = add(v, dppx<0x111, 0xf>(v));  // row_shr:1
+    v = add(v, dppx<0x112, 0xf>(v));  // row_shr:2
+    v = add(v, dppx<0x114, 0xf>(v));  // row_shr:4
+    v = add(v, dppx<0x118, 0xf>(v));  // row_shr:8
+    v = add(v, dppx<0x142, 0xa>(v));  // row_bcast:15 into rows 1, 3
+    v = add(v, dppx<0x143, 0xc>(v));  // row_bcast:31 into rows 2, 3
     return v;
 }
 
@@ -141,7 +134,6 @@ struct Ctx {
     u32 lb, nb;      // this workgroup within the step, workgroups of the step
     u64 gtid, gstride;
     u64 r;           // challenge drawn in the prologue
-    u64 r2;          // the second one, after a two-round step
     u64 rl;          // lane k: the k-th challenge drawn
 };
 
@@ -151,20 +143,6 @@ struct TailIn {
     u64 st;
     u32 drew;
 };
-
-__device__ __forceinline__ u64 fold1(u64 x0, u64 x1, u64 r) {
-    return fp::red128((u128)x0 + fp::wide(r, x1 + (fp::P - x0)));  // x1 - x0 + p < 2 p, unreduced
-}
-
-// fold1(fold1(x0, x1, r0), fold1(x2, x3, r0), r1) = x0 + r0 (x1 - x0) +
-// r1 (x2 - x0) + r0 r1 ((x3 - x2) - (x1 - x0)), summed in 128 bits
-// and reduced once; r01 = r0 r1.  Inputs canonical.
-__device__ __forceinline__ u64 fold2(u64 x0, u64 x1, u64 x2, u64 x3, u64 r0, u64 r1, u64 r01) {
-    // the differences unreduced: d1, d2 = x1 - x0 + p, x2 - x0 + p < 2 p and
-    // d3 = x3 - x2 - x1 + x0 + 2 p < 4 p, so the sum stays below 8 p^2 + p < 2^125
-    const u64 d1 = x1 + (fp::P - x0), d2 = x2 + (fp::P - x0), d3 = (x3 + x0) + (2 * fp::P - x1 - x2);
-    return fp::red128((u128)x0 + fp::wide(r0, d1) + fp::wide(r1, d2) + fp::wide(r01, d3));
-}
 
 // Value t of a p-phase message from the two sums: G(0) = C (1-z) S0,
 // G(1) = C z S1, G(2) = C (3z - 1)(2 S1 - S0); t is chosen per lane.
@@ -244,6 +222,122 @@ __device__ __forceinline__ u64 beta_prefix(u64 C0, u32 k, const u64 *z, const u6
     return uniform(mul(C0, row_product(lane < k ? fp::eq(z[lane], r[lane]) : 1)));
 }
 
+// Three table rounds from octs of entries, one entry a lane (lane j of the
+// oct: bits x, y, z of j).  At a point of {0, 1, inf}^3 the term is a product
+// of A's and F's values there, a difference along every inf axis (either sign:
+// both factors share it), plus C at the corners.  Lane j takes four of the 27:
+//   slot 0: corner j;
+//   slot 1: x inf (lanes x = 0); x, z inf (x = 1, z = 0); all inf (lane 5);
+//   slot 2: y inf (lanes y = 0); x, y inf (y = 1, x = 0);
+//   slot 3: z inf (lanes z = 0); y, z inf (z = 1, y = 0).
+// Every lane runs the same instructions (operands chosen by its bits).  o: this
+// lane's factors of slots 1..3, below 2p.
+__device__ __forceinline__ void oct_factors(u32 lane, u64 v, u64 (&o)[3]) {
+    const bool x = lane & 1, y = lane & 2, z = lane & 4;
+    const u64 dx = v + (P - from1(v)), dy = v + (P - from2(v)), dz = v + (P - from4(v));
+    const u64 dxz = fp::fold64_mad(dx + (2 * P - from4(dx))), dxy = fp::fold64_mad(dx + (2 * P - from2(dx)));
+    const u64 dyz = fp::fold64_mad(dy + (2 * P - from4(dy)));
+    const u64 dxyz = fp::fold64_mad(dxz + (2 * P - from2(dxz)));  // (dxz below 2^61 + 8)
+    o[0] = !x ? dx : (!z ? dxz : dxyz);
+    o[1] = !y ? dy : dxy;
+    o[2] = !z ? dz : dyz;
+}
+// One slot's factor alone (SLOT 1..3), as oct_factors forms it.
+template <int SLOT>
+__device__ __forceinline__ u64 oct_factor(u32 lane, u64 v) {
+    const bool x = lane & 1, y = lane & 2, z = lane & 4;
+    if (SLOT == 1) {
+        const u64 dx = v + (P - from1(v)), dxz = fp::fold64_mad(dx + (2 * P - from4(dx)));
+        const u64 dxyz = fp::fold64_mad(dxz + (2 * P - from2(dxz)));
+        return !x ? dx : (!z ? dxz : dxyz);
+    }
+    const u64 dy = v + (P - from2(v));
+    if (SLOT == 2) {
+        const u64 dx = v + (P - from1(v)), dxy = fp::fold64_mad(dx + (2 * P - from2(dx)));
+        return !y ? dy : dxy;
+    }
+    const u64 dz = v + (P - from4(v)), dyz = fp::fold64_mad(dy + (2 * P - from4(dy)));
+    return !z ? dz : dyz;
+}
+// Sums of the lane's four slots: products below 2^124, up to eight between
+// reductions.
+struct OctSums {
+    u128 acc[4] = {0, 0, 0, 0};
+    u64 s[4] = {0, 0, 0, 0};
+    u32 terms = 0;
+};
+__device__ __forceinline__ void oct_flush(OctSums &q) {
+    q.terms = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        q.s[k] = add(q.s[k], fp::red128(q.acc[k]));
+        q.acc[k] = 0;
+    }
+}
+__device__ __forceinline__ void oct_add(u32 lane, u64 A, u64 C, u64 F, OctSums &q) {
+    u64 a[3], f[3];
+    oct_factors(lane, A, a);
+    oct_factors(lane, F, f);
+    q.acc[0] += fp::wide(A, F) + C;
+#pragma unroll
+    for (int k = 0; k < 3; k++) q.acc[k + 1] += fp::wide(a[k], f[k]);
+    if (++q.terms == 8) oct_flush(q);
+}
+// The wave's sums into out[4 j + k]: lanes of equal j = lane mod 8 added.
+__device__ __forceinline__ void oct_wave(OctSums &q, u64 *out) {
+    const u32 lane = threadIdx.x & 63;
+    oct_flush(q);
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const u64 v = reduced(plus32(plus16(q.s[k] + from8(q.s[k]))));  // (eight values below p)
+        if (lane < 8) out[4 * lane + k] = v;
+    }
+}
+// A grid step's row.
+__device__ __forceinline__ void oct_row(OctSums &q, u64 *part, u64 *row) {
+    oct_wave(q, part + (threadIdx.x >> 6) * T_ROW);
+    __syncthreads();
+    if (threadIdx.x < T_ROW) {
+        u64 t = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVES; w++) t = add(t, part[w * T_ROW + threadIdx.x]);
+        row[threadIdx.x] = t;
+    }
+}
+// Message k of the three rounds from the octs' sums E (T_ROW words, LDS): lane
+// x + 3 y + 9 z holds the point (x, y, z), 2 for inf.  The rounds before k are
+// bound (a quadratic is q0 (1 - r) + q1 r + qinf (r^2 - r)), those after it
+// summed over 0 and 1; G(2) = 2 G(1) - G(0) + 2 G(inf).  One wave.
+__device__ __forceinline__ void t_message(const u64 *E, u32 k, const u64 *r, u64 *msg) {
+    const u32 lane = threadIdx.x & 63;
+    const u32 d[3] = {lane % 3, (lane / 3) % 3, lane / 9};
+    const u32 x = d[0], y = d[1], z = d[2];
+    u32 at;
+    if (x < 2 && y < 2 && z < 2)
+        at = 4 * (x + 2 * y + 4 * z);
+    else if (x == 2 && y < 2)
+        at = 4 * (z < 2 ? 2 * y + 4 * z : 1 + 2 * y) + 1;
+    else if (x == 2 && z == 2)
+        at = 4 * 5 + 1;
+    else if (y == 2 && z < 2)
+        at = 4 * (x < 2 ? x + 4 * z : 2 + 4 * z) + 2;
+    else
+        at = 4 * (y == 2 ? x + 4 : x + 2 * y) + 3;
+    u64 v = lane < 27 ? E[at] : 0;
+#pragma unroll
+    for (u32 i = 0; i < 3; i++) {
+        if (i < k) {  // (uniform)
+            const u64 ri = r[i];
+            v = mul(v, d[i] == 0 ? sub(1, ri) : (d[i] == 1 ? ri : sub(mul(ri, ri), ri)));
+        } else if (i > k && d[i] == 2) {
+            v = 0;
+        }
+    }
+    const u32 dk = k == 0 ? x : (k == 1 ? y : z);
+    const u64 q0 = wave_total(dk == 0 ? v : 0), q1 = wave_total(dk == 1 ? v : 0), q2 = wave_total(dk == 2 ? v : 0);
+    if (lane < 3) msg[lane] = lane == 0 ? q0 : (lane == 1 ? q1 : sub(add(add(q1, q1), add(q2, q2)), q0));
+}
+
 // One item of ST_FINISH: a round's rows into its message, lanes t < 3 (and
 // 3..5 for a second message) writing one value each; operands that do not
 // depend on the rows are loaded before the row sums.
@@ -292,22 +386,29 @@ __device__ __forceinline__ void step_finish(const FinishArgs &a, const Ctx &c) {
             }
             break;
         }
-        case FIN_T: {
-            u64 t[3];
-            rows_total<3>(it.rows, 0, it.nrows, t);
-            if (tid < 3) it.msg[tid] = pick(t, tid);
-            break;
-        }
-        case FIN_T2: {
-            const u64 r = a.chals[it.draw];
-            u64 t[12];
-            rows_total<12>(it.rows, 0, it.nrows, t);
-            if (tid < 3) {
-                it.msg[tid] = pick(t, tid);
-            } else if (tid < 6) {  // round k+1 at t = tid - 3: Q0 + r (Q1 + r Q2)
-                const u32 q = tid - 3;
-                it.msg[tid] = add(pick(t, 3 + q), mul(r, add(pick(t, 6 + q), mul(r, pick(t, 9 + q)))));
+        case FIN_T: {  // the octs' sums, then a wave a message
+            u64 *s_col = c.lds;
+            const u32 x = tid & (T_ROW - 1);
+            constexpr u32 G = SBLOCK / T_ROW, U = 16;
+            u64 t = 0;
+            for (u32 q0 = tid / T_ROW; q0 < it.nrows; q0 += G * U) {
+                u64 v[U];
+#pragma unroll
+                for (u32 i = 0; i < U; i++) {
+                    const u32 q = q0 + i * G;
+                    v[i] = q < it.nrows ? it.rows[(u64)q * T_ROW + x] : 0;
+                }
+#pragma unroll
+                for (u32 i = 0; i < U; i++) t = add(t, v[i]);
             }
+            s_col[tid] = t;
+            __syncthreads();
+            for (u32 h = SBLOCK / 2; h >= T_ROW; h >>= 1) {
+                if (tid < h) s_col[tid] = add(s_col[tid], s_col[tid + h]);
+                __syncthreads();
+            }
+            const u32 k = tid >> 6;
+            if (k < it.nvals) t_message(s_col, k, a.chals + it.draw, it.msg + 3 * k);
             break;
         }
         case FIN_LINE: {
@@ -830,116 +931,6 @@ __device__ __forceinline__ void step_wagg(const WaggArgs &a, const ProofPtrs &pp
     }
 }
 
-// Message sums of one pair of a table round.  HC: whether the layer has a
-// C table, when known at compile time (without one C is zero and skipped).
-template <int HC = 1>
-__device__ __forceinline__ void table_terms(u64 A0, u64 A1, u64 C0, u64 C1, u64 F0, u64 F1,
-                                            u64 (&acc)[3]) {
-    const u64 A2 = sub(add(A1, A1), A0), F2 = sub(add(F1, F1), F0);
-    if (HC) {
-        const u64 C2 = sub(add(C1, C1), C0);
-        acc[0] = add(acc[0], add(mul(A0, F0), C0));
-        acc[1] = add(acc[1], add(mul(A1, F1), C1));
-        acc[2] = add(acc[2], add(mul(A2, F2), C2));
-    } else {
-        acc[0] = add(acc[0], mul(A0, F0));
-        acc[1] = add(acc[1], mul(A1, F1));
-        acc[2] = add(acc[2], mul(A2, F2));
-    }
-}
-
-// One quad of level-k tables, held one entry per lane by four adjacent
-// lanes.  Lane t < 3 adds, for its t, round k's value over the quad's two
-// pairs and round k+1's three coefficients (lane 3's sums are dropped): the quad
-// folds to the pair (X0 + r dX0, X2 + r dX2), dX0 = X1 - X0, dX2 = X3 - X2,
-// whose value at t is a_t + r b_t with a = (X0, X2, 2 X2 - X0),
-// b = (dX0, dX2, 2 dX2 - dX0):
-//   Q0(t) += aA aF + aC, Q1(t) += aA bF + bA aF + bC, Q2(t) += bA bF.
-// Every lane runs the same instructions (operands chosen by t), so a wave
-// does six products per quad.  acc: G(t), Q0(t), Q1(t), Q2(t) of this lane.
-struct QuadAcc {
-    u64 g = 0, q0 = 0, q1 = 0, q2 = 0;
-};
-
-
-// x at t in {0, 1, 2} on the line through (0, x0), (1, x1), not reduced:
-// with x0, x1 < K p the value is below 3 K p (K <= 2: below 2^64).  It only
-// feeds 128-bit product sums, which red128 reduces whatever their size.
-template <int K>
-__device__ __forceinline__ u64 at_t_lz(u64 x0, u64 x1, u32 t) {
-    static_assert(K == 1 || K == 2, "3 K p < 2^64");
-    const u64 x2 = 2 * x1 + ((u64)K * fp::P - x0);
-    return t == 0 ? x0 : (t == 1 ? x1 : x2);
-}
-
-// HC: whether the layer has a C table (1, 0), or -1 to take hasC.  The line
-// values and differences stay unreduced (below 6 p); each of g, q0, q1, q2
-// is one 128-bit sum of at most two products and two such values, reduced
-// once (below 2^128: 2 (3p)(6p) + 9p < 2^127.3).
-template <int HC>
-__device__ __forceinline__ void table_quad(u32 j, u64 A, u64 C, u64 F, bool hasC, QuadAcc &acc) {
-    const bool hc = HC >= 0 ? HC != 0 : hasC;
-    const u64 A0 = quad_get<0>(A), A1 = quad_get<1>(A), A2 = quad_get<2>(A), A3 = quad_get<3>(A);
-    const u64 F0 = quad_get<0>(F), F1 = quad_get<1>(F), F2 = quad_get<2>(F), F3 = quad_get<3>(F);
-    u64 C0 = 0, C1 = 0, C2 = 0, C3 = 0;
-    if (hc) {
-        C0 = quad_get<0>(C);
-        C1 = quad_get<1>(C);
-        C2 = quad_get<2>(C);
-        C3 = quad_get<3>(C);
-    }
-    const u32 t = j < 3 ? j : 2;
-    // round k at t: pairs (X0, X1) and (X2, X3)
-    u128 gs = fp::wide(at_t_lz<1>(A0, A1, t), at_t_lz<1>(F0, F1, t)) +
-              fp::wide(at_t_lz<1>(A2, A3, t), at_t_lz<1>(F2, F3, t));
-    if (HC != 0) gs += (u128)at_t_lz<1>(C0, C1, t) + at_t_lz<1>(C2, C3, t);  // (zero without a C table)
-    // round k+1's coefficients at t
-    const u64 aA = at_t_lz<1>(A0, A2, t), bA = at_t_lz<2>(diff_lz(A1, A0), diff_lz(A3, A2), t);
-    const u64 aF = at_t_lz<1>(F0, F2, t), bF = at_t_lz<2>(diff_lz(F1, F0), diff_lz(F3, F2), t);
-    u128 s0 = fp::wide(aA, aF), s1 = fp::wide(aA, bF) + fp::wide(bA, aF);
-    if (HC != 0) {
-        s0 += at_t_lz<1>(C0, C2, t);
-        s1 += at_t_lz<2>(diff_lz(C1, C0), diff_lz(C3, C2), t);
-    }
-    const u64 g = red128_lz(gs), q0 = red128_lz(s0), q1 = red128_lz(s1), q2 = red128_lz(fp::wide(bA, bF));
-    // sums kept below p + 4 (lane 3's are never stored, see table_quad_store)
-    acc.g = fp::fold64(acc.g + g);
-    acc.q0 = fp::fold64(acc.q0 + q0);
-    acc.q1 = fp::fold64(acc.q1 + q1);
-    acc.q2 = fp::fold64(acc.q2 + q2);
-}
-
-// Rows of a two-round table step: G(0..2), Q0(0..2), Q1(0..2), Q2(0..2);
-// lane t contributes slot t of each.
-// The workgroup's row: G(t), Q0(t), Q1(t), Q2(t) at t, 3 + t, 6 + t, 9 + t.
-// Lane j of every quad holds t = j, so lanes of equal j are summed: row
-// shifts by 4 and 8 leave a row's sums in its lanes 12 + j, shuffles add the
-// four rows of the wave, LDS the waves.
-__device__ __forceinline__ void table_quad_store(u32 j, const QuadAcc &q, u64 *row) {
-    u64 (*sm)[12] = reinterpret_cast<u64 (*)[12]>(sum_lds());
-    u64 v[4] = {fp::canon(q.g), fp::canon(q.q0), fp::canon(q.q1), fp::canon(q.q2)};  // (below p + 4)
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        v[k] = add(v[k], dpp64<0x114, 0xf>(v[k]));  // row_shr:4
-        v[k] = add(v[k], dpp64<0x118, 0xf>(v[k]));  // row_shr:8
-        v[k] = add(v[k], xor64(v[k], 16));
-        v[k] = add(v[k], xor64(v[k], 32));
-    }
-    const u32 lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane >= 12 && lane < 15) {
-#pragma unroll
-        for (int k = 0; k < 4; k++) sm[wid][3 * k + (lane - 12)] = v[k];
-    }
-    (void)j;
-    __syncthreads();
-    if (threadIdx.x < 12) {
-        u64 t = sm[0][threadIdx.x];
-#pragma unroll
-        for (int w = 1; w < NWAVES; w++) t = add(t, sm[w][threadIdx.x]);
-        row[threadIdx.x] = t;
-    }
-}
-
 // Level-0 entries from a wire's sums (phase 2: ADD gates w (v1 + G(t)),
 // MUL gates w v1 G(t)).
 __device__ __forceinline__ void level0(u32 ph, u64 v1, u64 sA, u64 sC, u64 &A, u64 &C) {
@@ -952,42 +943,38 @@ __device__ __forceinline__ void level0(u32 ph, u64 v1, u64 sA, u64 sC, u64 &A, u
     }
 }
 
-// Level-0 tables of an omega phase and round 0; a thread takes a pair of
-// wires.  wire(x, sA, sC) gives the sums of wire x's gates.  GK, PH: the
-// gate mix and phase when known at compile time (-1, 0: ph and hasC).
+// Level-0 tables of an omega phase and the sums of its first three rounds
+// (sum); a lane takes a wire, so eight adjacent lanes hold an oct (nw and the
+// stride are multiples of 8).  wire(x, sA, sC) gives the sums of wire x's
+// gates.  GK, PH: the gate mix and phase when known at compile time (-1, 0: ph
+// and hasC).
 template <int GK, int PH, typename Wire>
-__device__ __forceinline__ void level0_round(u32 ph_rt, u32 hasC_rt, u64 npairs, const u64 *F, u64 *At, u64 *Ct,
+__device__ __forceinline__ void level0_round(u32 ph_rt, u32 hasC_rt, u32 sum, u64 nw, const u64 *F, u64 *At, u64 *Ct,
                                              const ProofPtrs &pp, const Ctx &c, u64 *row, Wire wire) {
     const u32 ph = PH > 0 ? (u32)PH : ph_rt;
     const bool hasC = GK >= 0 ? GK != 1 : hasC_rt != 0;
     const u64 v1 = ph == 2 ? pp.state[1] : 0;
-    u64 acc[3] = {0, 0, 0};
-    for (u64 m = c.gtid; m < npairs; m += c.gstride) {
-        u64 A[2], C[2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            u64 sA, sC;
-            wire(2 * m + h, sA, sC);
-            if (GK == 1 && ph == 2) {  // MUL gates only: sA is zero
-                A[h] = mul(v1, sC);
-                C[h] = 0;
-            } else {
-                level0(ph, v1, sA, sC, A[h], C[h]);
-            }
-            if (!hasC) C[h] = 0;
+    const u32 lane = threadIdx.x & 63;
+    OctSums q;
+    for (u64 x = c.gtid; x < nw; x += c.gstride) {
+        const u64 f = F[x];
+        u64 sA, sC, A, C;
+        wire(x, sA, sC);
+        if (GK == 1 && ph == 2) {  // MUL gates only: sA is zero
+            A = mul(v1, sC);
+            C = 0;
+        } else {
+            level0(ph, v1, sA, sC, A, C);
         }
-        st2(At, 2 * m, A[0], A[1]);
-        if (hasC) st2(Ct, 2 * m, C[0], C[1]);
-        const u64x2 f = ld2(F, 2 * m);
-        if (GK == 1)
-            table_terms<0>(A[0], A[1], C[0], C[1], f.x, f.y, acc);
-        else
-            table_terms(A[0], A[1], C[0], C[1], f.x, f.y, acc);
+        if (!hasC) C = 0;
+        At[x] = A;
+        if (hasC) Ct[x] = C;
+        if (sum) oct_add(lane, A, C, f, q);  // (uniform)
     }
-    block_store<3>(acc, row);
+    if (sum) oct_row(q, c.lds, row);
 }
 
-// Round 0 from the chunk sums: wire x's sums add its chunks
+// Level 0 from the chunk sums: wire x's sums add its chunks
 // [xch[x], xch[x+1]).  A lane adds the chunks of its own wire when they are
 // few; a wire with more (the pattern entries of pattern matching feed up to
 // 2^18 gates) is summed by the whole wave, lanes striding over its chunks,
@@ -997,192 +984,137 @@ constexpr u32 WT0_LANE_CHUNKS = 64;
 __device__ __forceinline__ void step_wt0(const Wt0Args &a, const ProofPtrs &pp, const Ctx &c, u64 *row) {
     const u64 v1 = a.ph == 2 ? pp.state[1] : 0;
     const u32 lane = threadIdx.x & 63;
-    u64 acc[3] = {0, 0, 0};
-    for (u64 base = c.gtid - lane; base < a.npairs; base += c.gstride) {  // wave-uniform
-        const u64 m = base + lane;
-        const bool on = m < a.npairs;
-        u64 A[2], C[2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            u32 c0 = 0, c1 = 0;
-            if (on) {
-                c0 = a.xch[2 * m + h];
-                c1 = a.xch[2 * m + h + 1];
-            }
-            const bool many = c1 - c0 > WT0_LANE_CHUNKS;
-            u64 sA = 0, sC = 0;
-            if (!many) {
-                for (u32 ch = c0; ch < c1; ch++) {
-                    sA = add(sA, a.partA[ch]);
-                    sC = add(sC, a.partC[ch]);
-                }
-            }
-            for (u64 hm = __ballot(many); hm; hm &= hm - 1) {
-                const u32 l = (u32)__ffsll((long long)hm) - 1;  // uniform
-                const u32 b0 = (u32)__builtin_amdgcn_readlane((int)c0, l);
-                const u32 b1 = (u32)__builtin_amdgcn_readlane((int)c1, l);
-                u64 wA = 0, wC = 0;
-#pragma unroll 4
-                for (u32 ch = b0 + lane; ch < b1; ch += 64) {
-                    wA = add(wA, a.partA[ch]);
-                    wC = add(wC, a.partC[ch]);
-                }
-                wA = lane_value(wave_sum63(wA), 63);
-                wC = lane_value(wave_sum63(wC), 63);
-                if (lane == l) {
-                    sA = wA;
-                    sC = wC;
-                }
-            }
-            level0(a.ph, v1, sA, sC, A[h], C[h]);
-            if (!a.hasC) C[h] = 0;
-        }
+    OctSums q;
+    for (u64 base = c.gtid - lane; base < a.nw; base += c.gstride) {  // wave-uniform
+        const u64 x = base + lane;
+        const bool on = x < a.nw;
+        u32 c0 = 0, c1 = 0;
         if (on) {
-            st2(a.A, 2 * m, A[0], A[1]);
-            if (a.hasC) st2(a.C, 2 * m, C[0], C[1]);
-            const u64x2 f = ld2(a.F, 2 * m);
-            table_terms(A[0], A[1], C[0], C[1], f.x, f.y, acc);
+            c0 = a.xch[x];
+            c1 = a.xch[x + 1];
         }
+        const bool many = c1 - c0 > WT0_LANE_CHUNKS;
+        u64 sA = 0, sC = 0;
+        if (!many) {
+            for (u32 ch = c0; ch < c1; ch++) {
+                sA = add(sA, a.partA[ch]);
+                sC = add(sC, a.partC[ch]);
+            }
+        }
+        for (u64 hm = __ballot(many); hm; hm &= hm - 1) {
+            const u32 l = (u32)__ffsll((long long)hm) - 1;  // uniform
+            const u32 b0 = (u32)__builtin_amdgcn_readlane((int)c0, l);
+            const u32 b1 = (u32)__builtin_amdgcn_readlane((int)c1, l);
+            u64 wA = 0, wC = 0;
+#pragma unroll 4
+            for (u32 ch = b0 + lane; ch < b1; ch += 64) {
+                wA = add(wA, a.partA[ch]);
+                wC = add(wC, a.partC[ch]);
+            }
+            wA = lane_value(wave_sum63(wA), 63);
+            wC = lane_value(wave_sum63(wC), 63);
+            if (lane == l) {
+                sA = wA;
+                sC = wC;
+            }
+        }
+        u64 A, C, f = 0;
+        level0(a.ph, v1, sA, sC, A, C);
+        if (!a.hasC) C = 0;
+        if (on) {
+            a.A[x] = A;
+            if (a.hasC) a.C[x] = C;
+            f = a.F[x];
+        } else {
+            A = C = 0;
+        }
+        if (a.sum) oct_add(lane, A, C, f, q);  // (uniform)
     }
-    block_store<3>(acc, row);
+    if (a.sum) oct_row(q, c.lds, row);
 }
 
 // GK, PH: the gate mix and phase, compile-time (one kernel each) or -1, 0.
 template <int GK, int PH>
 __device__ __forceinline__ void step_wa0(const Wa0Args &a, const ProofPtrs &pp, const Ctx &c, u64 *row) {
-    level0_round<GK, PH>(a.ph, a.hasC, a.npairs, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
+    level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
         wire_sums<GK, PH>(a, a.rowptr[x], a.rowptr[x + 1], sA, sC);
     });
 }
 
+// The eight entries of one entry of the level three below, and their fold by
+// three challenges (chi: the eight weights).
+struct Eight {
+    u64x2 p[4];
+};
+__device__ __forceinline__ Eight ld8(const u64 *X, u64 g) {
+    Eight e;
+#pragma unroll
+    for (u32 k = 0; k < 4; k++) e.p[k] = ld2(X, 8 * g + 2 * k);
+    return e;
+}
+__device__ __forceinline__ u64 fold3(const Eight &e, const u64 (&chi)[8]) {
+    u128 t = 0;
+#pragma unroll
+    for (u32 k = 0; k < 4; k++) t += fp::wide(chi[2 * k], e.p[k].x) + fp::wide(chi[2 * k + 1], e.p[k].y);
+    return fp::red128(t);
+}
+// The weights of a fold by the challenges in lanes off .. off + 2 of rl: one a
+// lane, then scalars.
+__device__ __forceinline__ void chi8(u64 rl, u64 (&chi)[8]) {
+    const u32 lane = threadIdx.x;
+    const u64 x = mul(mul(fp::eqbit(lane & 1, lane_value(rl, 0)), fp::eqbit((lane >> 1) & 1, lane_value(rl, 1))),
+                      fp::eqbit((lane >> 2) & 1, lane_value(rl, 2)));
+#pragma unroll
+    for (u32 e = 0; e < 8; e++) chi[e] = lane_value(x, e);
+}
+
 // HC: whether the layer has a C table, compile-time (one kernel each) or -1.
-template <int HC>
-__device__ __forceinline__ void step_wt(const WtArgs &a, const Ctx &c, u64 *row) {
+// The first entries' loads are issued before draw() waits for the challenge
+// state.
+template <int HC, typename Draw>
+__device__ __forceinline__ void step_wt(const WtArgs &a, const Ctx &c, u64 *row, Draw draw) {
     const bool hasC = HC >= 0 ? HC != 0 : a.hasC != 0;
-    const u64 r0 = c.r, r1 = c.r2, r01 = mul(r0, r1);
-    QuadAcc acc;
-    const u32 pend = a.pend;
-    auto foldp = [&](const u64 *X, u64 g) {  // level-(k+pend) entry g from level k
-        if (pend == 1) {
-            const u64x2 p = ld2(X, 2 * g);
-            return fold1(p.x, p.y, r0);
+    const u32 lane = threadIdx.x & 63;
+    u64 g = c.gtid;
+    Eight A = {}, F = {}, C = {};
+    auto load = [&](u64 e) {
+        if (e < a.nu) {
+            A = ld8(a.A, e);
+            F = ld8(a.F, e);
+            if (hasC) C = ld8(a.C, e);
         }
-        const u64x2 p = ld2(X, 4 * g), q = ld2(X, 4 * g + 2);
-        return fold2(p.x, p.y, q.x, q.y, r0, r1, r01);
     };
-    // lane g = entry 4u + j of level k+pend (the stride is a multiple of 4)
-    for (u64 g = c.gtid; (g >> 2) < a.nu; g += c.gstride) {
-        const u32 j = (u32)(g & 3);
-        const u64 A = foldp(a.A, g), F = foldp(a.F, g);
-        const u64 C = hasC ? foldp(a.C, g) : 0;
-        a.An[g] = A;
-        a.Fn[g] = F;
-        if (hasC) a.Cn[g] = C;
-        table_quad<HC>(j, A, C, F, hasC, acc);
+    load(g);
+    draw();
+    u64 chi[8];
+    chi8(c.rl, chi);
+    OctSums q;
+    for (; g < a.nu; g += c.gstride) {  // (whole octs)
+        const u64 vA = fold3(A, chi), vF = fold3(F, chi), vC = hasC ? fold3(C, chi) : 0;
+        a.An[g] = vA;
+        a.Fn[g] = vF;
+        if (hasC) a.Cn[g] = vC;
+        oct_add(lane, vA, vC, vF, q);
+        load(g + c.gstride);  // (48 registers: not held across oct_add)
     }
-    table_quad_store((u32)(c.gtid & 3), acc, row);
+    oct_row(q, c.lds, row);
 }
 
 // ------------------------------------------------------------------ tails
 //
-// A tail runs the last rounds of a phase in one workgroup, over tables in
-// LDS laid out as binary trees: with n = 2^L entries in level 0, level k
-// (n_k = n >> k entries) sits at [2n - 2 n_k, 2n - n_k), so pair m of
-// level k is the tail's pair q = n - n_k + m, it holds entries 2q, 2q + 1
-// and it folds into entry n + q.  Every round first sums its message over
-// the level's pairs into partial sums in LDS; a barrier completes them, and
-// only after it is the round's challenge used (folds, the p-phase's beta
-// prefix); a second barrier publishes the next level.  While a level has at
-// least 128 entries every thread takes one pair of every table, adds its
-// three terms into 64-pair chunk sums and then folds the pair it holds;
-// below that wave t sums value t of the message and then folds table t.
-// The partial sums of all rounds are added into the messages at the end.
-
-constexpr int TAIL_CHUNKS = TAIL_LIM / 64;          // 64-pair chunks of a tail
-constexpr int TAIL_SLOTS = TAIL_CHUNKS + TAIL_LOG;  // chunk sums, then the small rounds' sums
+// An omega tail runs the last rounds of a phase in one workgroup, three rounds
+// at a time (see FIN_T) over tables in LDS: the sums of a level's octs are
+// complete at a barrier, the level is folded by the three challenges, one
+// thread a table and entry, and a second barrier publishes the next level, an
+// eighth as long.  A wave issues an instruction every four to six cycles and
+// waits for the instruction cache on code it has not run yet, so the tail's
+// length is what one wave runs between barriers, and every level runs the same
+// code: a wave sums one of the octs' four slots, the last wave draws the
+// challenges and forms the fold's weights.  ST_FINISH forms the messages from
+// the sums.
 static_assert((1 << TAIL_LOG) == TAIL_LIM, "TAIL_LOG");
-static_assert(TAIL_LIM / 2 <= SBLOCK, "a wide round gives every pair a thread");
-static_assert(NWAVES >= 3, "one wave per message value");
-
-// Partial message sums of a tail, per value t: chunk c's sum in slot c
-// (rounds of at least 64 pairs), round k's sum in slot TAIL_CHUNKS + k
-// (rounds of fewer).
-__device__ __forceinline__ u64 (*tail_parts())[TAIL_SLOTS] {
-    __shared__ u64 p[3][TAIL_SLOTS];
-    return p;
-}
-
-
-// Sum over the wave of field elements, left in lane 63: as wave_sum63, but
-// the first three and the last three steps add without reducing (eight
-// values below p stay below 2^64), with one reduction after each three.
-__device__ __forceinline__ u64 wave_sum63_lazy(u64 v) {
-    v += dpp64<0x111, 0xf>(v);  // row_shr:1
-    v += dpp64<0x112, 0xf>(v);  // row_shr:2
-    v += dpp64<0x114, 0xf>(v);  // row_shr:4
-    v = fp::canon(fp::fold64(v));
-    v += dpp64<0x118, 0xf>(v);  // row_shr:8
-    v += dpp64<0x142, 0xa>(v);  // row_bcast:15 into rows 1, 3
-    v += dpp64<0x143, 0xc>(v);  // row_bcast:31 into rows 2, 3
-    return fp::canon(fp::fold64(v));
-}
-
-// A wave's three message terms of one 64-pair chunk c, summed into the
-// chunk's partial sums.
-__device__ __forceinline__ void chunk_sums(u64 (&t)[3], u32 c, u32 lane) {
-    u64 (*mp)[TAIL_SLOTS] = tail_parts();
-#pragma unroll
-    for (int i = 0; i < 3; i++) t[i] = wave_sum63_lazy(t[i]);
-    if (lane == 63) {
-#pragma unroll
-        for (int i = 0; i < 3; i++) mp[i][c] = t[i];
-    }
-}
-
-// Value t of round k's message sum from the partials.
-__device__ __forceinline__ u64 tail_sum(u32 n, u32 k, u32 t) {
-    const u64 (*mp)[TAIL_SLOTS] = tail_parts();
-    const u32 half = n >> (k + 1);
-    if (half < 64) return mp[t][TAIL_CHUNKS + k];
-    u64 s = 0;
-    for (u32 c = (n - 2 * half) >> 6; c < (n - half) >> 6; c++) s = add(s, mp[t][c]);
-    return s;
-}
-
-// X at t = T on the line through (0, x0), (1, x1).
-template <int T>
-__device__ __forceinline__ u64 line_at(u64 x0, u64 x1) {
-    return T == 0 ? x0 : (T == 1 ? x1 : sub(add(x1, x1), x0));
-}
-
-// The three terms of one pair of a tail round, canonical: A(t) F(t) (+ C(t))
-// at t = 0, 1, 2, the values at t = 2 unreduced (below 3p) in one 128-bit
-// sum reduced once.
-template <int HC>
-__device__ __forceinline__ void tail_pair_terms(u64 A0, u64 A1, u64 C0, u64 C1, u64 F0, u64 F1, u64 (&t)[3]) {
-    u128 t0 = fp::wide(A0, F0), t1 = fp::wide(A1, F1);
-    u128 t2 = fp::wide(2 * A1 + (fp::P - A0), 2 * F1 + (fp::P - F0));
-    if (HC != 0) {
-        t0 += C0;
-        t1 += C1;
-        t2 += 2 * C1 + (fp::P - C0);
-    }
-    t[0] = fp::red128(t0);
-    t[1] = fp::red128(t1);
-    t[2] = fp::red128(t2);
-}
-
-// Entry e of the level a tail starts from, folded from memory by the
-// pending challenge(s) of the prologue.
-__device__ __forceinline__ u64 tail_entry(const u64 *X, u32 e, u32 pend, const Ctx &c) {
-    if (pend == 0) return X[e];
-    if (pend == 1) {
-        const u64x2 p = ld2(X, 2 * e);
-        return fold1(p.x, p.y, c.r);
-    }
-    const u64x2 p = ld2(X, 4 * e), q = ld2(X, 4 * e + 2);
-    return fold2(p.x, p.y, q.x, q.y, c.r, c.r2, mul(c.r, c.r2));
-}
+static_assert(NWAVES == 8, "two waves a slot");
+static_assert(3 * TAIL_LIM / 8 <= SBLOCK, "one thread a table and folded entry");
 
 // RNG state of the tail's first round: the prologue drew the pending
 // challenges and left the state after them; a tail without them reads it.
@@ -1194,79 +1126,105 @@ __device__ __forceinline__ u64 tail_state(const ProofPtrs &pp, u32 c0, u32 drew,
     return uniform(s_st);
 }
 
-// The rounds of an omega tail over tables A, C, F in LDS (level 0 of each,
-// n entries, at the start of its area of TAIL_TAB entries): messages to
-// msgp, challenges c0, c0 + 1, ... recorded with the RNG states after them
-// (and into rec[k], in LDS, when rec is not NULL); F's last entry is v1
-// (last = 1) or v2.  Round k's message is, at t = 0, 1, 2, the sum over its
-// pairs of A_t F_t + C_t with X_t the line through the pair.  Returns the
-// RNG state after the last round.
+// The rounds of an omega tail over tables A, C, F in LDS (areas of TAIL_TAB
+// entries one after another from tab, then TAIL_EXTRA words).  Level 0, 2^L
+// entries, is at the start of each area, complete at a barrier.  The steps'
+// sums go to cols, challenges c0, c0 + 1, ... are recorded (and into rec, in
+// LDS, when rec is not NULL) with the RNG state after them; F's last entry is v1
+// (last = 1) or v2, to *vout and left in tab[2 TAIL_TAB + TAIL_TAB - 1].  Returns
+// the RNG state after the last round.
 // HC: whether the phase has a C table, compile-time (1, 0) or -1 to take hc_rt.
 template <int HC = -1>
-__device__ __forceinline__ u64 wtail_rounds(u64 *A, u64 *Ct, u64 *F, u32 n, bool hc_rt, u64 st, u64 *msgp, u32 c0,
-                                            u32 last, u64 *vout, const ProofPtrs &pp, u64 *rec = nullptr) {
+__device__ __forceinline__ u64 wtail_rounds(u64 *tab, u32 L, bool hc_rt, u64 st, u64 *cols, u32 c0, u32 last, u64 *vout,
+                                            const ProofPtrs &pp, u64 *rec = nullptr) {
     const bool hc = HC >= 0 ? HC != 0 : hc_rt;
+    u64 *A = tab, *Ct = tab + TAIL_TAB, *F = tab + 2 * TAIL_TAB;
+    u64 *s_w = tab + 3 * TAIL_TAB, *part = s_w + 8, *s_r = part + 2 * T_ROW, *s_st = s_r + 15;
     const u32 tid = threadIdx.x, lane = tid & 63;
     const u32 w = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));  // wave-uniform
-    const u32 L = 31 - (u32)__builtin_clz(n);
-    u64 (*mp)[TAIL_SLOTS] = tail_parts();
-    for (u32 k = 0, nk = n; nk > 1; nk >>= 1, k++) {
-        const u32 half = nk >> 1, qb = n - nk;
-        const u64 r = fp::sm_field(st);  // challenge k: used after message k's sums
-        if (half >= 64) {  // thread tid takes pair qb + tid (whole waves)
-            const u32 q = qb + tid;
-            u64x2 pa = {0, 0}, pc = {0, 0}, pf = {0, 0};
-            if (tid < half) {
-                pa = ld2(A, 2 * q);
-                pf = ld2(F, 2 * q);
-                if (hc) pc = ld2(Ct, 2 * q);
-                u64 t[3];
-                tail_pair_terms<HC == 0 ? 0 : 1>(pa.x, pa.y, pc.x, pc.y, pf.x, pf.y, t);
-                chunk_sums(t, q >> 6, lane);
-            }
-            __syncthreads();  // message k's sums are complete
-            if (tid < half) {
-                A[n + q] = fold1(pa.x, pa.y, r);
-                F[n + q] = fold1(pf.x, pf.y, r);
-                if (hc) Ct[n + q] = fold1(pc.x, pc.y, r);
-            }
-        } else {  // wave t < 3 sums value t over the pairs, lane m < half taking pair qb + m
-            const u32 q = qb + lane;
-            const bool on = lane < half;
-            u64x2 own = {0, 0};
-            if (w < 3) {
-                u64x2 pa = {0, 0}, pc = {0, 0}, pf = {0, 0};
-                if (on) {
-                    pa = ld2(A, 2 * q);
-                    pf = ld2(F, 2 * q);
-                    if (hc) pc = ld2(Ct, 2 * q);
+    const u32 slot = w & 3, half = w >> 2;
+    u32 n = 1u << L, base = 0;
+    u64 rl = 0;  // last wave, lane k: challenge k
+    for (u32 k0 = 0;; k0 += 3) {
+        const u32 nr = L - k0 < 3 ? L - k0 : 3;
+        const bool end = k0 + 3 >= L;
+        // this wave's slot of entries 64 q + lane, q = half, half + 2, ... (at
+        // most eight products below 2^124)
+        if (64 * half < n) {
+            u128 acc = 0;
+            auto sums = [&](auto term) {  // term(a, f, e, on) of each entry
+                for (u32 q = half; 64 * q < n; q += 2) {
+                    const u32 e = 64 * q + lane;
+                    const bool on = e < n;
+                    acc += term(on ? A[base + e] : 0, on ? F[base + e] : 0, e, on);
                 }
-                // value w's term; the values at t = 2 unreduced (below 3p), reduced once
-                const u64 xa = w == 0 ? pa.x : (w == 1 ? pa.y : 2 * pa.y + (fp::P - pa.x));
-                const u64 xf = w == 0 ? pf.x : (w == 1 ? pf.y : 2 * pf.y + (fp::P - pf.x));
-                u128 tw = fp::wide(xa, xf);
-                if (HC != 0) tw += w == 0 ? pc.x : (w == 1 ? pc.y : 2 * pc.y + (fp::P - pc.x));
-                const u64 term = fp::red128(tw);
-                own = w == 0 ? pa : (w == 1 ? pc : pf);
-                const u64 v = wave_sum63_lazy(term);
-                if (lane == 63) mp[w][TAIL_CHUNKS + k] = v;
+            };
+            switch (slot) {
+                case 0:
+                    sums([&](u64 a, u64 f, u32 e, bool on) {
+                        return fp::wide(a, f) + (on && hc ? Ct[base + e] : 0);
+                    });
+                    break;
+                case 1:
+                    sums([&](u64 a, u64 f, u32, bool) { return fp::wide(oct_factor<1>(lane, a), oct_factor<1>(lane, f)); });
+                    break;
+                case 2:
+                    sums([&](u64 a, u64 f, u32, bool) { return fp::wide(oct_factor<2>(lane, a), oct_factor<2>(lane, f)); });
+                    break;
+                default:
+                    sums([&](u64 a, u64 f, u32, bool) { return fp::wide(oct_factor<3>(lane, a), oct_factor<3>(lane, f)); });
+                    break;
             }
-            __syncthreads();  // message k's sums are complete
-            if (w < 3 && (w != 1 || hc) && on) (w == 0 ? A : (w == 1 ? Ct : F))[n + q] = fold1(own.x, own.y, r);
+            const u64 p = fp::red128(acc), v = reduced(plus32(plus16(p + from8(p))));
+            if (lane < 8) part[half * T_ROW + 4 * lane + slot] = v;
         }
-        if (tid == 0) {
-            pp.chals[c0 + k] = r;
-            pp.rngst[c0 + k + 1] = st;
-            if (rec) rec[k] = r;
+        if (w == NWAVES - 1) {  // the challenges (used after the sums are complete) and their fold's weights
+            rl = draw_lanes(st, nr, k0, rl);
+            u64 f[3];
+#pragma unroll
+            for (u32 k = 0; k < 3; k++)  // (entries past the level weigh 0)
+                f[k] = fp::eqbit((lane >> k) & 1, k < nr ? lane_value(rl, k0 + k) : 0);
+            const u64 x = mul(mul(f[0], f[1]), f[2]);
+            if (lane < 8) s_w[lane] = x;
+            if (end && lane < L) s_r[lane] = rl;
+            if (end && lane == 0) *s_st = st;
         }
-        __syncthreads();  // level k + 1 is complete
+        __syncthreads();  // the sums of these rounds are complete
+        if (tid >= SBLOCK - T_ROW) {  // (the last wave is idle in the fold)
+            const u32 x = tid - (SBLOCK - T_ROW);
+            cols[k0 / 3 * T_ROW + x] = n > 64 ? add(part[x], part[T_ROW + x]) : part[x];
+        }
+        const u32 lo = n > 8 ? 31 - (u32)__builtin_clz(n >> 3) : 0, no = 1u << lo;  // entries of the next level
+        const u32 t = tid >> lo, o = tid & (no - 1);
+        if (t < (end ? 1u : (hc ? 3u : 2u))) {  // F, A, C
+            u64 *X = t == 0 ? F : (t == 1 ? A : Ct);
+            u128 s = 0;
+            if (n >= 8) {
+                const u64 *src = X + base + 8 * o;
+#pragma unroll
+                for (u32 k = 0; k < 8; k += 2) {
+                    const u64x2 x = ld2(src, k), wk = ld2(s_w, k);
+                    s += fp::wide(wk.x, x.x) + fp::wide(wk.y, x.y);
+                }
+            } else {
+                for (u32 k = 0; k < n; k++) s += fp::wide(s_w[k], X[base + k]);
+            }
+            X[end ? TAIL_TAB - 1 : base + n + o] = fp::red128(s);
+        }
+        __syncthreads();  // the next level is complete, the weights and partial sums are read
+        if (end) break;
+        base += n;
+        n = no;
     }
-    if (tid < 3 * L) {
-        const u32 k = tid / 3, t = tid - 3 * k;
-        msgp[3 * k + t] = tail_sum(n, k, t);
+    if (tid < L) {
+        const u64 r = s_r[tid];
+        pp.chals[c0 + tid] = r;
+        if (rec) rec[tid] = r;
     }
+    st = uniform(*s_st);
     if (tid == 0) {
-        const u64 v = F[2 * n - 2];  // the root
+        const u64 v = F[TAIL_TAB - 1];
+        pp.rngst[c0 + L] = st;
         *vout = v;
         if (last == 1) pp.state[1] = v;
     }
@@ -1274,21 +1232,52 @@ __device__ __forceinline__ u64 wtail_rounds(u64 *A, u64 *Ct, u64 *F, u32 n, bool
 }
 
 // HC: whether the phase has a C table, compile-time (one kernel each) or -1.
+// After pend = 3 rounds this step finishes them itself: its first loads are
+// issued before the wait for the challenge state.
 template <int HC>
-__device__ __forceinline__ void step_wtail(const WtailArgs &a, const ProofPtrs &pp, const Ctx c, u32 drew, u64 st0) {
+__device__ __forceinline__ void step_wtail(const WtailArgs &a, const ProofPtrs &pp, const Ctx c, u64 st_raw) {
     u64 *tab = c.lds;
-    const u32 tid = threadIdx.x;
+    const u32 tid = threadIdx.x, lane = tid & 63;
     const bool hc = HC >= 0 ? HC != 0 : a.hasC != 0;
-    const u32 n = 1u << (a.sp - a.k0);  // entries of level k0, at most TAIL_LIM
-    for (u32 e = tid; e < n; e += SBLOCK) {
-        const bool on = e < a.live;  // (the grid steps wrote level k0 - pend below live << pend)
-        tab[e] = on ? tail_entry(a.A, e, a.pend, c) : 0;
-        if (hc) tab[TAIL_TAB + e] = on ? tail_entry(a.C, e, a.pend, c) : 0;
-        tab[2 * TAIL_TAB + e] = on ? tail_entry(a.F, e, a.pend, c) : 0;
+    const u32 L = a.sp - a.k0;  // 2^L entries of level k0, at most TAIL_LIM
+    u64 st;
+    if (a.pend) {
+        Eight A = {}, F = {}, C = {};
+        auto load = [&](u32 e) {
+            if (e < a.live) {  // (the grid steps wrote level k0 - 3 below 8 live)
+                A = ld8(a.A, e);
+                F = ld8(a.F, e);
+                if (hc) C = ld8(a.C, e);
+            }
+        };
+        load(tid);
+        st = uniform(st_raw);
+        const u64 rl = draw_lanes(st, 3);
+        u64 chi[8];
+        chi8(rl, chi);
+        if (tid < 3) pp.chals[a.c0 - 3 + lane] = rl;
+#pragma unroll
+        for (u32 i = 0; i < 2; i++) {
+            const u32 e = tid + i * SBLOCK;
+            if (i && (1u << L) > SBLOCK) load(e);
+            if (e < (1u << L)) {
+                const bool on = e < a.live;
+                tab[e] = on ? fold3(A, chi) : 0;
+                if (hc) tab[TAIL_TAB + e] = on ? fold3(C, chi) : 0;
+                tab[2 * TAIL_TAB + e] = on ? fold3(F, chi) : 0;
+            }
+        }
+    } else {
+        for (u32 e = tid; e < (1u << L); e += SBLOCK) {
+            const bool on = e < a.live;
+            tab[e] = on ? a.A[e] : 0;
+            if (hc) tab[TAIL_TAB + e] = on ? a.C[e] : 0;
+            tab[2 * TAIL_TAB + e] = on ? a.F[e] : 0;
+        }
+        st = tail_state(pp, a.c0, 0, 0);
     }
-    const u64 st = tail_state(pp, a.c0, drew, st0);
     __syncthreads();
-    wtail_rounds<HC>(tab, tab + TAIL_TAB, tab + 2 * TAIL_TAB, n, hc, st, a.msg, a.c0, a.last, a.vout, pp);
+    wtail_rounds<HC>(tab, L, hc, st, a.cols, a.c0, a.last, a.vout, pp);
 }
 
 // A whole omega phase of a small layer in one workgroup: the eq table of
@@ -1324,8 +1313,7 @@ __device__ __forceinline__ void step_wsmall(const WsmallArgs &a, const ProofPtrs
     }
     const u64 st = tail_state(pp, a.c0, 0, 0);
     __syncthreads();
-    wtail_rounds(tab, tab + TAIL_TAB, tab + 2 * TAIL_TAB, n, hc, st, a.msg, a.c0, a.last, a.vout, pp);
-    (void)c;
+    wtail_rounds(tab, a.sp, hc, st, a.cols, a.c0, a.last, a.vout, pp);
 }
 
 // p-phase rounds in one workgroup over v, the level's 2^L <= TAIL_LIM entries
@@ -1762,8 +1750,8 @@ __device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp, 
         __syncthreads();
         top_level0(Ld, 1, beta, 0, eqa, s / 2, eqb, 0, Z, X, Y, hc);
         __syncthreads();
-        st = wtail_rounds(X, Y, Z, N, hc, st, Ld.msg + 3 * s, Ld.co + s, 1, Ld.msg + 3 * n, pp, s_r + s);
-        const u64 v1 = Z[2 * N - 2];  // the root of F
+        st = wtail_rounds(tab, sp, hc, st, Ld.wcols[0], Ld.co + s, 1, Ld.msg + 3 * n, pp, s_r + s);
+        const u64 v1 = Z[TAIL_TAB - 1];  // F bound in every variable
         __syncthreads();  // phase 1's partial sums are read; its tree in Y is no longer needed
         // phase 2: the gates on in2, with v1
         eq_halves_lds(s_r, s, eqa, eqa + 32);
@@ -1771,8 +1759,7 @@ __device__ __forceinline__ void step_top(const TopArgs &a, const ProofPtrs &pp, 
         __syncthreads();
         top_level0(Ld, 2, beta, v1, eqa, s / 2, eqb, sp / 2, Z, X, Y, hc);
         __syncthreads();
-        st = wtail_rounds(X, Y, Z, N, hc, st, Ld.msg + 3 * (s + sp), Ld.co + s + sp, 2, Ld.msg + 3 * n + 1, pp,
-                          s_r + s + sp);
+        st = wtail_rounds(tab, sp, hc, st, Ld.wcols[1], Ld.co + s + sp, 2, Ld.msg + 3 * n + 1, pp, s_r + s + sp);
         __syncthreads();
         // the line (level 0 of Z is still V_{i+1}); its point tables in X
         if (sp >= 2) {
@@ -1824,25 +1811,23 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
     // for a barrier before the body's first loads.
     u64 st_after = 0;
     c.r = 0;
-    c.r2 = 0;
     c.rl = 0;
     const u64 st_raw = f.draw >= 0 ? pp.rngst[f.draw] : 0;
     auto draw = [&]() {
         if (f.draw < 0) return;
         u64 st = uniform(st_raw);
-        const u32 nd = f.kind == FIN_T2 ? 2 : ((fin_mask(KIND) & (1u << FIN_P)) && f.kind == FIN_P ? f.R : 1);
+        const u32 nd = f.kind == FIN_T ? 3 : ((fin_mask(KIND) & (1u << FIN_P)) && f.kind == FIN_P ? f.R : 1);
         c.rl = draw_lanes(st, nd);
         c.r = lane_value(c.rl, 0);
-        c.r2 = lane_value(c.rl, 1);
         if (recorder && threadIdx.x < nd) pp.chals[f.draw + threadIdx.x] = c.rl;
         if (recorder && threadIdx.x == 0) pp.rngst[f.draw + nd] = st;
         st_after = st;  // the state after the drawn challenge(s)
     };
-    // a p-phase tail finishes the rounds before it itself; a later p-phase
-    // step's body draws after issuing its loads
-    const bool own_fin = (KIND == ST_PTAIL || KIND == KALL) && kind == ST_PTAIL && f.kind == FIN_P;
+    // a tail finishes the rounds before it itself; a table step's body and a
+    // later p-phase step's draw after issuing their loads
+    const bool own_fin = tail && (f.kind == FIN_P || f.kind == FIN_T);
     const bool pfirst = (KIND == ST_P || KIND == KALL) && kind == ST_P && sd.u.p.pend == 0;
-    const bool late = own_fin || ((KIND == ST_P || KIND == KALL) && kind == ST_P && !pfirst && !fin_block);
+    const bool late = own_fin || (((kind == ST_P && !pfirst) || kind == ST_WT) && !fin_block);
     if (!late) draw();
     TailIn ti = {st_after, f.draw >= 0 ? 1u : 0u};
     // points assembled in LDS (challenges drawn by earlier launches are in
@@ -1877,6 +1862,7 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
 
     // --- body
     u64 *row = sd.rows ? sd.rows + (u64)c.lb * ROW_STRIDE : nullptr;
+    u64 *trow = sd.rows + (u64)c.lb * T_ROW;  // of table rounds
     switch (kind) {
         case ST_LOAD: step_load(sd.u.load, pp, c); break;
         case ST_EVAL: step_eval(sd.u.eval, c); break;
@@ -1907,10 +1893,10 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
         case ST_LT: step_lt(sd.u.lt, c, s_pt, s_pt + sd.u.lt.sp); break;
         case ST_LINE: step_line(sd.u.line, c, row); break;
         case ST_WAGG: step_wagg<KIND == ST_WAGG ? GK : -1, KIND == ST_WAGG ? PH : 0>(sd.u.wagg, pp, c); break;
-        case ST_WT0: step_wt0(sd.u.wt0, pp, c, row); break;
-        case ST_WA0: step_wa0<KIND == ST_WA0 ? GK : -1, KIND == ST_WA0 ? PH : 0>(sd.u.wa0, pp, c, row); break;
-        case ST_WT: step_wt<KIND == ST_WT ? GK : -1>(sd.u.wt, c, row); break;
-        case ST_WTAIL: step_wtail<KIND == ST_WTAIL ? GK : -1>(sd.u.wtail, pp, c, ti.drew, ti.st); break;
+        case ST_WT0: step_wt0(sd.u.wt0, pp, c, trow); break;
+        case ST_WA0: step_wa0<KIND == ST_WA0 ? GK : -1, KIND == ST_WA0 ? PH : 0>(sd.u.wa0, pp, c, trow); break;
+        case ST_WT: step_wt<KIND == ST_WT ? GK : -1>(sd.u.wt, c, trow, draw); break;
+        case ST_WTAIL: step_wtail<KIND == ST_WTAIL ? GK : -1>(sd.u.wtail, pp, c, st_raw); break;
         case ST_PTAIL: step_ptail(sd.u.ptail, pp, c, ti.drew, ti.st, st_raw); break;
         case ST_FINISH: step_finish(sd.u.finish, c); break;
         case ST_WSMALL: step_wsmall(sd.u.wsmall, pp, c); break;
@@ -1930,29 +1916,31 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
 
 // LDS words of a kind's body (the kernel of mixed batches holds every kind's
 // code, and its LDS decides how many workgroups a CU takes).
+constexpr u32 TAIL_WORDS = 3 * TAIL_TAB + TAIL_EXTRA, LFOLD_WORDS = 64 + SBLOCK * 6 + SBLOCK / 2 * 7;
 constexpr u32 lds_words(u32 kind) {
     return kind == ST_P       ? 64 + NWAVES * 64
            : kind == ST_PTAIL ? PT_LDS
            : kind == ST_FINISH ? SBLOCK
            : kind == ST_LINE   ? 64 * LINE_CHUNK
-           : kind == ST_LFOLD  ? 64 + SBLOCK * 6 + SBLOCK / 2 * 7
-           : kind == KALL || kind == ST_WTAIL || kind == ST_WSMALL || kind == ST_TOP ? 3 * TAIL_TAB
-                               : 2;
+           : kind == ST_LFOLD  ? LFOLD_WORDS
+           : kind == ST_WA0 || kind == ST_WT0 || kind == ST_WT ? NWAVES * T_ROW
+           : kind == ST_WTAIL || kind == ST_WSMALL || kind == ST_TOP ? TAIL_WORDS
+           : kind == KALL ? (TAIL_WORDS > LFOLD_WORDS ? TAIL_WORDS : LFOLD_WORDS)
+                          : 2;
 }
-static_assert(64 + SBLOCK * 6 + SBLOCK / 2 * 7 <= 3 * TAIL_TAB && 64 + NWAVES * 64 >= (1 << P_ROUNDS) + NWAVES * 8,
-              "lds_words");
+static_assert(64 + NWAVES * 64 >= (1 << P_ROUNDS) + NWAVES * 8, "lds_words");
 
 // A single proof's step, its descriptor passed by value as kernel argument;
 // one instantiation per step kind (and per gate mix and phase for omega
 // rounds) keeps each kernel's code and registers to what the kind needs.
 template <u32 KIND, int GK, int PH>
-__global__ void __launch_bounds__(SBLOCK) k_step_one(const StepDesc sd) {
+__global__ void __launch_bounds__(SBLOCK, 4) k_step_one(const StepDesc sd) {
     __shared__ __align__(16) u64 lds[lds_words(KIND)];
     run_step<KIND, GK, PH>(sd, blockIdx.x, lds);
 }
 
 // One step of each of several proofs.
-__global__ void __launch_bounds__(SBLOCK) k_step_jobs(const JobEntry *__restrict__ jobs, u32 njobs) {
+__global__ void __launch_bounds__(SBLOCK, 4) k_step_jobs(const JobEntry *__restrict__ jobs, u32 njobs) {
     u32 lo = 0, hi = njobs;
     const u32 b = blockIdx.x;
     while (hi - lo > 1) {
@@ -1964,7 +1952,7 @@ __global__ void __launch_bounds__(SBLOCK) k_step_jobs(const JobEntry *__restrict
 }
 
 // One step of each of several proofs, the job table in the kernel arguments.
-__global__ void __launch_bounds__(SBLOCK) k_step_table(const JobTable t) {
+__global__ void __launch_bounds__(SBLOCK, 4) k_step_table(const JobTable t) {
     u32 lo = 0, hi = t.n;
     const u32 b = blockIdx.x;
     while (hi - lo > 1) {

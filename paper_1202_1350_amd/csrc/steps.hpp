@@ -67,8 +67,7 @@ enum FinKind : u32 {
     FIN_P,     // R p-phase messages from rows of 2^R column sums
     FIN_W,     // omega message from rows of (E0, E1, O0, O1)
     FIN_LINE,  // h(t) values from rows of line sums; then tau and z_{i+1}
-    FIN_T,     // message (G(0), G(1), G(2)) from rows of three sums
-    FIN_T2,    // two table-round messages from rows of (G(0..2), Q0(0..2), Q1(0..2), Q2(0..2))
+    FIN_T,     // three table-round messages from rows of an oct's sums (T_ROW)
 };
 
 // Several rounds per launch.  The sums of a later round are, before the
@@ -79,7 +78,10 @@ enum FinKind : u32 {
 //     by eq(z, their other bits), add up to 2^R column sums T[x]; round k's
 //     S_t = sum over x with bit k = t of T[x] prod_{i<k} eq(x_i, r_i)
 //     prod_{i>k} eq(x_i, z_i), at one product an entry.
-//   table rounds, two: G'(t) = Q0(t) + r_k Q1(t) + r_k^2 Q2(t).
+//   table rounds, three: A F + C over an oct of entries is a polynomial of
+//     degree two in each of the three variables the rounds bind; its values at
+//     {0, 1, inf}^3 (inf: the leading coefficient, a product of differences),
+//     summed over the octs, are 27 words from which the three messages follow.
 
 constexpr u32 KALL = 0xFFFF;  // kind resolved at run time (mixed batches)
 
@@ -89,8 +91,8 @@ __host__ __device__ constexpr u32 fin_mask(u32 kind) {
     return kind == KALL                              ? 0xFFu
            : kind == ST_P                            ? (1u << FIN_P) | (1u << FIN_LINE)
            : kind == ST_PTAIL                        ? (1u << FIN_P) | (1u << FIN_LINE)
-           : kind == ST_WT                           ? (1u << FIN_T) | (1u << FIN_T2)
-           : kind == ST_WTAIL                        ? (1u << FIN_T) | (1u << FIN_T2)
+           : kind == ST_WT                           ? 1u << FIN_T
+           : kind == ST_WTAIL                        ? 1u << FIN_T
            : kind == ST_EQ                           ? (1u << FIN_LINE) | (1u << FIN_W)
            : kind == ST_END                          ? 1u << FIN_LINE
            : (kind == ST_W || kind == ST_FOLD || kind == ST_LT || kind == ST_LFOLD) ? 1u << FIN_W
@@ -117,6 +119,8 @@ struct ProofPtrs {
 // p-phase rounds, the beta prefix and z values recorded in `rec`, P_REC words).
 constexpr u32 P_ROUNDS = 7;  // most p-phase rounds a step sums (2^7 columns)
 constexpr u32 P_REC = 16;    // C and up to 15 z values
+constexpr u32 T_ROW = 32;    // an oct's sums: four slots for each of its eight lanes
+constexpr u32 WT_COLS = 4 * T_ROW;  // the sums of a tail's steps of three rounds
 constexpr u32 P_LAST = 5;    // a tail's last rounds, summed together
 constexpr u32 PT_COLS = 64;  // words of a tail's columns: its first rounds' at 0, the last ones' at 32
 struct Fin {
@@ -145,8 +149,8 @@ struct FinItem {
     const u64 *rows;
     u64 *msg;
     const u64 *rec;    // FIN_P
-    i32 draw;          // FIN_T2: the challenge drawn after the first message; FIN_P: of rec's first z
-    u32 nvals;         // FIN_LINE: values of this chunk; FIN_P: rounds
+    i32 draw;          // FIN_T: the first round's challenge; FIN_P: the challenge of rec's first z
+    u32 nvals;         // FIN_LINE: values of this chunk; FIN_P, FIN_T: rounds
     u32 pre;           // FIN_P: rounds between rec's C and the first of these
 };
 struct FinishArgs {
@@ -281,9 +285,11 @@ struct WaggArgs {
     u32 ntiles;              // tiles of whole chunks, at most 64 sorted positions each:
     const u32 *tch;          // tile t holds chunks [tch[t], tch[t+1])
 };
+// sum: whether the step sums rounds 0..2 (else it only forms the tables); nw
+// wires, whole octs if it does.
 struct Wt0Args {
-    u32 ph, hasC;
-    u64 npairs;
+    u32 ph, hasC, sum;
+    u64 nw;
     const u32 *xch;          // chunks of wire x: [xch[x], xch[x+1])
     const u64 *partA, *partC;
     const u64 *F;            // V_{i+1}
@@ -292,8 +298,8 @@ struct Wt0Args {
 // ST_WA0: wire x's gates sit at sorted positions [rowptr[x], rowptr[x+1])
 // (at most one chunk of gates per wire).
 struct Wa0Args {
-    u32 kind, ph, hasC;
-    u64 npairs;
+    u32 kind, ph, hasC, sum;
+    u64 nw;
     const u32 *perm, *rowptr;
     const u32 *oths;
     const u8 *types;
@@ -304,23 +310,21 @@ struct Wa0Args {
     u32 Lb;
     u64 *A, *C;              // level-0 tables
 };
-// Table step reading level k with pend (1 or 2) pending challenges: the
-// tables folded to level k+pend, that round's sums and the next round's
-// coefficients; a unit is a quad of level k+pend (4 << pend entries of
-// level k).
+// Table step: level k folded by its three challenges to level k + 3, stored,
+// and that level's sums; a unit is an entry of level k + 3 (whole octs).
 struct WtArgs {
-    u32 hasC, pend;
+    u32 hasC;
     u64 nu;
     const u64 *A, *C, *F;    // level k
-    u64 *An, *Cn, *Fn;       // level k+pend
+    u64 *An, *Cn, *Fn;       // level k + 3
 };
 struct WtailArgs {
     u32 k0, sp, hasC, last;
-    u32 pend;                // challenges the prologue drew (1 or 2): level k0 - pend is in memory
+    u32 pend;                // challenges this step draws first: level k0 - pend is in memory (3, or 0)
     u32 live;                // level-k0 entries [live, 2^{sp-k0}) are zero (not read)
     const u64 *A, *C, *F;    // level k0-pend, 2^{sp-k0+pend} entries
     u32 c0;                  // challenge index of round k0
-    u64 *msg;                // message slot of round k0
+    u64 *cols;               // WT_COLS words
     u64 *vout;
 };
 struct PtailArgs {
@@ -342,7 +346,7 @@ struct WsmallArgs {
     u32 eqn, eqL, eqbase;  // the point: coordinates, lo-table coordinates, challenge index
     u64 *eqlo, *eqhi;
     u32 sp, last, c0;       // last = phase (1: v1 into state[1]); c0: challenge index of round 0
-    u64 *msg, *vout;
+    u64 *cols, *vout;       // cols: WT_COLS words
 };
 
 // ST_TOP: the sum-check of layers 0 .. nl-1 in one workgroup.  Every one of
@@ -361,6 +365,7 @@ struct TopLayer {
     const u8 *type;            // its gate types (mixed layers)
     u64 *V;                    // V_i, written by the evaluation
     u64 *rec, *cols;           // the p-phase's record and columns (as PtailArgs)
+    u64 *wcols[2];             // the omega phases' sums (WT_COLS words each)
 };
 // ST_TOP also evaluates its layers, nl - 1 down to 0, from V_nl (the layer
 // below them, evaluated by ST_EVAL launches), and starts the proof as
