@@ -2528,31 +2528,39 @@ extern "C" int gkr_batch_prove(uint32_t n, const gkr_circuit *const *circuits,
 
 namespace {
 
-// Lagrange interpolation of y[0..D] at nodes 0..D, evaluated at x.
+// Interpolation of y[0..D] at nodes 0..D <= 32, evaluated at x: sum_i y_i
+// (-1)^{D-i} / (i! (D-i)!) prod_{j != i} (x - j), the products from both ends
+// (an inverse a node and D^2 products took half of a deep circuit's check).
 u64 lagrange_host(const u64 *y, u32 D, u64 x) {
     using namespace fp;
-    u64 acc = 0;
-    for (u32 i = 0; i <= D; i++) {
-        u64 num = 1, den = 1;
-        for (u32 j = 0; j <= D; j++) {
-            if (j == i) continue;
-            num = mul(num, sub(x, j));
-            den = mul(den, sub(i, j));
+    constexpr u32 MAXD = 32;
+    static const std::array<u64, MAXD + 1> ifact = [] {
+        std::array<u64, MAXD + 1> f{};
+        u64 p = 1;
+        for (u32 i = 0; i <= MAXD; i++) {
+            if (i) p = mul(p, i);
+            f[i] = inv(p);
         }
-        acc = add(acc, mul(y[i], mul(num, inv(den))));
+        return f;
+    }();
+    u64 suf[MAXD + 2];  // suf[i] = prod_{j >= i} (x - j)
+    suf[D + 1] = 1;
+    for (u32 i = D + 1; i-- > 0;) suf[i] = mul(suf[i + 1], sub(x, i));
+    u64 acc = 0, pre = 1;
+    for (u32 i = 0; i <= D; i++) {
+        const u64 t = mul(mul(y[i], mul(ifact[i], ifact[D - i])), mul(pre, suf[i + 1]));
+        acc = (D - i) & 1 ? sub(acc, t) : add(acc, t);
+        pre = mul(pre, sub(x, i));
     }
     return acc;
 }
 
-// G(r) for a degree-2 message given at 0, 1, 2.
+// G(r) for a degree-2 message given at 0, 1, 2: G0 + r (G1 - G0) +
+// r (r - 1) / 2 (G2 - 2 G1 + G0).
 u64 quad_at(const u64 *G, u64 r) {
     using namespace fp;
-    const u64 inv2 = 1ull << 60;  // 2 * 2^60 = 2^61 = 1
-    const u64 r1 = sub(r, 1), r2 = sub(r, 2);
-    u64 t0 = mul(mul(G[0], mul(r1, r2)), inv2);
-    u64 t1 = mul(G[1], mul(r, r2));
-    u64 t2 = mul(mul(G[2], mul(r, r1)), inv2);
-    return add(sub(t0, t1), t2);
+    const u64 c = mul(r, sub(r, 1)), half = c & 1 ? (c + P) >> 1 : c >> 1;
+    return red128(wide(r, sub(G[1], G[0])) + wide(half, sub(add(G[2], G[0]), add(G[1], G[1]))) + G[0]);
 }
 
 // ~T(pt) on the host by binding variables one at a time (small tables).
@@ -2693,130 +2701,164 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
         z[i + 1].resize(sp);
         for (u32 k = 0; k < sp; k++) z[i + 1][k] = add(r[s + k], mul(tau, sub(r[s + sp + k], r[s + k])));
     }
-    // Device part: add~ / mult~ per layer, and the inputs' extension at z_d.
+    // Device part: add~ / mult~ of every layer without a closed form, and the
+    // inputs' extension at z_d; each workgroup's sums go to pinned host memory.
     std::lock_guard<std::mutex> lk(g_vs.mu);
+    const bool closed = g_closed_forms.load() != 0;
+    std::vector<u32> gl;  // the layers passed over
+    u64 tab_words = 0;
+    u32 eq_blocks = 0, gate_blocks = 0;
+    std::vector<WireLayer> wl;
+    for (u32 i = 0; i < d; i++) {
+        if (closed && c->form[i] != GKR_WIRING_GATES) continue;  // on the host below
+        const u32 s = c->s[i], sp = c->s[i + 1];
+        WireLayer w;
+        memset(&w, 0, sizeof w);
+        w.kind = (u32)c->kind[i];
+        w.S = c->S[i];
+        w.s = s;
+        w.sp = sp;
+        split_half(s, &w.La);
+        split_half(sp, &w.Lb);
+        w.pt = (u32)c->co[i];
+        w.eq0 = eq_blocks;
+        w.block0 = gate_blocks;
+        w.type = c->type[i];
+        w.in1 = c->in1[i];
+        w.in2 = c->in2[i];
+        w.tab = (u64 *)tab_words;  // (its offset, for now)
+        eq_blocks += wire_eq_blocks(s, sp);
+        gate_blocks += wire_gate_blocks(c->S[i]);
+        tab_words += wire_table_words(s, sp) + BLOCK;  // (the last workgroup's threads past the tables write nothing)
+        gl.push_back(i);
+        wl.push_back(w);
+    }
+    const size_t wl_words = (wl.size() + 1) * sizeof(WireLayer) / 8;
+    static_assert(sizeof(WireLayer) % 8 == 0, "descriptors are staged as words");
     Arena sz;
-    const u64 npts = c->n_chals + c->s[d] + 8;
     struct {
-        u64 *pts, *tab, *partials, *res, *in;
-        u32 *flag;
+        u64 *up, *tab, *partials, *in;
     } v;
     auto lay = [&](Arena &a) {
-        v.pts = a.take<u64>(npts);
-        v.tab = a.take<u64>(6ull * HALF_MAX);
-        v.partials = a.take<u64>((u64)MAX_BLOCKS * 4);
-        v.res = a.take<u64>(2ull * d + 2);
+        v.up = a.take<u64>(c->n_chals + wl_words);  // points, then descriptors
+        v.tab = a.take<u64>(std::max<u64>(tab_words, 1));
+        v.partials = a.take<u64>(MLE_BLOCKS);
         v.in = a.take<u64>(inputs_on_device ? 1 : 2 * std::min<u64>(Sd, VCHUNK));
-        v.flag = a.take<u32>(1);
     };
     lay(sz);
-    int rc = vs_reserve(sz.used, 2ull * d + 3);
+    // pinned: the upload, the passes' sums, the extension's sums, the range flag
+    int rc = vs_reserve(sz.used, c->n_chals + wl_words + 2ull * gate_blocks + MLE_BLOCKS + 1);
     if (rc) return rc;
     Arena a;
     a.base = (char *)g_vs.mem;
     lay(a);
-    // points: chals as drawn, then z_d
-    std::vector<u64> pts(npts, 0);
-    std::copy(ch.begin(), ch.end(), pts.begin());
-    std::copy(z[d].begin(), z[d].end(), pts.begin() + c->n_chals);
-    HIP_TRY(hipMemcpyAsync(v.pts, pts.data(), npts * 8, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemsetAsync(v.flag, 0, 4, st));
-    u64 *T = v.tab;
-    int nb = 0;
-    const bool closed = g_closed_forms.load() != 0;
-    for (u32 i = 0; i < d; i++) {
-        if (closed && c->form[i] != GKR_WIRING_GATES) continue;  // on the host below
-        const u32 s = c->s[i], sp = c->s[i + 1];
-        const u64 *r = v.pts + c->co[i];
-        u32 La, Lb;
-        split_half(s, &La);
-        split_half(sp, &Lb);
-        LAUNCH(PC_TABLES, 0, launch_eq_halves(st, r, s, La, T, T + HALF_MAX));
-        LAUNCH(PC_TABLES, 0, launch_eq_halves(st, r + s, sp, Lb, T + 2 * HALF_MAX, T + 3 * HALF_MAX));
-        LAUNCH(PC_TABLES, 0,
-               launch_eq_halves(st, r + s + sp, sp, Lb, T + 4 * HALF_MAX, T + 5 * HALF_MAX));
-        WiringArgs wa;
-        wa.kind = c->kind[i];
-        wa.S = c->S[i];
-        wa.type = c->type[i];
-        wa.in1 = c->in1[i];
-        wa.in2 = c->in2[i];
-        wa.alo = T;
-        wa.ahi = T + HALF_MAX;
-        wa.La = La;
-        wa.blo = T + 2 * HALF_MAX;
-        wa.bhi = T + 3 * HALF_MAX;
-        wa.Lb = Lb;
-        wa.clo = T + 4 * HALF_MAX;
-        wa.chi = T + 5 * HALF_MAX;
-        wa.Lc = Lb;
-        wa.partials = v.partials;
-        LAUNCH(PC_WIRING, c->S[i] * 8.0, launch_wiring(st, wa, &nb));
-        LAUNCH(PC_MISC, 0, launch_reduce_rows(st, nb, 2, v.partials, v.res + 2 * i));
-    }
+    u64 *h_up = g_vs.h_res, *h_wire = h_up + c->n_chals + wl_words, *h_mle = h_wire + 2ull * gate_blocks;
+    u64 *h_flag = h_mle + MLE_BLOCKS;
+    *h_flag = 0;
+    int nb = mle_blocks(Sd);
     {
         MlePoint pt;
         memset(&pt, 0, sizeof pt);
         pt.s = c->s[d];
         for (u32 k = 0; k < pt.s; k++) pt.r[k] = z[d][k];
-        nb = mle_blocks(Sd);
         if (inputs_on_device) {
-            LAUNCH(PC_MLE, Sd * 8.0, launch_mle(st, Sd, inputs, nullptr, pt, 0, v.partials, nb, 0, v.flag));
+            LAUNCH(PC_MLE, Sd * 8.0, launch_mle(st, Sd, inputs, nullptr, pt, 0, h_mle, nb, 0, (u32 *)h_flag));
         } else {
-            rc = stream_mle<u64>(st, inputs, Sd, v.in, pt, v.partials, &nb, v.flag);
+            rc = stream_mle<u64>(st, inputs, Sd, v.in, pt, v.partials, &nb, (u32 *)h_flag);
             if (rc) return rc;
+            HIP_TRY(hipMemcpyAsync(h_mle, v.partials, nb * 8ull, hipMemcpyDeviceToHost, st));
         }
-        LAUNCH(PC_MISC, 0, launch_reduce_rows(st, nb, 1, v.partials, v.res + 2 * d));
     }
-    HIP_TRY(hipMemcpyAsync(g_vs.h_res, v.res, (2ull * d + 1) * 8, hipMemcpyDeviceToHost, st));
-    g_vs.h_res[2ull * d + 1] = 0;
-    HIP_TRY(hipMemcpyAsync(g_vs.h_res + 2ull * d + 1, v.flag, 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if ((uint32_t)g_vs.h_res[2ull * d + 1])
-        return fail(GKR_ERR_RANGE, "input value not below p");
-    const u64 *res = g_vs.h_res;
-    // Host replay of the protocol (a10).
+    if (!gl.empty()) {
+        u64 gates = 0;
+        for (WireLayer &w : wl) {
+            w.tab = v.tab + (u64)(uintptr_t)w.tab;
+            gates += w.S;
+        }
+        WireLayer endw;
+        memset(&endw, 0, sizeof endw);
+        endw.eq0 = eq_blocks;
+        endw.block0 = gate_blocks;
+        wl.push_back(endw);
+        memcpy(h_up, ch.data(), c->n_chals * 8);
+        memcpy(h_up + c->n_chals, wl.data(), wl.size() * sizeof(WireLayer));
+        HIP_TRY(hipMemcpyAsync(v.up, h_up, (c->n_chals + wl_words) * 8, hipMemcpyHostToDevice, st));
+        LAUNCH(PC_WIRING, gates * 8.0,
+               launch_wiring(st, (const WireLayer *)(v.up + c->n_chals), (u32)gl.size(), eq_blocks, gate_blocks, v.up,
+                             h_wire));
+    }
+    // Host replay of the protocol (a10) beside it, up to the first round that
+    // fails; what a layer's wiring check needs is kept for when the sums are in.
+    struct Layer {
+        u64 claim, beta, v1, v2, w;
+        bool line;  // v1 = v2 where layer i + 1 has one gate
+    };
+    std::vector<Layer> lv(d);
+    u32 upto = d;          // layers whose rounds all passed
+    int32_t bad_round = -1;
     u64 mi = 0;
     std::vector<u64> outs(1ull << c->s[0], 0);
     for (u32 g = 0; g < c->S[0]; g++) outs[g] = msgs[mi++];
     u64 claim = mle_host(outs, z[0].data(), c->s[0]);
-    for (u32 i = 0; i < d; i++) {
+    for (u32 i = 0; i < d && bad_round < 0; i++) {
         const u32 s = c->s[i], sp = c->s[i + 1], n = s + 2 * sp;
         const u64 *r = ch.data() + c->co[i];
         for (u32 j = 0; j < n; j++) {
             const u64 *G = msgs + mi;
             mi += 3;
             if (add(G[0], G[1]) != claim) {
-                reject(accepted, why, (int)i, (int)j, GKR_CHECK_ROUND);
-                return GKR_OK;
+                bad_round = (i32)j;
+                upto = i;
+                break;
             }
             claim = quad_at(G, r[j]);
         }
-        const u64 v1 = msgs[mi++], v2 = msgs[mi++];
-        u64 beta = 1;
-        for (u32 k = 0; k < s; k++) beta = mul(beta, eq(z[i][k], r[k]));
-        u64 addv = res[2 * i], mulv = res[2 * i + 1];
+        if (bad_round >= 0) break;
+        Layer &l = lv[i];
+        l.claim = claim;
+        l.v1 = msgs[mi++];
+        l.v2 = msgs[mi++];
+        l.beta = 1;
+        for (u32 k = 0; k < s; k++) l.beta = mul(l.beta, eq(z[i][k], r[k]));
+        if (closed && c->form[i] != GKR_WIRING_GATES)
+            l.w = wiring_closed(c->form[i], c->S[i], s, sp, r, r + s, r + s + sp);
+        l.line = sp != 0 || l.v1 == l.v2;
+        u64 y[33];  // (s_{i+1} <= 31)
+        y[0] = l.v1;
+        y[1] = l.v2;
+        for (u32 t = 2; t <= sp; t++) y[t] = msgs[mi++];
+        claim = lagrange_host(y, std::max<u32>(sp, 1), r[n]);
+    }
+    HIP_TRY(hipStreamSynchronize(st));
+    if ((u32)*h_flag) return fail(GKR_ERR_RANGE, "input value not below p");
+    for (u32 i = 0, q = 0; i < upto; i++) {
+        const Layer &l = lv[i];
+        u64 addv = 0, mulv = 0;
         if (closed && c->form[i] != GKR_WIRING_GATES) {
-            const u64 w = wiring_closed(c->form[i], c->S[i], s, sp, r, r + s, r + s + sp);
-            addv = c->kind[i] == KIND_ADD ? w : 0;
-            mulv = c->kind[i] == KIND_MUL ? w : 0;
+            (c->kind[i] == KIND_ADD ? addv : mulv) = l.w;
+        } else {
+            for (u32 b = wl[q].block0; b < wl[q + 1].block0; b++) {
+                addv = add(addv, h_wire[2 * b]);
+                mulv = add(mulv, h_wire[2 * b + 1]);
+            }
+            q++;
         }
-        const u64 rhs = mul(beta, add(mul(addv, add(v1, v2)), mul(mulv, mul(v1, v2))));
-        if (rhs != claim) {
-            reject(accepted, why, (int)i, (int)n, GKR_CHECK_WIRING);
+        if (mul(l.beta, add(mul(addv, add(l.v1, l.v2)), mul(mulv, mul(l.v1, l.v2)))) != l.claim) {
+            reject(accepted, why, (int)i, (int)(c->s[i] + 2 * c->s[i + 1]), GKR_CHECK_WIRING);
             return GKR_OK;
         }
-        if (sp == 0 && v1 != v2) {
+        if (!l.line) {
             reject(accepted, why, (int)i, -1, GKR_CHECK_LINE);
             return GKR_OK;
         }
-        std::vector<u64> y(std::max<u32>(sp, 1) + 1);
-        y[0] = v1;
-        y[1] = v2;
-        for (u32 t = 2; t <= sp; t++) y[t] = msgs[mi++];
-        claim = lagrange_host(y.data(), std::max<u32>(sp, 1), r[n]);
     }
-    if (res[2 * d] != claim) {
+    if (bad_round >= 0) {
+        reject(accepted, why, (int)upto, bad_round, GKR_CHECK_ROUND);
+        return GKR_OK;
+    }
+    u64 ext = 0;
+    for (int k = 0; k < nb; k++) ext = add(ext, h_mle[k]);
+    if (ext != claim) {
         reject(accepted, why, (int)d, -1, GKR_CHECK_INPUT);
         return GKR_OK;
     }

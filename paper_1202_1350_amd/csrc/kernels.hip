@@ -61,50 +61,77 @@ __device__ __forceinline__ u64 chi_bits(u64 x, const u64 *pt, u32 n) {
     return e;
 }
 
-__global__ void __launch_bounds__(BLOCK) k_eq_halves(const u64 *pt, u32 s, u32 L, u64 *lo, u64 *hi) {
-    const u64 nlo = 1ull << L, nhi = 1ull << (s - L);
-    for (u64 x = GTID; x < nlo + nhi; x += GSTRIDE) {
-        if (x < nlo)
-            lo[x] = chi_bits(x, pt, L);
-        else
-            hi[x - nlo] = chi_bits(x - nlo, pt + L, s - L);
-    }
-}
-
-hipError_t launch_eq_halves(hipStream_t st, const u64 *pt, u32 s, u32 L, u64 *lo, u64 *hi) {
-    u64 n = (1ull << L) + (1ull << (s - L));
-    hipLaunchKernelGGL(k_eq_halves, dim3(blocks_for(n)), dim3(BLOCK), 0, st, pt, s, L, lo, hi);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------- verifier (a10)
+//
+// All layers in two launches: a layer's own launches (three tables, a pass, a
+// reduction) are a few thousand gates' work and cost their launch latencies
+// (the MatMult check at N = 64, 66 such layers: 330 launches, 1.5 ms a
+// verification; two launches, with the host's replay beside them, 0.07 ms).
 
-template <int KIND>
-__global__ void __launch_bounds__(BLOCK) k_wiring(WiringArgs a) {
-    const u64 am = (1ull << a.La) - 1, bm = (1ull << a.Lb) - 1, cm = (1ull << a.Lc) - 1;
-    u64 acc[2] = {0, 0};
-    for (u64 g = GTID; g < a.S; g += GSTRIDE) {
-        const u32 i1 = a.in1[g], i2 = a.in2[g];
-        const u64 ea = mul(a.alo[g & am], a.ahi[g >> a.La]);
-        const u64 eb = mul(a.blo[i1 & bm], a.bhi[i1 >> a.Lb]);
-        const u64 ec = mul(a.clo[i2 & cm], a.chi[i2 >> a.Lc]);
-        const u64 e = mul(ea, mul(eb, ec));
-        const bool ismul = KIND == KIND_MUL || (KIND == KIND_MIXED && a.type[g]);
-        if (ismul)
-            acc[1] = add(acc[1], e);
-        else
-            acc[0] = add(acc[0], e);
+// The layer of workgroup b.
+template <u32 WireLayer::*FIRST>
+__device__ __forceinline__ u32 layer_of(const WireLayer *L, u32 n, u32 b) {
+    u32 lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const u32 mid = (lo + hi) >> 1;
+        if (L[mid].*FIRST <= b) lo = mid; else hi = mid;
     }
-    block_store<2>(acc, a.partials + 2 * (u64)blockIdx.x);
+    return lo;
 }
 
-hipError_t launch_wiring(hipStream_t st, const WiringArgs &a, int *nblocks) {
-    int nb = blocks_for(a.S, 4);
-    *nblocks = nb;
-    dim3 g(nb), b(BLOCK);
-    if (a.kind == KIND_ADD) hipLaunchKernelGGL(k_wiring<KIND_ADD>, g, b, 0, st, a);
-    else if (a.kind == KIND_MUL) hipLaunchKernelGGL(k_wiring<KIND_MUL>, g, b, 0, st, a);
-    else hipLaunchKernelGGL(k_wiring<KIND_MIXED>, g, b, 0, st, a);
+__global__ void __launch_bounds__(BLOCK) k_wire_eq(const WireLayer *__restrict__ L, u32 n, const u64 *__restrict__ pts) {
+    const WireLayer &w = L[layer_of<&WireLayer::eq0>(L, n, blockIdx.x)];
+    u64 x = (u64)(blockIdx.x - w.eq0) * BLOCK + threadIdx.x;
+    u64 *tab = w.tab + x;
+    // the half this entry is of
+    const u32 bits[6] = {w.La, w.s - w.La, w.Lb, w.sp - w.Lb, w.Lb, w.sp - w.Lb};
+    u32 at = w.pt;
+#pragma unroll
+    for (u32 h = 0; h < 6; h++) {
+        const u64 len = 1ull << bits[h];
+        if (x < len) {
+            *tab = chi_bits(x, pts + at, bits[h]);
+            return;
+        }
+        x -= len;
+        at += bits[h];
+    }
+}
+
+__global__ void __launch_bounds__(BLOCK) k_wiring(const WireLayer *__restrict__ L, u32 n, u64 *out) {
+    const u32 q = layer_of<&WireLayer::block0>(L, n, blockIdx.x);
+    const WireLayer &w = L[q];
+    const u32 lb = blockIdx.x - w.block0, nb = L[q + 1].block0 - w.block0;
+    const u64 am = (1ull << w.La) - 1, bm = (1ull << w.Lb) - 1;
+    const u64 *alo = w.tab, *ahi = alo + (1ull << w.La), *blo = ahi + (1ull << (w.s - w.La));
+    const u64 *bhi = blo + (1ull << w.Lb), *clo = bhi + (1ull << (w.sp - w.Lb)), *chi = clo + (1ull << w.Lb);
+    u64 acc[2] = {0, 0};
+    for (u64 g = (u64)lb * BLOCK + threadIdx.x; g < w.S; g += (u64)nb * BLOCK) {
+        const u32 i1 = w.in1[g], i2 = w.in2[g];
+        const u64 ea = mul(alo[g & am], ahi[g >> w.La]);
+        const u64 eb = mul(blo[i1 & bm], bhi[i1 >> w.Lb]);
+        const u64 ec = mul(clo[i2 & bm], chi[i2 >> w.Lb]);
+        const u64 e = mul(ea, mul(eb, ec));
+        const bool ismul = w.kind == KIND_MUL || (w.kind == KIND_MIXED && w.type[g]);
+        acc[0] = add(acc[0], ismul ? 0 : e);
+        acc[1] = add(acc[1], ismul ? e : 0);
+    }
+    block_store<2>(acc, out + 2 * (u64)blockIdx.x);
+}
+
+u64 wire_table_words(u32 s, u32 sp) {
+    return (1ull << (s / 2)) + (1ull << (s - s / 2)) + 2 * ((1ull << (sp / 2)) + (1ull << (sp - sp / 2)));
+}
+u32 wire_eq_blocks(u32 s, u32 sp) { return (u32)((wire_table_words(s, sp) + BLOCK - 1) / BLOCK); }
+u32 wire_gate_blocks(u32 S) {
+    // two gates a thread before another workgroup starts, at most 256 a layer
+    return std::max<u32>(1, std::min<u32>(256, (S + 2 * BLOCK - 1) / (2 * BLOCK)));
+}
+
+hipError_t launch_wiring(hipStream_t st, const WireLayer *L, u32 n, u32 eq_blocks, u32 gate_blocks, const u64 *pts,
+                         u64 *out) {
+    hipLaunchKernelGGL(k_wire_eq, dim3(eq_blocks), dim3(BLOCK), 0, st, L, n, pts);
+    hipLaunchKernelGGL(k_wiring, dim3(gate_blocks), dim3(BLOCK), 0, st, L, n, out);
     return hipGetLastError();
 }
 
@@ -224,21 +251,6 @@ hipError_t launch_mle(hipStream_t st, u64 n, const u64 *T64, const u32 *T32, con
         hipLaunchKernelGGL((k_mle<u32, 4>), g, b, 0, st, n, T32, pt, x0, partials, accumulate, bad);
     else
         hipLaunchKernelGGL((k_mle<u32, 1>), g, b, 0, st, n, T32, pt, x0, partials, accumulate, bad);
-    return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(BLOCK) k_reduce_rows(int nparts, int K, const u64 *partials, u64 *out) {
-    u64 v[4] = {0, 0, 0, 0};
-    for (int r = threadIdx.x; r < nparts; r += BLOCK)
-        for (int k = 0; k < K; k++) v[k] = add(v[k], partials[(u64)r * K + k]);
-    __shared__ u64 res[4];
-    block_store<4>(v, res);
-    __syncthreads();
-    if (threadIdx.x < K) out[threadIdx.x] = res[threadIdx.x];
-}
-
-hipError_t launch_reduce_rows(hipStream_t st, int nparts, int K, const u64 *partials, u64 *out) {
-    hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(BLOCK), 0, st, nparts, K, partials, out);
     return hipGetLastError();
 }
 

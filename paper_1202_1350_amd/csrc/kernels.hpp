@@ -32,27 +32,29 @@ inline int blocks_for(u64 n, u64 per = 1) {
     return (int)b;
 }
 
-// ---- proof bookkeeping ----------------------------------------------------
-// eq half tables of a point pt[0..s): lo[x] = chi_x(pt[0..L)) for x < 2^L,
-// hi[y] = chi_y(pt[L..s)) for y < 2^{s-L}; chi_x(pt) = lo[x & (2^L-1)] * hi[x >> L].
-hipError_t launch_eq_halves(hipStream_t st, const u64 *pt, u32 s, u32 L, u64 *lo, u64 *hi);
-
 // ---- verifier (a10) ---------------------------------------------------------
-// Per workgroup (add~, mult~) partial sums at (a*, b*, c*) from half tables.
-struct WiringArgs {
-    int kind;
-    u32 S;
+// A layer whose add~ and mult~ at (a*, b*, c*) take a pass over its gates.
+// Its eq half tables (entry x of a point's halves: chi_x = lo[x mod 2^L]
+// hi[x >> L]) sit one after another from tab: a* (2^La, 2^{s-La}), b* and c*
+// (2^Lb, 2^{sp-Lb} each).  One launch forms the tables of every such layer and
+// one passes over all their gates; workgroups [eq0, next eq0) and [block0,
+// next block0) of them belong to the layer.
+struct WireLayer {
+    u32 kind, S, s, sp, La, Lb;
+    u32 pt;            // a*, b*, c* in the points
+    u32 eq0, block0;
+    u32 pad;
     const u8 *type;
     const u32 *in1, *in2;
-    const u64 *alo, *ahi;
-    u32 La;
-    const u64 *blo, *bhi;
-    u32 Lb;
-    const u64 *clo, *chi;
-    u32 Lc;
-    u64 *partials;
+    u64 *tab;
 };
-hipError_t launch_wiring(hipStream_t st, const WiringArgs &a, int *nblocks);
+u64 wire_table_words(u32 s, u32 sp);
+u32 wire_eq_blocks(u32 s, u32 sp);
+u32 wire_gate_blocks(u32 S);
+// L: n descriptors on the device, then one whose eq0 and block0 are the totals.
+// out[2b], out[2b+1]: workgroup b's sums over ADD and MUL gates.
+hipError_t launch_wiring(hipStream_t st, const WireLayer *L, u32 n, u32 eq_blocks, u32 gate_blocks, const u64 *pts,
+                         u64 *out);
 // Multilinear extension of T (n values, u64 or u32) at the point pt (s
 // coordinates, the others 0): partial sums of nb workgroups, stored, or added
 // to the sums already there (accumulate).  A chunk of a longer table starts
@@ -65,9 +67,6 @@ constexpr int MLE_BLOCKS = 2048;
 int mle_blocks(u64 n);
 hipError_t launch_mle(hipStream_t st, u64 n, const u64 *T64, const u32 *T32, const MlePoint &pt, u64 x0, u64 *partials,
                       int nb, int accumulate, u32 *bad);
-// Fold nparts rows of K partial sums into out[0..K).
-hipError_t launch_reduce_rows(hipStream_t st, int nparts, int K, const u64 *partials, u64 *out);
-
 // ---- field check ----------------------------------------------------------
 hipError_t launch_field_op(hipStream_t st, int op, const u64 *a, const u64 *b, u64 *out, u64 n);
 
