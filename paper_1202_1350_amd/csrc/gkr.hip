@@ -3648,7 +3648,7 @@ extern "C" int nif2_verify(const uint64_t *a, uint64_t n, uint32_t h, int on_dev
     hipStream_t st = pick_stream(hip_stream);
     if (!st) return fail(GKR_ERR_DEVICE, "no stream");
     const u64 v = (n + h - 1) / h;
-    const u32 nb = nif2_rowsum_blocks(v);
+    const u32 nb = nif2_rowsum_blocks(h, v);
     std::lock_guard<std::mutex> lk(g_nif2.mu);
     struct {
         u64 *L, *in;

@@ -11,7 +11,7 @@
 // are the data squared, the odd points are f_y on the coset xi H, obtained
 // from an inverse transform (values -> coefficients c), a twist
 // c_k xi^k / h and a forward transform.
-#include "fp61.hpp"
+#include "lanes.hpp"
 #include "nif2.hpp"
 
 namespace gkr {
@@ -318,7 +318,15 @@ __device__ __forceinline__ void row_pass(u64 *W, u32 h, u32 s, u32 logty, const 
     }
 }
 
-// Squares of the tile's TY values at each of the thread's positions.
+// The square of a value, added to sums of at most four terms.
+__device__ __forceinline__ void square(Sums &s, u64 v) {
+    const Half x = halves(fold(v));
+    s.ll += (u64)x.l * x.l;
+    s.mm += (u64)x.l * (2 * x.h);
+    s.hh += (u64)x.h * x.h;
+}
+// Squares of the tile's values added per position.  Tiles of few rows (long
+// ones): a thread sums its positions' TY values into acc.
 template <int NC>
 __device__ __forceinline__ void square_sums(const u64 *W, u32 h, u32 logty, u64 (&acc)[NC]) {
 #pragma unroll
@@ -329,27 +337,49 @@ __device__ __forceinline__ void square_sums(const u64 *W, u32 h, u32 logty, u64 
             for (u32 y = 0; y < (1u << logty); y += 4) {
                 Sums s;
 #pragma unroll
-                for (u32 i = 0; i < 4; i++) {
-                    const Half x = halves(fold(W[(p << logty) + y + i]));
-                    s.ll += (u64)x.l * x.l;
-                    s.mm += (u64)x.l * (2 * x.h);
-                    s.hh += (u64)x.h * x.h;
-                }
+                for (u32 i = 0; i < 4; i++) square(s, W[(p << logty) + y + i]);
                 t = fold(t + total<4>(s));
             }
             acc[c] = t;
         }
     }
 }
+// Short rows: a row a lane (a thread a position would leave most threads
+// idle), summed over the lanes of a position into s_acc, LDS.
+__device__ __forceinline__ void square_lanes(const u64 *W, u32 h, u32 logty, u64 *s_acc) {
+    const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, lw = logty < 6 ? logty : 6;  // log2 lanes a position
+    const u32 y0 = lane & ((1u << lw) - 1), per = 64 >> lw;
+    for (u32 p0 = w * per; p0 < h; p0 += RB / 64 * per) {  // (wave-uniform)
+        const u32 p = p0 + (lane >> lw);
+        u64 t = 0;
+        if (p < h) {
+            for (u32 y = y0; y < (1u << logty); y += 64 * 4) {
+                Sums s;
+#pragma unroll
+                for (u32 i = 0; i < 4; i++)
+                    if (y + 64 * i < (1u << logty)) square(s, W[(p << logty) + y + 64 * i]);
+                t = fold(t + total<4>(s));
+            }
+        }
+        t = fp::canon(t);
+        for (u32 b = 0; b < lw; b++) t = plus_bit(t, b);  // (uniform)
+        if (y0 == 0 && p < h) s_acc[p] = add(s_acc[p], t);
+    }
+}
 
-// NC: positions a thread accumulates, ceil(h / RB).
+// NC: positions a thread accumulates, ceil(h / RB); 0: positions accumulated in
+// LDS, after the tile.
 template <int NC>
 __global__ void __launch_bounds__(RB, NC <= 5 ? 4 : 2) k_nif2_rows_lds(const RowArgs a) {
     extern __shared__ u64 W[];
+    constexpr int NA = NC ? NC : 1;
     const u32 tid = threadIdx.x, ty = 1u << a.logty;
-    u64 even[NC], odd[NC];
+    u64 *s_acc = W + ((u64)a.h << a.logty);
+    u64 even[NA], odd[NA];
 #pragma unroll
-    for (int c = 0; c < NC; c++) even[c] = odd[c] = 0;
+    for (int c = 0; c < NA; c++) even[c] = odd[c] = 0;
+    if (!NC)
+        for (u32 p = tid; p < 2 * a.h; p += RB) s_acc[p] = 0;
     // Adjacent tiles share cache lines, so workgroups of one XCD (equal
     // blockIdx mod 8) take adjacent tiles.
     const u32 xcd = blockIdx.x & 7, per = (a.ntiles + 7) / 8;
@@ -385,7 +415,7 @@ __global__ void __launch_bounds__(RB, NC <= 5 ? 4 : 2) k_nif2_rows_lds(const Row
             }
         }
         __syncthreads();
-        square_sums<NC>(W, a.h, a.logty, even);
+        if (NC) square_sums<NA>(W, a.h, a.logty, even); else square_lanes(W, a.h, a.logty, s_acc);
         for (u32 q = 0; q < 2 * a.nf; q++) {
             const u32 d = q < a.nf ? q : q - a.nf;
             const Half *rt = a.roots + a.root_at[q];
@@ -399,7 +429,11 @@ __global__ void __launch_bounds__(RB, NC <= 5 ? 4 : 2) k_nif2_rows_lds(const Row
             }
         }
         __syncthreads();
-        square_sums<NC>(W, a.h, a.logty, odd);
+        if (NC) square_sums<NA>(W, a.h, a.logty, odd); else square_lanes(W, a.h, a.logty, s_acc + a.h);
+    }
+    if (!NC) {
+        __syncthreads();
+        for (u32 p = tid; p < 2 * a.h; p += RB) a.part[(u64)blockIdx.x * 2 * a.h + p] = s_acc[p];
     }
 #pragma unroll
     for (int c = 0; c < NC; c++) {
@@ -440,17 +474,23 @@ __global__ void __launch_bounds__(1024) k_nif2_parts(const PfaPlan pl, const u64
     }
 }
 
-// Rows a tile holds: a power of two, 4 to 64, at most 80 KB of LDS (two
+// Rows a tile holds: a power of two, at least 4, at most 80 KB of LDS (two
 // workgroups a CU: one loads while the other transforms), except that rows of
-// more than 2560 values take 160 KB with 4.
+// more than 2560 values take 160 KB with 4.  Rows of fewer than 64 values
+// accumulate over lanes in LDS with up to 512 a tile, longer ones over threads'
+// positions with up to 64: 24 million values at h = 9 take 190 us so (820 with
+// a thread a position), at h = 99 302 us (400 over lanes), at 225 373 (491).
+static bool over_lanes(u32 h) { return h < 64; }
+static u64 tile_bytes(u32 h, u32 l) { return 8ull * h * ((1ull << l) + (over_lanes(h) ? 2 : 0)); }
 static u32 tile_log(u32 h) {
+    const u32 most = over_lanes(h) ? 9 : 6;
     u32 l = 2;
-    while (l < 6 && (u64)h * 8 * (2u << l) <= 80 * 1024) l++;
+    while (l < most && tile_bytes(h, l + 1) <= 80 * 1024) l++;
     return l;
 }
 u32 nif2_lds_groups(u32 h, u64 v) {
-    const u64 tiles = (v + (1ull << tile_log(h)) - 1) >> tile_log(h);
-    const u64 lds = (u64)h * 8 << tile_log(h), most = 256 * std::min<u64>(4, 160 * 1024 / lds);
+    const u32 l = tile_log(h);
+    const u64 tiles = (v + (1ull << l) - 1) >> l, most = 256 * std::min<u64>(4, 160 * 1024 / tile_bytes(h, l));
     return (u32)((std::min<u64>(tiles, most) + 7) / 8 * 8);
 }
 
@@ -486,11 +526,12 @@ hipError_t launch_nif2_rows_lds(hipStream_t st, const PfaPlan &pl, const u64 *a,
             for (u32 n2 = 1; n2 < 5; n2++)
                 for (u32 k1 = 1; k1 < 5; k1++) put(fp::pow(w, n2 * k1));
     }
-    const u32 nwg = nif2_lds_groups(pl.h, v), lds = pl.h * 8u << r.logty;
+    const u32 nwg = nif2_lds_groups(pl.h, v), lds = (u32)tile_bytes(pl.h, r.logty);
     hipLaunchKernelGGL(k_nif2_tables, dim3((pl.h + NT - 1) / NT), dim3(NT), 0, st, pl, xi, fp::inv(pl.h), pos, tw);
     const u32 nc = (pl.h + RB - 1) / RB;
 #define RK(N) hipLaunchKernelGGL(k_nif2_rows_lds<N>, dim3(nwg), dim3(RB), lds, st, r)
-    if (nc <= 1) RK(1);
+    if (over_lanes(pl.h)) RK(0);
+    else if (nc <= 1) RK(1);
     else if (nc <= 3) RK(3);
     else if (nc <= 5) RK(5);
     else RK(10);
@@ -662,8 +703,11 @@ __global__ void __launch_bounds__(RB) k_nif2_rowsum(const u64 *__restrict__ a, u
     if (tid == 0) out[blockIdx.x] = s;
 }
 
-u32 nif2_rowsum_blocks(u64 v) {
-    const u64 rw = v >= 64 * 512 ? 64 : 16, b = (v + rw - 1) / rw;
+// Rows a workgroup takes at a time: 512, a thread a row, where rows are short;
+// else 64 while they fill the chip.
+static u64 rowsum_rows(u32 h, u64 v) { return v < 64 * 512 ? 16 : h > 64 ? 64 : 512; }
+u32 nif2_rowsum_blocks(u32 h, u64 v) {
+    const u64 rw = rowsum_rows(h, v), b = (v + rw - 1) / rw;
     return 1 + (u32)std::min<u64>(b, NIF2_ROW_BLOCKS - 1);
 }
 
@@ -672,10 +716,13 @@ hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h,
     const u64 rh = fp::pow(r, h);
     hipLaunchKernelGGL(k_nif2_bases, dim3((3 * h + NT - 1) / NT), dim3(NT), 0, st, w, xi, (u64)h, r, sub(rh, 1),
                        sub(mul(rh, rh), 1), L, flag);
-    const dim3 g(nif2_rowsum_blocks(v));
+    const dim3 g(nif2_rowsum_blocks(h, v));
+    const u64 rw = rowsum_rows(h, v);
     const u32 full = (u32)(n / v);
     const u64 rem = n % v;
-    if (v >= 64 * 512)
+    if (rw == 512)
+        hipLaunchKernelGGL(k_nif2_rowsum<512>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
+    else if (rw == 64)
         hipLaunchKernelGGL(k_nif2_rowsum<64>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
     else
         hipLaunchKernelGGL(k_nif2_rowsum<16>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
