@@ -1231,8 +1231,12 @@ struct Planner {
             // eq table of the phase's point.
             const bool wsmall = c->omega_algo != GKR_OMEGA_GATES && sp >= 1 &&
                                 (1ull << sp) <= (u64)TAIL_LIM && c->grp[0][i].single && c->grp[1][i].single;
+            // Level-0 steps that sum the gates per wire form narrow points' eq
+            // tables themselves.
+            const bool singles = c->omega_algo != GKR_OMEGA_GATES && c->grp[0][i].single && c->grp[1][i].single;
+            const u32 eqL = singles && sp >= 1 && std::max(s, sp) <= EQ_THIRDS ? std::max<u32>(1, (std::max(s, sp) + 2) / 3) : 0;
             // ---- eq tables of a* (the p-phase tail recorded every challenge)
-            if (!wsmall) {
+            if (!wsmall && !eqL) {
                 const u32 La = s / 2;
                 const u64 ne = (1ull << La) + (1ull << (s - La));
                 StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
@@ -1325,7 +1329,7 @@ struct Planner {
                 for (u32 ph = 1; ph <= 2; ph++) {
                     const u32 rbase = s + (ph == 2 ? sp : 0);
                     const u32 Lb = sp / 2;
-                    if (ph == 2) {
+                    if (ph == 2 && !eqL) {
                         const u64 ne = (1ull << Lb) + (1ull << (sp - Lb));
                         StepDesc &e = addg(ST_EQ, ne, 1, 8.0 * ne);
                         e.u.eq = EqArgs{sp, Lb, co + s, w ? w->blo : nullptr, w ? w->bhi : nullptr};
@@ -1342,6 +1346,10 @@ struct Planner {
                         a.ph = ph;
                         a.hasC = hasC;
                         a.sum = k0 > 0;
+                        a.eqL = eqL;
+                        a.s = s;
+                        a.sp = sp;
+                        a.co = co;
                         a.nw = NL;
                         a.perm = dg->perm;
                         a.rowptr = dg->rowptr;

@@ -814,17 +814,17 @@ __device__ __forceinline__ void step_line(const LineArgs &a, const Ctx &c, u64 *
 // gates (sC); v1 enters when the level-0 tables are formed.
 // GK, PH: the layer's gate mix (0 ADD, 1 MUL, 2 mixed) and the phase when
 // known at compile time, -1 and 0 to read them from a.
-template <int GK = -1, int PH = 0, typename Args>
-__device__ __forceinline__ void wire_sums(const Args &a, u32 p0, u32 p1, u64 &sA_out, u64 &sC_out) {
+// wa(g): beta chi_g(a*); wb(i): chi_i(b*).
+template <int GK, int PH, typename Args, typename Wa, typename Wb>
+__device__ __forceinline__ void wire_sums_of(const Args &a, u32 p0, u32 p1, u64 &sA_out, u64 &sC_out, Wa wa, Wb wb) {
     const u32 kind = GK >= 0 ? (u32)GK : a.kind, ph = PH > 0 ? (u32)PH : a.ph;
-    const u64 amask = (1ull << a.La) - 1, bmask = (1ull << a.Lb) - 1;
     // branch-free updates keep both sums in registers; a sum that a gate
     // mix leaves at zero is not updated
     u64 sA = 0, sC = 0;
     for (u32 p = p0; p < p1; p++) {
         const u32 g = a.perm[p], o = a.oths[p];
         const bool ismul = kind == 1 || (kind == 2 && a.types[p]);
-        u64 w = mul(a.alo[g & amask], a.ahi[g >> a.La]);  // beta chi_g(a*): lo carries beta
+        u64 w = wa(g);
         if (ph == 1) {
             const u64 wy = mul(w, a.Vn[o]);
             if (kind == 1) {
@@ -834,8 +834,7 @@ __device__ __forceinline__ void wire_sums(const Args &a, u32 p0, u32 p1, u64 &sA
                 sC = add(sC, ismul ? 0 : wy);
             }
         } else {
-            const u32 i1 = o;
-            w = mul(w, mul(a.blo[i1 & bmask], a.bhi[i1 >> a.Lb]));
+            w = mul(w, wb(o));
             if (kind == 1) {
                 sC = add(sC, w);
             } else if (kind == 0) {
@@ -848,6 +847,13 @@ __device__ __forceinline__ void wire_sums(const Args &a, u32 p0, u32 p1, u64 &sA
     }
     sA_out = sA;
     sC_out = sC;
+}
+template <int GK = -1, int PH = 0, typename Args>
+__device__ __forceinline__ void wire_sums(const Args &a, u32 p0, u32 p1, u64 &sA_out, u64 &sC_out) {
+    const u64 amask = (1ull << a.La) - 1, bmask = (1ull << a.Lb) - 1;
+    wire_sums_of<GK, PH>(
+        a, p0, p1, sA_out, sC_out, [&](u32 g) { return mul(a.alo[g & amask], a.ahi[g >> a.La]); },
+        [&](u32 i) { return mul(a.blo[i & bmask], a.bhi[i >> a.Lb]); });
 }
 
 // Value v of lane l (l uniform or not; every lane of the wave takes part).
@@ -1033,9 +1039,49 @@ __device__ __forceinline__ void step_wt0(const Wt0Args &a, const ProofPtrs &pp, 
     if (a.sum) oct_row(q, c.lds, row);
 }
 
+// Thirds of the eq table of the n coordinates pt (chals): entry (q, x) of tab,
+// x < 2^L, is chi of x over coordinates q L .. (q+1) L - 1 (those past n are 0),
+// times scale in third 0.  One entry a thread and turn.
+__device__ __forceinline__ void eq_thirds(u64 *tab, const u64 *pt, u32 n, u32 L, u64 scale, u32 first, u32 step) {
+    for (u32 e = first; e < (3u << L); e += step) {
+        const u32 q = e >> L, x = e & ((1u << L) - 1);
+        u64 f[7];  // (L <= 7)
+#pragma unroll
+        for (u32 k = 0; k < 7; k++) {
+            const u32 j = q * L + k;
+            const u64 r = k < L && j < n ? pt[j] : 0;
+            f[k] = fp::eqbit((x >> k) & 1, r);
+        }
+        const u64 v = mul(mul(mul(f[0], f[1]), mul(f[2], f[3])), mul(mul(f[4], f[5]), f[6]));
+        tab[q * EQ_THIRD + x] = q == 0 ? mul(scale, v) : v;
+    }
+}
+static_assert(EQ_THIRD == 1 << 7 && EQ_THIRDS <= 3 * 7, "thirds of at most 7 coordinates");
+
 // GK, PH: the gate mix and phase, compile-time (one kernel each) or -1, 0.
 template <int GK, int PH>
 __device__ __forceinline__ void step_wa0(const Wa0Args &a, const ProofPtrs &pp, const Ctx &c, u64 *row) {
+    if (a.eqL) {  // (uniform)
+        const u32 ph = PH > 0 ? (u32)PH : a.ph, L = a.eqL, m = (1u << L) - 1;
+        u64 *ta = c.lds + NWAVES * T_ROW, *tb = ta + 3 * EQ_THIRD;
+        const u32 half = SBLOCK / 2, tid = threadIdx.x;
+        if (ph == 1)
+            eq_thirds(ta, pp.chals + a.co, a.s, L, pp.state[0], tid, SBLOCK);
+        else if (tid < half)  // (the two tables side by side)
+            eq_thirds(ta, pp.chals + a.co, a.s, L, pp.state[0], tid, half);
+        else
+            eq_thirds(tb, pp.chals + a.co + a.s, a.sp, L, 1, tid - half, half);
+        __syncthreads();
+        auto chi = [&](const u64 *t, u32 x) {
+            return mul(mul(t[x & m], t[EQ_THIRD + ((x >> L) & m)]), t[2 * EQ_THIRD + (x >> (2 * L))]);
+        };
+        level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
+            wire_sums_of<GK, PH>(
+                a, a.rowptr[x], a.rowptr[x + 1], sA, sC, [&](u32 g) { return chi(ta, g); },
+                [&](u32 i) { return chi(tb, i); });
+        });
+        return;
+    }
     level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
         wire_sums<GK, PH>(a, a.rowptr[x], a.rowptr[x + 1], sA, sC);
     });
@@ -1923,7 +1969,8 @@ constexpr u32 lds_words(u32 kind) {
            : kind == ST_FINISH ? SBLOCK
            : kind == ST_LINE   ? 64 * LINE_CHUNK
            : kind == ST_LFOLD  ? LFOLD_WORDS
-           : kind == ST_WA0 || kind == ST_WT0 || kind == ST_WT ? NWAVES * T_ROW
+           : kind == ST_WA0 ? NWAVES * T_ROW + 6 * EQ_THIRD
+           : kind == ST_WT0 || kind == ST_WT ? NWAVES * T_ROW
            : kind == ST_WTAIL || kind == ST_WSMALL || kind == ST_TOP ? TAIL_WORDS
            : kind == KALL ? (TAIL_WORDS > LFOLD_WORDS ? TAIL_WORDS : LFOLD_WORDS)
                           : 2;

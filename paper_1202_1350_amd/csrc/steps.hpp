@@ -270,6 +270,11 @@ struct SgeArgs {
 // wave each in the per-chunk sums), or a single big chunk of a heavy wire:
 // tile t holds chunks [tch[t], tch[t+1]).
 constexpr u32 TILE_POS = 64;
+// Widest point whose eq tables a level-0 step forms in LDS: thirds of at most
+// 2^7 entries.  Up to here an ST_EQ launch (4.2 us) costs more than the step's
+// own tables (about 1 us) and the further products; at 2^22 gates these cost
+// more than the launch.
+constexpr u32 EQ_THIRDS = 20, EQ_THIRD = 128;
 struct WaggArgs {
     u32 kind, ph;
     u32 nch;                 // chunks: sorted positions [cstart[ch], cstart[ch+1]) share one wire x
@@ -296,9 +301,14 @@ struct Wt0Args {
     u64 *A, *C;              // level-0 tables
 };
 // ST_WA0: wire x's gates sit at sorted positions [rowptr[x], rowptr[x+1])
-// (at most one chunk of gates per wire).
+// (at most one chunk of gates per wire).  eqL > 0: the step forms the eq
+// tables of a* (and b*, phase 2) itself, in LDS, as thirds of eqL coordinates
+// each (an entry weighs one entry of each third): a launch less, a product
+// more a point and gate than from the halves of an ST_EQ step.  The line:
+// EQ_THIRDS coordinates (see there).
 struct Wa0Args {
     u32 kind, ph, hasC, sum;
+    u32 eqL, s, sp, co;      // coordinates of a* and b*, challenge index of a* (b* follows)
     u64 nw;
     const u32 *perm, *rowptr;
     const u32 *oths;
