@@ -2350,7 +2350,9 @@ int enqueue_batch(BatchPlan &B, hipStream_t st, bool profile) {
         if (profile) prof_pair(PC_BATCH, B.l_bytes[t], &a, &b, B.l_mods[t]);
         HIP_TRY(launch_steps(st, B.d_jobs + B.l_off[t], B.l_njobs[t], B.l_blocks[t], a, b));
     }
-    HIP_TRY(launch_batch_gather(st, B.d_slots, n, B.d_out));
+    u64 most = 0;
+    for (u32 q = 0; q < n; q++) most = std::max<u64>(most, B.h_slots[q].n_msgs);
+    HIP_TRY(launch_batch_gather(st, B.d_slots, n, most, B.d_out));
     return GKR_OK;
 }
 

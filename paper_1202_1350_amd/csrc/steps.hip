@@ -2104,12 +2104,16 @@ __global__ void k_batch_setup(const BatchSlot *slots, u32 n) {
 
 // Transcripts (and range flags) of the batch into one contiguous buffer:
 // proof q's msgs at out[slots[q].out_off ...], its flag at out[slots[q].flag_off].
+// A workgroup copies GATHER words at a time, blockIdx.x the proof (one
+// workgroup a proof took 460 us for 6 MB).
+constexpr u32 GATHER = 2048;
 __global__ void k_batch_gather(const BatchSlot *slots, u32 n, u64 *out) {
-    const u32 q = blockIdx.x;
-    if (q >= n) return;
-    const BatchSlot &s = slots[q];
-    for (u64 k = threadIdx.x; k < s.n_msgs; k += blockDim.x) out[s.out_off + k] = s.msgs[k];
-    if (threadIdx.x == 0) out[s.flag_off] = s.state[4];
+    const BatchSlot &s = slots[blockIdx.x];
+    for (u64 k0 = (u64)blockIdx.y * GATHER; k0 < s.n_msgs; k0 += (u64)gridDim.y * GATHER) {
+        const u64 k1 = k0 + GATHER < s.n_msgs ? k0 + GATHER : s.n_msgs;
+        for (u64 k = k0 + threadIdx.x; k < k1; k += blockDim.x) out[s.out_off + k] = s.msgs[k];
+    }
+    if (blockIdx.y == 0 && threadIdx.x == 0) out[s.flag_off] = s.state[4];
 }
 
 hipError_t launch_batch_setup(hipStream_t st, const BatchSlot *slots, u32 n) {
@@ -2117,8 +2121,9 @@ hipError_t launch_batch_setup(hipStream_t st, const BatchSlot *slots, u32 n) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_gather(hipStream_t st, const BatchSlot *slots, u32 n, u64 *out) {
-    hipLaunchKernelGGL(k_batch_gather, dim3(n), dim3(256), 0, st, slots, n, out);
+hipError_t launch_batch_gather(hipStream_t st, const BatchSlot *slots, u32 n, u64 most_msgs, u64 *out) {
+    const u64 nb = (most_msgs + GATHER - 1) / GATHER;
+    hipLaunchKernelGGL(k_batch_gather, dim3(n, (u32)(nb < 1 ? 1 : nb > 1024 ? 1024 : nb)), dim3(256), 0, st, slots, n, out);
     return hipGetLastError();
 }
 

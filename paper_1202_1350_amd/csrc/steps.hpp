@@ -454,6 +454,7 @@ struct BatchSlot {
     u64 n_msgs, out_off, flag_off;
 };
 hipError_t launch_batch_setup(hipStream_t st, const BatchSlot *slots, u32 n);
-hipError_t launch_batch_gather(hipStream_t st, const BatchSlot *slots, u32 n, u64 *out);
+// most_msgs: the longest transcript.
+hipError_t launch_batch_gather(hipStream_t st, const BatchSlot *slots, u32 n, u64 most_msgs, u64 *out);
 
 }  // namespace gkr
