@@ -1057,17 +1057,19 @@ struct Planner {
         auto P_ = [&](u64 *p) -> u64 * { return w ? p : nullptr; };
         {
             const u64 Sd = c->S[d], npad = 1ull << c->s[d];
-            StepDesc &s = addg(ST_LOAD, npad, 4, Sd * 8.0 + npad * 8.0);
+            StepDesc &s = addg(ST_LOAD, npad, 1, Sd * 8.0 + npad * 8.0);
             s.u.load = LoadArgs{c->S[d], npad, V(d)};
         }
-        // circuit evaluation (a3), layer d-1 down to 0; the first K layers
+        // circuit evaluation (a3), a gate a thread by default: a layer is a chain
+        // of three dependent accesses, and 2^18 gates at four a thread (128
+        // workgroups) took 6.9 us, at one 3.6; layer d-1 down to 0, the first K layers
         // (run by ST_TOP, which evaluates them and starts the proof itself)
         // down to K
         const u32 K = top_layers(c);
         for (int i = (int)d - 1; i >= (int)K; i--) {
             const u64 S = c->S[i], npad = 1ull << c->s[i];
             eval_at[i] = (int)out.size();
-            StepDesc &s = addg(ST_EVAL, npad, 4,
+            StepDesc &s = addg(ST_EVAL, npad, 1,
                               S * (8.0 + 16 + 8 + (c->kind[i] == KIND_MIXED)) + (npad - S) * 8.0);
             mods.back() = c->kind[i] == KIND_ADD ? 0.0 : (double)S;  // one product a MUL gate
             s.u.eval = EvalArgs{(u32)c->kind[i], c->S[i], npad, soa_at(i, c->type[i]), soa_at(i, c->in1[i]),
