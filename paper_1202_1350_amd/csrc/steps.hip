@@ -1494,14 +1494,19 @@ __device__ __forceinline__ void step_ptail(const PtailArgs &a, const ProofPtrs &
 // products an entry, against one per entry and line point for the sums over
 // eq tables (ST_LT, ST_LINE), so wide layers take this path.  A thread folds
 // 2^tb entries in registers (tb coordinates, 1 <= tb <= 5); the workgroup's 512
-// polynomials of degree tb take 9 more coordinates in LDS, one coefficient
-// per work item, leaving Q_g of degree D = tb + 9 for the workgroup's block
-// g of 2^D entries.  Since h(t) = sum_g Q_g(t) prod_{k >= D} (g_{k-D} ?
-// l_k(t) : 1 - l_k(t)), the workgroup then evaluates its term at t = 2..s'
-// and writes it as a row (two rows: 16 values a row); ST_FINISH adds the
-// rows up.
-constexpr u32 LF_LDS = 9;  // coordinates folded in LDS (SBLOCK = 2^9 polynomials)
-static_assert((1 << LF_LDS) == SBLOCK, "a workgroup's threads hold 2^9 polynomials");
+// polynomials of degree tb lose six more coordinates in LDS, two a level, one
+// coefficient per work item; and the eight polynomials left, of degree
+// tb + 6, are evaluated at t = 2..s', an item per point and polynomial, and
+// weighted along every coordinate from tb + 6 on, prod_k (bit ? l_k(t) :
+// 1 - l_k(t)) (a row of 16 lanes forms a point's weights beside the second
+// and third level).  The workgroup's sums are written as a row (two rows: 16
+// values a row); ST_FINISH adds the rows up.
+// A workgroup's time is its chain of levels: nine levels of one coordinate,
+// Horner's rule and the weights one after another took 10.2 us a launch at
+// 2^17 entries, this takes 7.2 (27.1 -> 24.8 at 2^22, 73 -> 68 at 2^24).
+constexpr u32 LF_POLYS = 8;  // polynomials left after the levels in LDS
+constexpr u32 LF_LDS = 9;    // coordinates below a workgroup's in LDS: SBLOCK = 2^9 polynomials
+static_assert((1 << LF_LDS) == SBLOCK && (SBLOCK >> 6) == LF_POLYS, "512 polynomials, three levels of two coordinates");
 
 // The fold of a and b (degree D, in registers) into o (degree D + 1).
 template <int D>
@@ -1524,39 +1529,44 @@ __device__ __forceinline__ void fold_level_reg(const u64 (&p)[N][D + 1], u64 (&q
     for (int m = 0; m < N / 2; m++) fold_poly<D>(p[2 * m], p[2 * m + 1], bk, dk, q[m]);
 }
 
-// L fold levels in LDS: M polynomials of degree d at src (d + 1 words each,
-// one after another) along coordinates k .. k + L - 1, one work item per
-// output coefficient, between src and dst in turn; returns the buffer with
-// the M >> L polynomials of degree d + L.  Ends with the workgroup in step.
-__device__ __forceinline__ u64 *lds_fold(u64 *src, u64 *dst, u32 M, u32 d, u32 k, u32 L, const u64 *bk,
-                                         const u64 *dk) {
-    for (u32 l = 0; l < L; l++, d++, M >>= 1, k++) {
-        const u32 nc = d + 2, items = (M >> 1) * nc;
-        const u64 b = bk[k], dl = dk[k];
-        for (u32 it = threadIdx.x; it < items; it += SBLOCK) {
-            const u32 m = it / nc, j = it - m * nc;
-            const u64 *P0 = src + (2 * m) * (d + 1), *P1 = P0 + (d + 1);
-            const u64 a0 = j <= d ? P0[j] : 0;
-            const u64 Dj = j <= d ? diff_lz(P1[j], P0[j]) : 0;  // (< 2p: the sum stays below 2^125)
-            const u64 Dm = j >= 1 ? diff_lz(P1[j - 1], P0[j - 1]) : 0;
-            dst[it] = fp::red128((u128)a0 + fp::wide(b, Dj) + fp::wide(dl, Dm));  // (it = m nc + j)
+// Two coordinates of the 4M polynomials of degree d at src folded into M of
+// degree d + 2 at dst; coefficient j of polynomial m of n is word j n + m, so
+// a work item reads a coefficient of its four polynomials in two 16-byte
+// loads.  With l0, l1 the coordinates' lines, D0 = P1 - P0, D1 = P2 - P0 and
+// D01 = P3 - P2 - P1 + P0, the fold is P0 + l0 D0 + l1 D1 + l0 l1 D01; e holds
+// l0 l1's coefficients.
+template <u32 M>
+__device__ __forceinline__ void lds_fold2(const u64 *src, u64 *dst, u32 d, const u64 *b, const u64 *dl, const u64 *e) {
+    const u64 b0 = b[0], d0 = dl[0], b1 = b[1], d1 = dl[1], e0 = e[0], e1 = e[1], e2 = e[2];
+    for (u32 it = threadIdx.x; it < M * (d + 3); it += SBLOCK) {
+        const u32 j = it / M, m = it % M;
+        u64 p0 = 0, D0[2] = {0, 0}, D1[2] = {0, 0}, D01[3] = {0, 0, 0};
+#pragma unroll
+        for (u32 q = 0; q < 3; q++) {
+            if (j < q || j - q > d) continue;
+            const u64 *S = src + (j - q) * (4 * M) + 4 * m;
+            const u64x2 lo = ld2(S, 0), hi = ld2(S, 2);
+            if (q == 0) p0 = lo.x;
+            if (q < 2) {
+                D0[q] = diff_lz(lo.y, lo.x);  // (< 2p)
+                D1[q] = diff_lz(hi.x, lo.x);
+            }
+            D01[q] = (hi.y + lo.x) + (2 * P - hi.x - lo.y);  // (< 4p)
         }
-        __syncthreads();
-        u64 *t = src;
-        src = dst;
-        dst = t;
+        // below 2^61 + 4 2^123 + 3 2^124 < 2^127
+        dst[it] = fp::red128((u128)p0 + fp::wide(b0, D0[0]) + fp::wide(d0, D0[1]) + fp::wide(b1, D1[0]) +
+                             fp::wide(d1, D1[1]) + fp::wide(e0, D01[0]) + fp::wide(e1, D01[1]) + fp::wide(e2, D01[2]));
     }
-    return src;
 }
 
 // Register levels D .. TB-1 of N polynomials of degree D; the one left
-// (degree TB) goes to out.
+// (degree TB) goes to out, a coefficient every SBLOCK words.
 template <int N, int D, int TB>
 __device__ __forceinline__ void fold_regs(const u64 (&p)[N][D + 1], const u64 *bk, const u64 *dk, u64 *out) {
     if constexpr (D == TB) {
         static_assert(N == 1, "2^TB entries make one polynomial of degree TB");
 #pragma unroll
-        for (int j = 0; j <= TB; j++) out[j] = p[0][j];
+        for (int j = 0; j <= TB; j++) out[j * SBLOCK] = p[0][j];
     } else {
         u64 q[N / 2][D + 2];
         fold_level_reg<N, D>(p, q, bk[D], dk[D]);
@@ -1567,9 +1577,8 @@ __device__ __forceinline__ void fold_regs(const u64 (&p)[N][D + 1], const u64 *b
 template <int TB>
 __device__ __forceinline__ void lfold_body(const LfoldArgs &a, const Ctx &c, i32 draw) {
     constexpr int E = 1 << TB;  // entries a thread folds
-    u64 *tab = c.lds;
-    u64 *bk = tab, *dk = tab + 32;
-    u64 *buf0 = tab + 64, *buf1 = buf0 + SBLOCK * (TB + 1);  // 512 x (TB+1), then 256 x (TB+2) words
+    u64 *bk = c.lds, *dk = bk + 32, *ee = dk + 32, *wt = ee + 16;  // l_k = b_k + t d_k; products of pairs; weights
+    u64 *buf0 = wt + 32 * LF_POLYS, *buf1 = buf0 + SBLOCK * (TB + 1);  // 512 x (TB + 1), then 128 x (TB + 3) words
     const u32 tid = threadIdx.x;
     // the thread's entries (loaded before the line's coordinates are read)
     const u64 *src = a.V + ((u64)c.lb << (TB + LF_LDS)) + ((u64)tid << TB);
@@ -1587,22 +1596,45 @@ __device__ __forceinline__ void lfold_body(const LfoldArgs &a, const Ctx &c, i32
         dk[tid] = sub(cc, b);
     }
     __syncthreads();
-    fold_regs<E, 0, TB>(x, bk, dk, buf0 + tid * (TB + 1));
+    if (tid >= SBLOCK - 9) {  // coefficient i of l_k l_{k+1}, k = TB + 2 q
+        const u32 q = (SBLOCK - 1 - tid) / 3, i = (SBLOCK - 1 - tid) % 3, k = TB + 2 * q;
+        const u64 u = i == 2 ? dk[k] : bk[k], v = i ? dk[k + 1] : bk[k + 1];
+        ee[3 * q + i] = fp::red128(fp::wide(u, v) + (i == 1 ? fp::wide(dk[k], bk[k + 1]) : 0));
+    }
+    fold_regs<E, 0, TB>(x, bk, dk, buf0 + tid);
     __syncthreads();
-    constexpr u32 D = TB + LF_LDS;
-    const u64 *h = lds_fold(buf0, buf1, SBLOCK, TB, TB, LF_LDS, bk, dk);  // Q_g, degree D
-    // Q_g(t) times the weight of this workgroup's block along the remaining
-    // coordinates, prod_{k >= D} (g_{k-D} ? l_k(t) : 1 - l_k(t)), at t = 2..s'
-    if (tid + 2 <= a.sp) {
-        const u64 t = tid + 2;
-        u64 q = h[D];
+    lds_fold2<128>(buf0, buf1, TB, bk + TB, dk + TB, ee);
+    __syncthreads();
+    // Beside the second and third level, from the last row of lanes down: the
+    // row of point t = 2 + pt multiplies the factors of the workgroup's own
+    // bits, then each of its first eight lanes those of its polynomial's.
+    const u32 T = a.sp - 1, pt = (SBLOCK - 1 - tid) / 16, l16 = tid % 16;
+    constexpr u32 K8 = TB + 6, D = TB + LF_LDS;
+    const auto factor = [&](u32 k, u32 bit, u64 t) { return fp::eqbit(bit, add(bk[k], mul(t, dk[k]))); };
+    lds_fold2<32>(buf1, buf0, TB + 2, bk + TB + 2, dk + TB + 2, ee + 3);
+    u64 w = 1;
+    if (pt < T) {
+        for (u32 k = D + l16; k < a.sp; k += 16) w = mul(w, factor(k, (c.lb >> (k - D)) & 1, pt + 2));
+        w = row_product(w);
+    }
+    __syncthreads();
+    lds_fold2<LF_POLYS>(buf0, buf1, TB + 4, bk + TB + 4, dk + TB + 4, ee + 6);
+    if (pt < T && l16 < LF_POLYS) {
+        const u64 f = mul(factor(K8, l16 & 1, pt + 2), factor(K8 + 1, (l16 >> 1) & 1, pt + 2));
+        wt[pt * LF_POLYS + l16] = mul(mul(w, factor(K8 + 2, l16 >> 2, pt + 2)), f);
+    }
+    __syncthreads();
+    const u32 tp = tid / LF_POLYS, m = tid % LF_POLYS;
+    if (tp < T) {  // (whole octs of lanes)
+        u64 pw = 1;  // t^j <= 32^11
+        u128 v = 0;
 #pragma unroll
-        for (int j = D - 1; j >= 0; j--) q = add(mul(q, t), h[j]);
-        for (u32 k = D; k < a.sp; k++) {
-            const u64 l = add(bk[k], mul(t, dk[k]));
-            q = mul(q, (c.lb >> (k - D)) & 1 ? l : sub(1, l));
+        for (u32 j = 0; j <= K8; j++) {
+            v += fp::wide(buf1[j * LF_POLYS + m], pw);
+            pw *= tp + 2;
         }
-        a.rows[((u64)(tid / ROW_STRIDE) * c.nb + c.lb) * ROW_STRIDE + tid % ROW_STRIDE] = q;
+        const u64 h = reduced(oct_total(mul(fp::red128(v), wt[tid])));
+        if (m == 0) a.rows[((u64)(tp / ROW_STRIDE) * c.nb + c.lb) * ROW_STRIDE + tp % ROW_STRIDE] = h;
     }
 }
 
@@ -1962,7 +1994,7 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
 
 // LDS words of a kind's body (the kernel of mixed batches holds every kind's
 // code, and its LDS decides how many workgroups a CU takes).
-constexpr u32 TAIL_WORDS = 3 * TAIL_TAB + TAIL_EXTRA, LFOLD_WORDS = 64 + SBLOCK * 6 + SBLOCK / 2 * 7;
+constexpr u32 TAIL_WORDS = 3 * TAIL_TAB + TAIL_EXTRA, LFOLD_WORDS = 80 + 32 * LF_POLYS + SBLOCK * 6 + 128 * 8;
 constexpr u32 lds_words(u32 kind) {
     return kind == ST_P       ? 64 + NWAVES * 64
            : kind == ST_PTAIL ? PT_LDS
