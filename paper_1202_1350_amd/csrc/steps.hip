@@ -304,6 +304,153 @@ __device__ __forceinline__ void oct_row(OctSums &q, u64 *part, u64 *row) {
         row[threadIdx.x] = t;
     }
 }
+// LDS written before by this wave's lanes is read after (one wave's LDS
+// operations stay in order; this keeps the compiler's order).
+__device__ __forceinline__ void wave_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// Word of a row that holds the point (x, y, z), 2 for inf.
+__device__ __forceinline__ u32 point_word(u32 x, u32 y, u32 z) {
+    if (x < 2 && y < 2 && z < 2) return 4 * (x + 2 * y + 4 * z);
+    if (x == 2 && y < 2) return 4 * (z < 2 ? 2 * y + 4 * z : 1 + 2 * y) + 1;
+    if (x == 2 && z == 2) return 4 * 5 + 1;
+    if (y == 2 && z < 2) return 4 * (x < 2 ? x + 4 * z : 2 + 4 * z) + 2;
+    return 4 * (y == 2 ? x + 4 : x + 2 * y) + 3;
+}
+
+// The octs' sums on the matrix cores, for steps whose threads take several
+// entries.  Every one of the 27 sums is a combination of the 64 sums S_ij =
+// sum over the octs of A_i F_j, and with the entries written in eight signed
+// digits, v = sum_l d_l(v) 256^l with -128 <= d_l < 128, those are
+// combinations of the 64 x 64 sums of products of digits: one product of
+// bytes, contracted over the octs, exact in 32 bits for below 2^17 octs a
+// wave.  A wave collects 32 octs, four entries a lane (entry lane mod 8 of
+// octs lane / 8 + 8 u, u < 4), takes the bytes of its four entries apart by
+// digit and passes them through LDS to the lanes that own rows (digit l, entry
+// i): row l' 8 + i of the tile of digits 4 t + l'.  About 22 instructions an
+// entry against 180 of oct_add, but some 500 at a workgroup's end: a step of
+// fewer than four entries a thread stays with oct_add.  The level-0 step of a
+// layer of 2^22 gates 55 -> 44 us, of 2^24 wires 212 -> 172; the table steps
+// (ST_WT) gain nothing, near the rate of memory at such sizes.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+constexpr u32 GRAM_DIG = 68;               // LDS dwords a digit: 64 lanes, padded (reads without bank conflicts)
+constexpr u32 GRAM_WORDS = 8 * GRAM_DIG / 2;  // LDS words a wave
+struct Gram {
+    i32x16 acc[2][2];  // by tile of A's and F's digits
+    u64 c;             // sum of the lane's C entries, below 2^61 + 8
+};
+__device__ __forceinline__ bool gram_fits(u64 n, u64 stride) {  // (uniform)
+    return n >= 4 * stride && n <= (stride << 13);               // at most 2^16 octs a wave
+}
+// The lane's operands (both digit tiles) of its four entries v.
+__device__ __forceinline__ void gram_operand(u32 lane, const u64 (&v)[4], u32 *stage, i32x4 (&op)[2]) {
+    constexpr u64 H = 0x8080808080808080ull;
+    u32 lo[4], hi[4];
+#pragma unroll
+    for (u32 u = 0; u < 4; u++) {
+        const u64 d = (v[u] + H) ^ H;  // (v < 2^61: nothing is carried out of the top digit)
+        lo[u] = (u32)d;
+        hi[u] = (u32)(d >> 32);
+    }
+    auto put = [&](u32 l, const u32 (&x)[4]) {  // digits l .. l + 3, a dword of four octs each
+        const u32 a = __builtin_amdgcn_perm(x[1], x[0], 0x05010400), b = __builtin_amdgcn_perm(x[3], x[2], 0x05010400);
+        const u32 e = __builtin_amdgcn_perm(x[1], x[0], 0x07030602), f = __builtin_amdgcn_perm(x[3], x[2], 0x07030602);
+        u32 *o = stage + l * GRAM_DIG + (lane & 7) * 8 + (lane >> 3);
+        o[0] = __builtin_amdgcn_perm(b, a, 0x05040100);
+        o[GRAM_DIG] = __builtin_amdgcn_perm(b, a, 0x07060302);
+        o[2 * GRAM_DIG] = __builtin_amdgcn_perm(f, e, 0x05040100);
+        o[3 * GRAM_DIG] = __builtin_amdgcn_perm(f, e, 0x07060302);
+    };
+    put(0, lo);
+    put(4, hi);
+    wave_lds();
+#pragma unroll
+    for (u32 t = 0; t < 2; t++)
+        op[t] = *reinterpret_cast<const i32x4 *>(stage + (4 * t + (lane & 31) / 8) * GRAM_DIG + (lane & 7) * 8 +
+                                                 (lane >> 5) * 4);
+    wave_lds();
+}
+__device__ __forceinline__ void gram_add(u32 lane, const u64 (&A)[4], const u64 (&F)[4], u32 *stage, Gram &g) {
+    i32x4 a[2], f[2];
+    gram_operand(lane, A, stage, a);
+    gram_operand(lane, F, stage, f);
+#pragma unroll
+    for (u32 t = 0; t < 2; t++)
+#pragma unroll
+        for (u32 m = 0; m < 2; m++)
+            g.acc[t][m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t], f[m], g.acc[t][m], 0, 0, 0);
+}
+// The workgroup's row from its waves' sums; lds: GRAM_WORDS a wave.
+__device__ __forceinline__ void gram_row(const Gram &g, u64 *lds, u64 *row) {
+    const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    // Lane: column (digit m' of the tile, entry j of F), rows (digit l', entry
+    // i = 4 (lane / 32) + r of A) in word 4 l' + r.
+    const u32 sh = 8 * ((lane >> 3) & 3);
+    u64 s = 0;
+#pragma unroll
+    for (u32 r = 0; r < 4; r++) {
+        int64_t x[2][2];
+#pragma unroll
+        for (u32 t = 0; t < 2; t++)
+#pragma unroll
+            for (u32 m = 0; m < 2; m++) {
+                x[t][m] = g.acc[t][m][12 + r];
+#pragma unroll
+                for (int l = 2; l >= 0; l--) x[t][m] = x[t][m] * 256 + g.acc[t][m][4 * l + r];  // below 2^56
+            }
+        // (a multiple of p above 2^121 makes the sum positive)
+        const u64 v = fp::red128(((u128)P << 61) + (u128)x[0][0] + ((u128)(x[0][1] + x[1][0]) << 32) +
+                                 ((u128)x[1][1] << 64));
+        const u64 q = ((v << sh) & P) | (v >> (61 - sh));  // times 256^m'
+        const u64 tot = reduced(plus16(q + from8(q)));     // over m'
+        if (((lane >> 3) & 3) == r) s = tot;
+    }
+    const u64 c = reduced(plus32(plus16(reduced(g.c) + from8(reduced(g.c)))));
+    u64 *part = lds + w * GRAM_WORDS;
+    part[(4 * (lane >> 5) + ((lane >> 3) & 3)) * 8 + (lane & 7)] = s;  // S_ij
+    if (lane < 8) part[64 + lane] = c;
+    __syncthreads();
+    u64 *b0 = lds + 80, *b1 = b0 + 72;  // (past the first wave's part)
+    if (threadIdx.x < 72) {
+        u64 t = 0;
+#pragma unroll
+        for (u32 k = 0; k < NWAVES; k++) t = add(t, lds[k * GRAM_WORDS + threadIdx.x]);
+        b0[threadIdx.x] = t;
+    }
+    __syncthreads();
+    if (w) return;
+    // One variable after another: its bits (i, j) = (0, 0), (1, 1) give the
+    // points 0 and 1, (1 - 0)(1 - 0) the point inf.
+    u64 *src = b0, *dst = b1;
+#pragma unroll
+    for (u32 v = 0; v < 3; v++) {
+        const u32 np = v == 0 ? 1 : (v == 1 ? 3 : 9), nb = 4 >> v;  // points so far; entries left a side
+        const u32 rest = lane % (nb * nb), pd = lane / (nb * nb);
+        u64 x = 0;
+        if (pd < 3 * np) {
+            const u32 p = pd % np, d = pd / np;
+            const u64 *S = src + p * 4 * nb * nb + (rest / nb) * 4 * nb + 2 * (rest % nb);
+            const u64 s00 = S[0], s01 = S[1], s10 = S[2 * nb], s11 = S[2 * nb + 1];
+            x = d == 0 ? s00 : (d == 1 ? s11 : sub(add(s00, s11), add(s01, s10)));
+        }
+        wave_lds();
+        dst[lane] = x;
+        wave_lds();
+        u64 *t = src;
+        src = dst;
+        dst = t;
+    }
+    // points (x, y, z) in src[x + 3 y + 9 z]
+    const u32 x = lane % 3, y = (lane / 3) % 3, z = lane / 9;
+    const u64 val = add(src[lane], x < 2 && y < 2 && z < 2 ? b0[64 + x + 2 * y + 4 * z] : 0);
+    if (lane < T_ROW) dst[lane] = 0;
+    wave_lds();
+    if (lane < 27) dst[point_word(x, y, z)] = val;
+    wave_lds();
+    if (lane < T_ROW) row[lane] = dst[lane];
+}
 // Message k of the three rounds from the octs' sums E (T_ROW words, LDS): lane
 // x + 3 y + 9 z holds the point (x, y, z), 2 for inf.  The rounds before k are
 // bound (a quadratic is q0 (1 - r) + q1 r + qinf (r^2 - r)), those after it
@@ -312,18 +459,7 @@ __device__ __forceinline__ void t_message(const u64 *E, u32 k, const u64 *r, u64
     const u32 lane = threadIdx.x & 63;
     const u32 d[3] = {lane % 3, (lane / 3) % 3, lane / 9};
     const u32 x = d[0], y = d[1], z = d[2];
-    u32 at;
-    if (x < 2 && y < 2 && z < 2)
-        at = 4 * (x + 2 * y + 4 * z);
-    else if (x == 2 && y < 2)
-        at = 4 * (z < 2 ? 2 * y + 4 * z : 1 + 2 * y) + 1;
-    else if (x == 2 && z == 2)
-        at = 4 * 5 + 1;
-    else if (y == 2 && z < 2)
-        at = 4 * (x < 2 ? x + 4 * z : 2 + 4 * z) + 2;
-    else
-        at = 4 * (y == 2 ? x + 4 : x + 2 * y) + 3;
-    u64 v = lane < 27 ? E[at] : 0;
+    u64 v = lane < 27 ? E[point_word(x, y, z)] : 0;
 #pragma unroll
     for (u32 i = 0; i < 3; i++) {
         if (i < k) {  // (uniform)
@@ -956,15 +1092,14 @@ __device__ __forceinline__ void level0(u32 ph, u64 v1, u64 sA, u64 sC, u64 &A, u
 // and hasC).
 template <int GK, int PH, typename Wire>
 __device__ __forceinline__ void level0_round(u32 ph_rt, u32 hasC_rt, u32 sum, u64 nw, const u64 *F, u64 *At, u64 *Ct,
-                                             const ProofPtrs &pp, const Ctx &c, u64 *row, Wire wire) {
+                                             const ProofPtrs &pp, const Ctx &c, u64 *row, u64 *stage, Wire wire) {
     const u32 ph = PH > 0 ? (u32)PH : ph_rt;
     const bool hasC = GK >= 0 ? GK != 1 : hasC_rt != 0;
     const u64 v1 = ph == 2 ? pp.state[1] : 0;
     const u32 lane = threadIdx.x & 63;
-    OctSums q;
-    for (u64 x = c.gtid; x < nw; x += c.gstride) {
-        const u64 f = F[x];
-        u64 sA, sC, A, C;
+    auto entry = [&](u64 x, u64 &A, u64 &C, u64 &f) {
+        f = F[x];
+        u64 sA, sC;
         wire(x, sA, sC);
         if (GK == 1 && ph == 2) {  // MUL gates only: sA is zero
             A = mul(v1, sC);
@@ -975,6 +1110,28 @@ __device__ __forceinline__ void level0_round(u32 ph_rt, u32 hasC_rt, u32 sum, u6
         if (!hasC) C = 0;
         At[x] = A;
         if (hasC) Ct[x] = C;
+    };
+    if (GK >= 0 && sum && gram_fits(nw, c.gstride)) {  // (uniform)
+        u32 *st = reinterpret_cast<u32 *>(stage + (threadIdx.x >> 6) * GRAM_WORDS);
+        Gram g = {};
+        for (u64 b = c.gtid - lane; b < nw; b += 4 * c.gstride) {  // (whole waves)
+            u64 A[4] = {0, 0, 0, 0}, f[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (u32 u = 0; u < 4; u++) {
+                const u64 x = b + u * c.gstride + lane;
+                u64 C = 0;
+                if (x < nw) entry(x, A[u], C, f[u]);
+                if (hasC) g.c = fp::fold64(g.c + C);
+            }
+            gram_add(lane, A, f, st, g);
+        }
+        gram_row(g, stage, row);
+        return;
+    }
+    OctSums q;
+    for (u64 x = c.gtid; x < nw; x += c.gstride) {
+        u64 A, C, f;
+        entry(x, A, C, f);
         if (sum) oct_add(lane, A, C, f, q);  // (uniform)
     }
     if (sum) oct_row(q, c.lds, row);
@@ -1061,6 +1218,7 @@ static_assert(EQ_THIRD == 1 << 7 && EQ_THIRDS <= 3 * 7, "thirds of at most 7 coo
 // GK, PH: the gate mix and phase, compile-time (one kernel each) or -1, 0.
 template <int GK, int PH>
 __device__ __forceinline__ void step_wa0(const Wa0Args &a, const ProofPtrs &pp, const Ctx &c, u64 *row) {
+    u64 *stage = c.lds + NWAVES * T_ROW + 6 * EQ_THIRD;
     if (a.eqL) {  // (uniform)
         const u32 ph = PH > 0 ? (u32)PH : a.ph, L = a.eqL, m = (1u << L) - 1;
         u64 *ta = c.lds + NWAVES * T_ROW, *tb = ta + 3 * EQ_THIRD;
@@ -1075,14 +1233,14 @@ __device__ __forceinline__ void step_wa0(const Wa0Args &a, const ProofPtrs &pp, 
         auto chi = [&](const u64 *t, u32 x) {
             return mul(mul(t[x & m], t[EQ_THIRD + ((x >> L) & m)]), t[2 * EQ_THIRD + (x >> (2 * L))]);
         };
-        level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
+        level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, stage, [&](u64 x, u64 &sA, u64 &sC) {
             wire_sums_of<GK, PH>(
                 a, a.rowptr[x], a.rowptr[x + 1], sA, sC, [&](u32 g) { return chi(ta, g); },
                 [&](u32 i) { return chi(tb, i); });
         });
         return;
     }
-    level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, [&](u64 x, u64 &sA, u64 &sC) {
+    level0_round<GK, PH>(a.ph, a.hasC, a.sum, a.nw, a.Vn, a.A, a.C, pp, c, row, stage, [&](u64 x, u64 &sA, u64 &sC) {
         wire_sums<GK, PH>(a, a.rowptr[x], a.rowptr[x + 1], sA, sC);
     });
 }
@@ -2001,7 +2159,7 @@ constexpr u32 lds_words(u32 kind) {
            : kind == ST_FINISH ? SBLOCK
            : kind == ST_LINE   ? 64 * LINE_CHUNK
            : kind == ST_LFOLD  ? LFOLD_WORDS
-           : kind == ST_WA0 ? NWAVES * T_ROW + 6 * EQ_THIRD
+           : kind == ST_WA0 ? NWAVES * T_ROW + 6 * EQ_THIRD + NWAVES * GRAM_WORDS
            : kind == ST_WT0 || kind == ST_WT ? NWAVES * T_ROW
            : kind == ST_WTAIL || kind == ST_WSMALL || kind == ST_TOP ? TAIL_WORDS
            : kind == KALL ? (TAIL_WORDS > LFOLD_WORDS ? TAIL_WORDS : LFOLD_WORDS)
