@@ -36,6 +36,18 @@ __device__ __forceinline__ u64 plus32(u64 v) {
     const u32x2 b = __builtin_amdgcn_permlane32_swap((u32)(v >> 32), (u32)(v >> 32), false, false);
     return (((u64)b.x << 32) | a.x) + (((u64)b.y << 32) | a.y);
 }
+// The sum over lanes l and l ^ 32 (l ^ 16) of a in the lanes with that bit clear,
+// of b in the others; not reduced.
+__device__ __forceinline__ u64 swap32_sum(u64 a, u64 b) {
+    const u32x2 x = __builtin_amdgcn_permlane32_swap((u32)a, (u32)b, false, false);
+    const u32x2 y = __builtin_amdgcn_permlane32_swap((u32)(a >> 32), (u32)(b >> 32), false, false);
+    return (((u64)y.x << 32) | x.x) + (((u64)y.y << 32) | x.y);
+}
+__device__ __forceinline__ u64 swap16_sum(u64 a, u64 b) {
+    const u32x2 x = __builtin_amdgcn_permlane16_swap((u32)a, (u32)b, false, false);
+    const u32x2 y = __builtin_amdgcn_permlane16_swap((u32)(a >> 32), (u32)(b >> 32), false, false);
+    return (((u64)y.x << 32) | x.x) + (((u64)y.y << 32) | x.y);
+}
 
 // A value every lane holds the same copy of, moved to scalar registers.
 __device__ __forceinline__ u64 uniform(u64 v) {

@@ -283,25 +283,27 @@ __device__ __forceinline__ void oct_add(u32 lane, u64 A, u64 C, u64 F, OctSums &
     for (int k = 0; k < 3; k++) q.acc[k + 1] += fp::wide(a[k], f[k]);
     if (++q.terms == 8) oct_flush(q);
 }
-// The wave's sums into out[4 j + k]: lanes of equal j = lane mod 8 added.
+// The wave's sums into out[4 j + k]: lanes of equal j = lane mod 8 added, the
+// slots spread over the lanes on the way (an exchange of two slots leaves one
+// sum of each in either half): a narrow step ends with this, and runs each of
+// its instructions once; summing every slot in every lane made the steps 0.6
+// (ST_WT) and 1.1 us (ST_WA0) longer at 2^17 wires.
 __device__ __forceinline__ void oct_wave(OctSums &q, u64 *out) {
     const u32 lane = threadIdx.x & 63;
     oct_flush(q);
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const u64 v = reduced(plus32(plus16(q.s[k] + from8(q.s[k]))));  // (eight values below p)
-        if (lane < 8) out[4 * lane + k] = v;
-    }
+    const u64 v = swap16_sum(swap32_sum(q.s[0], q.s[1]), swap32_sum(q.s[2], q.s[3]));  // (four values below p)
+    const u64 t = reduced(v + from8(v));
+    if (!(lane & 8)) out[4 * (lane & 7) + ((lane >> 4) & 1) * 2 + (lane >> 5)] = t;
 }
 // A grid step's row.
 __device__ __forceinline__ void oct_row(OctSums &q, u64 *part, u64 *row) {
     oct_wave(q, part + (threadIdx.x >> 6) * T_ROW);
     __syncthreads();
     if (threadIdx.x < T_ROW) {
-        u64 t = 0;
+        u64 t = 0;  // (eight values below p)
 #pragma unroll
-        for (int w = 0; w < NWAVES; w++) t = add(t, part[w * T_ROW + threadIdx.x]);
-        row[threadIdx.x] = t;
+        for (int w = 0; w < NWAVES; w++) t += part[w * T_ROW + threadIdx.x];
+        row[threadIdx.x] = reduced(t);
     }
 }
 // LDS written before by this wave's lanes is read after (one wave's LDS
