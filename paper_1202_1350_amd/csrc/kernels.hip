@@ -1,12 +1,10 @@
-// kernels.hip -- HIP kernels (gfx950) of the GKR prover's per-layer
-// sum-check over F_p, p = 2^61 - 1, and of its verifier.
+// kernels.hip -- HIP kernels (gfx950) of the GKR verifier over F_p, p =
+// 2^61 - 1: the wiring predicates at a point and the inputs' extension.
 //
-// Sec. 4.1.1: each gate contributes independently to the prover's message;
-// a workgroup sums its gates' contributions (wave64 shuffles, then LDS),
-// writes one row of partial sums, and a one-workgroup *_final kernel folds
-// the rows, writes the message and only then draws the next challenge on
-// the device.  All arithmetic is exact modular integer arithmetic (no
-// floating point, Sec. 6.1), so any summation order gives identical bits.
+// A workgroup sums its share (wave64 shuffles, then LDS) into one row of
+// partial sums, which the host adds up.  All arithmetic is exact modular
+// integer arithmetic (no floating point, Sec. 6.1), so any summation order
+// gives identical bits.
 #include <algorithm>
 
 #include "fp61.hpp"

@@ -1,10 +1,8 @@
-// kernels.hpp -- launchers of the GKR / sum-check kernels (kernels.hip).
+// kernels.hpp -- launchers of the verifier's kernels (kernels.hip).
 //
 // Every launcher enqueues on `st` and returns the launch status; none of
 // them synchronises.  Device pointers only.  Reductions write one row of
-// partial sums per workgroup into `partials`; a *_final kernel (one
-// workgroup) folds the rows, writes the round message into the transcript,
-// and only then draws the next challenge.
+// partial sums per workgroup; the host adds the rows.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

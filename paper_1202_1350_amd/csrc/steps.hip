@@ -2,7 +2,8 @@
 //
 // Sec. 4.1.1 of the paper: every gate (or table entry) contributes
 // independently to the prover's message, so a step is a grid-stride pass in
-// which each workgroup sums its share (wave64 shuffles, then LDS) into one
+// which each workgroup sums its share (exchanges within a wave, matrix
+// products of digits where a thread has several entries, then LDS) into one
 // row of partial sums.  All arithmetic is exact in F_p (Sec. 6.1), so the
 // result does not depend on the summation order.
 #include <hip/hip_ext.h>
@@ -1531,7 +1532,7 @@ __device__ __forceinline__ void step_wsmall(const WsmallArgs &a, const ProofPtrs
 // ST_FINISH forms the messages from them.  Lane off + k of every wave holds
 // z of round k in zl and receives its challenge in rl; st becomes the state
 // after them.  lds: PT_LDS words.  A round at a time (sums, barrier, fold,
-// barrier, ten times) took 13.9 us a tail; this takes 5.
+// barrier, ten times) took 13.9 us a tail; this takes 6.5.
 constexpr u32 PT_LDS = 32 * (3 + NWAVES);
 __device__ __forceinline__ void ptail_rounds(const u64 (&v)[2], u32 L, u32 off, u64 zl, u64 &rl, u64 &st, u64 *cols,
                                              u64 *lds) {

@@ -2,11 +2,12 @@
 //
 // A proof is a fixed sequence of steps (evaluation of each layer, the
 // circuit's first small layers whole in one step that also evaluates them,
-// then per layer: the eq table of z, the p-phase rounds, the eq table of
-// a*, the two omega-phases, the eq table of b*, and the line: V_{i+1}
-// folded along it for layers of 2^11..2^22 entries, else the line points'
-// eq tables and the line sums).  Most steps are one grid pass; a step that
-// ends a sum-check round leaves one row of partial sums per workgroup.
+// then per layer: the p-phase, several rounds a step; the two omega phases,
+// three rounds a step, after the eq tables of a* and b* where the level-0
+// steps do not form them; and the line: V_{i+1} folded along it for layers of
+// 2^11 entries and more, else the line points' eq tables and the line sums).
+// Most steps are one grid pass; a step that ends sum-check rounds leaves one
+// row of partial sums per workgroup.
 //
 // Every workgroup of the next step draws the round's challenge from the
 // same SplitMix64 state (the verifier's coins do not depend on the
@@ -16,8 +17,8 @@
 // Folding the rows into the message values is needed by nothing but the
 // transcript, so every reducing step keeps rows of its own and one last
 // step, ST_FINISH, folds all of them at once, one workgroup per message.
-// The challenge of round j is drawn only in a launch that starts after the
-// launch computing message j's sums has completed.
+// The challenge of round j is used only after message j's sums are complete:
+// in a later launch, or past a barrier of the one workgroup that ends a phase.
 //
 // One launch runs one step of each of several proofs (a job table maps
 // workgroups to (proof, step)); a single proof is the one-job case.
