@@ -618,56 +618,62 @@ __device__ __forceinline__ void step_eq(const EqArgs &a, const Ctx &c, const u64
 // x1 - x0 + p, not reduced (canonical x0, x1: below 2 p).
 __device__ __forceinline__ u64 diff_lz(u64 x1, u64 x0) { return x1 + (fp::P - x0); }
 
-// x mod p as red128 computes it, without the final subtraction: a value
-// below p + 4 that is congruent to x.
-__device__ __forceinline__ u64 red128_lz(u128 x) {
-    const u64 lo = (u64)x, hi = (u64)(x >> 64);
-    u64 s = (lo & fp::P) + (lo >> 61) + ((hi << 3) & fp::P) + (hi >> 58);  // < 2^63
-    return (s & fp::P) + (s >> 61);
-}
-
-// Two-round steps give each quad (four consecutive entries of the level
-// they sum over) to four adjacent lanes: lane j of the quad holds entry j,
-// loads and stores stay coalesced, the quad's values are exchanged with DPP
-// quad permutes and the quad's products are split over its lanes.
-
 // p-phase grid steps (see PArgs).  zp: z_i in LDS (first step) or memory.
 // FIRST: whether this is the phase's first step, compile-time (1, 0; one
 // kernel each) or -1 to take a.pend.
 //
 // First step: bound by the read of V_i and one product an entry.  A thread
 // keeps its place in the SBLOCK-entry runs, so its entry's weight is one
-// scalar a run times a factor of its own, applied once at the end.
-__device__ __forceinline__ void step_p_first(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row) {
+// scalar a run times a factor of its own, applied once at the end.  A narrow
+// one is the chain of its loads: the first runs' values and the line's points
+// are asked for before the wait for the challenge state, and a run's weight is
+// a product over lanes (6.4 -> 5.4 us at 2^17 entries).
+struct Runs {  // a thread's values in its workgroup's next four runs
+    u64 v[4];
+};
+__device__ __forceinline__ Runs load_runs(const PArgs &a, const Ctx &c, u64 q0, u32 n) {
+    const u64 *src = a.Vsrc + q0 * SBLOCK + threadIdx.x;
+    Runs r;
+#pragma unroll
+    for (u32 i = 0; i < 4; i++) r.v[i] = i < n ? src[(u64)i * c.nb * SBLOCK] : 0;
+    return r;
+}
+__device__ __forceinline__ u32 runs_from(const PArgs &a, const Ctx &c, u64 q0) {  // 0 .. 64
+    if (q0 >= a.nu) return 0;
+    const u64 left = (a.nu - q0 + c.nb - 1) / c.nb;
+    return left < 64 ? (u32)left : 64;
+}
+// x: the first runs' values (under way since before the prologue's wait).
+__device__ __forceinline__ void step_p_first(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row, Runs x) {
     u64 *s_w = c.lds, (*s_sum)[64] = reinterpret_cast<u64 (*)[64]>(s_w + 64);
     constexpr u32 LB = 9;
     static_assert((1 << LB) == SBLOCK, "SBLOCK");
     const u32 tid = threadIdx.x, lane = tid & 63, R = a.R;
+    u64 own = 1;  // the weight of the thread's place in a run
+    for (u32 k = R; k < LB; k++) own = mul(own, fp::eqbit((tid >> k) & 1, zp[k]));
     u64 t = 0;
     for (u64 q0 = c.lb; q0 < a.nu; q0 += 64ull * c.nb) {  // 64 runs of this workgroup at a time
-        if (tid < 64) {
-            const u64 q = q0 + (u64)tid * c.nb;
+        const u32 n = runs_from(a, c, q0);
+        if (q0 != c.lb) x = load_runs(a, c, q0, n);
+        // their weights: a row of 16 lanes a run, a coordinate a lane
+        for (u32 i = tid >> 4; i < n; i += SBLOCK / 16) {
+            const u64 q = q0 + (u64)i * c.nb;
             u64 w = 1;
-            if (q < a.nu)
-                for (u32 k = LB; k < a.s; k++) w = mul(w, fp::eqbit((u32)(q >> (k - LB)) & 1, zp[k]));
-            s_w[tid] = w;
+            for (u32 k = LB + (tid & 15); k < a.s; k += 16) w = mul(w, fp::eqbit((u32)(q >> (k - LB)) & 1, zp[k]));
+            s_w[i] = row_product(w);
         }
         __syncthreads();
-        const u64 left = (a.nu - q0 + c.nb - 1) / c.nb;
-        const u32 n = left < 64 ? (u32)left : 64;
-        const u64 *src = a.Vsrc + q0 * SBLOCK + tid;
         u128 acc = 0;
         for (u32 i0 = 0; i0 < n; i0 += 4) {
-            u64 v[4];
+            if (i0) x = load_runs(a, c, q0 + (u64)i0 * c.nb, n - i0);
 #pragma unroll
-            for (u32 i = 0; i < 4; i++) v[i] = i0 + i < n ? src[(u64)(i0 + i) * c.nb * SBLOCK] : 0;
-#pragma unroll
-            for (u32 i = 0; i < 4; i++) acc += fp::wide(s_w[(i0 + i) & 63], v[i]);  // (up to 64 products below 2^122)
+            for (u32 i = 0; i < 4; i++)  // (up to 64 products below 2^122)
+                if (i0 + i < n) acc += fp::wide(s_w[i0 + i], x.v[i]);
         }
         t = add(t, fp::red128(acc));
         __syncthreads();  // s_w is read
     }
-    for (u32 k = R; k < LB; k++) t = mul(t, fp::eqbit((tid >> k) & 1, zp[k]));
+    t = mul(t, own);
     // threads of equal column tid mod 2^R, over the wave and the waves
     for (u32 b = R; b < 6; b++) t = plus_bit(t, b);
     s_sum[tid >> 6][lane] = t;
@@ -753,9 +759,9 @@ __device__ __forceinline__ void step_p_next(const PArgs &a, const Ctx &c, const 
 }
 
 template <int FIRST, typename Draw>
-__device__ __forceinline__ void step_p(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row, Draw draw) {
+__device__ __forceinline__ void step_p(const PArgs &a, const Ctx &c, const u64 *zp, u64 *row, Draw draw, Runs x) {
     if (FIRST == 1 || (FIRST < 0 && a.pend == 0))
-        step_p_first(a, c, zp, row);
+        step_p_first(a, c, zp, row, FIRST == 1 ? x : load_runs(a, c, c.lb, runs_from(a, c, c.lb)));
     else
         step_p_next(a, c, zp, row, draw);
 }
@@ -2067,16 +2073,25 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
     const bool own_fin = tail && (f.kind == FIN_P || f.kind == FIN_T);
     const bool pfirst = (KIND == ST_P || KIND == KALL) && kind == ST_P && sd.u.p.pend == 0;
     const bool late = own_fin || (((kind == ST_P && !pfirst) || kind == ST_WT) && !fin_block);
+    const bool line_fin = (fin_mask(KIND) & (1u << FIN_LINE)) && f.kind == FIN_LINE;
+    u64 bb = 0, cc = 0;
+    auto line_points = [&]() {
+        if (line_fin && threadIdx.x < f.sp) {
+            bb = f.bstar[threadIdx.x];
+            cc = f.cstar[threadIdx.x];
+        }
+    };
+    if (KIND != KALL) line_points();  // (the kernel of every kind would spill more)
+    Runs px = {};
+    if (KIND == ST_P && GK == 1 && !fin_block) px = load_runs(sd.u.p, c, lb, runs_from(sd.u.p, c, lb));
     if (!late) draw();
     TailIn ti = {st_after, f.draw >= 0 ? 1u : 0u};
     // points assembled in LDS (challenges drawn by earlier launches are in
     // chals; the one drawn just now is c.r)
-    const bool line_fin = (fin_mask(KIND) & (1u << FIN_LINE)) && f.kind == FIN_LINE;
     if (line_fin || kind == ST_EQ || kind == ST_LT || pfirst) {  // (uniform)
-        if (line_fin && threadIdx.x < f.sp) {
-            const u64 bb = f.bstar[threadIdx.x], cc = f.cstar[threadIdx.x];
+        if (KIND == KALL) line_points();
+        if (line_fin && threadIdx.x < f.sp)
             s_pt[threadIdx.x] = add(bb, mul(c.r, sub(cc, bb)));  // z_{i+1} = l(tau)
-        }
         if (pfirst && !line_fin && threadIdx.x < sd.u.p.s)
             s_pt[threadIdx.x] = pp.zbuf[threadIdx.x];  // z of the layer, already recorded
         if (kind == ST_EQ && threadIdx.x < sd.u.eq.n) {
@@ -2111,7 +2126,7 @@ __device__ __forceinline__ void run_step(const StepDesc &sd, u32 lb, u64 *lds) {
             break;
         case ST_P:
             step_p<KIND == ST_P ? GK : -1>(sd.u.p, c, pfirst ? s_pt : pp.zbuf,
-                                           sd.rows + ((u64)c.lb << sd.u.p.R), draw);
+                                           sd.rows + ((u64)c.lb << sd.u.p.R), draw, px);
             break;
         case ST_W: {
             const WArgs &a = sd.u.w;
