@@ -87,10 +87,18 @@ __device__ __forceinline__ Weights fold_weights(const u64 (&r)[3]) {
     return q;
 }
 
+// Four counts in one 16-byte load; the caller's vector may start at any count,
+// so nothing beyond 4-byte alignment is promised (the load is the same
+// instruction either way).
+__device__ __forceinline__ uint4 counts4(const u32 *p) {
+    uint4 v;
+    __builtin_memcpy(&v, p, sizeof v);
+    return v;
+}
+
 // Entry g of a level from the eight entries below it.
 __device__ __forceinline__ u64 fold8(const u32 *src, u64 g, const Weights &q) {
-    const uint4 a = *reinterpret_cast<const uint4 *>(src + OCT * g);
-    const uint4 b = *reinterpret_cast<const uint4 *>(src + OCT * g + 4);
+    const uint4 a = counts4(src + OCT * g), b = counts4(src + OCT * g + 4);
     return fp::red128(fp::wide(q.w[0], a.x) + fp::wide(q.w[1], a.y) + fp::wide(q.w[2], a.z) + fp::wide(q.w[3], a.w) +
                       fp::wide(q.w[4], b.x) + fp::wide(q.w[5], b.y) + fp::wide(q.w[6], b.z) + fp::wide(q.w[7], b.w));
 }
@@ -228,11 +236,11 @@ __global__ void __launch_bounds__(FB) k_f2sc_first(const F2scPass a, u64 nq, con
     for (; q + (U - 1) * stride < nq; q += U * stride) {
         uint4 v[U];
 #pragma unroll
-        for (u32 i = 0; i < U; i++) v[i] = *reinterpret_cast<const uint4 *>(src + 4 * (q + i * stride));
+        for (u32 i = 0; i < U; i++) v[i] = counts4(src + 4 * (q + i * stride));
 #pragma unroll
         for (u32 i = 0; i < U; i++) oct_half(v[i]);
     }
-    for (; q < nq; q += stride) oct_half(*reinterpret_cast<const uint4 *>(src + 4 * q));
+    for (; q < nq; q += stride) oct_half(counts4(src + 4 * q));
     // sums over the lanes with equal h, into the row's slots
     __shared__ u64 part[FW][F2SC_ROW];
     const u32 lane = threadIdx.x & 63, wid = threadIdx.x >> 6;

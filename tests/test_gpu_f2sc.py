@@ -71,3 +71,21 @@ def test_full_values_where_the_passes_change(logn):
     want_m, want_c = O.f2sc_prove(a, 60 + logn)
     got_m, got_c = G().f2_sumcheck_prove(device_tensor(a), 60 + logn)
     assert np.array_equal(got_m, want_m) and np.array_equal(got_c, want_c)
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("logn", [0, 2, 3, 9, 13, 18])
+def test_vectors_starting_at_any_count(logn, offset):
+    """Device vectors that are views into a larger one, 4, 8 or 12 bytes past a
+    16-byte boundary: read by the tail alone, by the first pass, by the pass
+    that folds the counts.  Exact, with and without allocation."""
+    n = 1 << logn
+    a = (W.splitmix64(logn, 3, n) >> np.uint64(32)).astype(np.uint32)
+    around = np.full(8, 0xFFFFFFFF, np.uint32)
+    t = device_tensor(np.concatenate([around[:offset], a, around]))[offset:offset + n]
+    assert t.data_ptr() % 16 == 4 * offset
+    say("f2sc view logn", logn, "offset", offset)
+    want_m, want_c = O.f2sc_prove(a, 80 + logn)
+    for prove in (G().f2_sumcheck_prove, G().f2_sumcheck_prove_noalloc):
+        got_m, got_c = prove(t, 80 + logn)
+        assert np.array_equal(got_m, want_m) and np.array_equal(got_c, want_c)
