@@ -127,9 +127,9 @@ int gkr_circuit_set_algorithm(gkr_circuit *c, int omega_algo);
  *                     and round tables all live in pinned host memory and
  *                     every round's kernels read and write them in place
  *                     through the host link, so each message moves its
- *                     layer's data again; the device holds only the small
- *                     per-proof state (eq half tables, partial rows,
- *                     transcript, step program).
+ *                     layer's data again (partial rows included); the
+ *                     device holds only the small per-proof state (eq half
+ *                     tables, transcript, step program).
  *   GKR_MEM_AUTO      the first of the three whose device bytes fit.
  * Transcripts do not depend on the mode.  Proofs in GKR_MEM_LAYER are
  * launched one by one (no graph replay) and cannot be batched; a server
@@ -208,9 +208,9 @@ int gkr_verify_closed_forms(int enable);
 
 /* Launch shapes.  A grid step over U work items (gates, wires, table
  * entries or quads of them) launches ceil(U / (512 q)) workgroups of 512
- * threads, at most `cap`, where q (items per thread: 1, 2, 4, 8) and cap
- * (256, 512, 1024, 2048) are chosen per step kind and size class (ceil
- * log2 U).  gkr_autotune proves each of the n circuits (inputs as in
+ * threads, at most `cap` (and at most 512 where the step sums three omega
+ * rounds), where q (items per thread: 1, 2, 4, 8) and cap (256, 512, 1024,
+ * 2048) are chosen per step kind and size class (ceil log2 U).  gkr_autotune proves each of the n circuits (inputs as in
  * gkr_prove, seeds 1..reps) under each of the 16 shapes, timing every grid
  * launch with events (one warm-up proof per shape), and keeps for each
  * (kind, class) met the fastest shape; plans made afterwards, including

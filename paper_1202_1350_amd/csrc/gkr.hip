@@ -264,7 +264,6 @@ struct Arena {
     }
 };
 
-constexpr u32 HALF_MAX = 1u << 16;  // eq half tables: at most 2^16 entries
 // Up to this many gates an omega round folds its table itself (two extra
 // products per gate) instead of a separate fold step.
 constexpr u32 INLINE_FOLD_MAX_GATES = 1u << 19;
@@ -290,7 +289,14 @@ void line_shape(u32 sp, u32 *L, u32 *M, u32 *H) {
 // above the largest one measured for its kind takes that one's shape, the
 // other classes it has not measured keep their defaults.  A shape code packs
 // log2 q (bits 0-1) and log2 cap - 8 (bits 2-3): 16 candidates.
+// Steps that leave an oct's sums take at most SMAX_BLOCKS workgroups whatever
+// the shape says: their rows are twice as long as the others', every row is
+// kept until the proof ends, and no tuning of theirs chose more (the caps of
+// 2048 it lists are of classes with fewer workgroups).
 constexpr u32 CAP_MAX = 2048;
+constexpr u32 cap_max(u32 kind) {
+    return kind == ST_WA0 || kind == ST_WT0 || kind == ST_WT ? (u32)SMAX_BLOCKS : CAP_MAX;
+}
 constexpr int NKIND = ST_WA0 + 1;
 constexpr int NCLASS = 48;
 constexpr u8 SHAPE_DEFAULT = 0xFF;
@@ -343,7 +349,7 @@ u32 grid_for(u32 kind, u64 units, u32 qdef) {
     }
     const u64 t = (units + (1ull << qlog) - 1) >> qlog;
     const u64 b = (t + SBLOCK - 1) / SBLOCK;
-    return (u32)std::max<u64>(1, std::min<u64>(b, 1ull << caplog));
+    return (u32)std::max<u64>(1, std::min<u64>(b, std::min<u64>(1ull << caplog, cap_max(kind))));
 }
 
 // Scratch of one proof on a circuit: the layer tables, the per-round tables
@@ -814,8 +820,9 @@ static size_t gate_block_max(const gkr_circuit *c) {
 // resident, every table on the device; per layer, the layer tables in host
 // memory with three device slots for them (and two for the gate arrays
 // when those are in host memory); per message, the layer and round tables
-// in host memory.  Small state (eq half tables, rows, transcript, step
-// program) is always on the device.
+// and the rows in host memory (a row is written once and read once; on the
+// device they were most of what the mode still needed there).  Small state
+// (eq half tables, transcript, step program) is always on the device.
 static void carve(const gkr_circuit *c, Arena &a, Arena &h, Workspace &w, const PlanSizes &ps) {
     const size_t nsteps = ps.nsteps;
     const int mode = w.mode;
@@ -828,22 +835,26 @@ static void carve(const gkr_circuit *c, Arena &a, Arena &h, Workspace &w, const 
         w.gslot = c->gates_host ? gate_block_max(c) : 0;
         for (int k = 0; k < 2; k++) w.Gslot[k] = w.gslot ? a.take<char>(w.gslot) : nullptr;
     }
-    const u64 half = std::max<u64>(1ull << (c->smax ? c->smax - 1 : 0), 2);
-    w.pA = rt.take<u64>(half);
-    w.pB = rt.take<u64>(half);
-    w.fA = rt.take<u64>(half);
-    w.fB = rt.take<u64>(half);
     const bool gates = c->omega_algo == GKR_OMEGA_GATES;
+    // Folded levels alternate between two buffers.  Steps of three rounds (the
+    // first p-phase step: three at least) store level 3 at most in one and
+    // level 6 at most in the other; per-gate rounds fold F one level at a time.
+    auto level = [](u32 s, u32 k) { return std::max<u64>(s > k ? 1ull << (s - k) : 1, 2); };
+    w.pA = rt.take<u64>(level(c->smax, 3));
+    w.pB = rt.take<u64>(level(c->smax, 6));
+    w.fA = rt.take<u64>(level(c->spmax, gates ? 1 : 3));
+    w.fB = rt.take<u64>(level(c->spmax, gates ? 1 : 6));
     w.w = rt.take<u64>(gates ? c->gmax : 1);   // per-gate weights: per-gate rounds only
     w.off = rt.take<u64>(gates ? c->gmax : 1);
-    w.alo = a.take<u64>(HALF_MAX);
-    w.ahi = a.take<u64>(HALF_MAX);
-    w.blo = a.take<u64>(HALF_MAX);
-    w.bhi = a.take<u64>(HALF_MAX);
+    const u64 eqhalf = 1ull << ((c->smax + 1) / 2);  // the longer half of the widest point's eq table
+    w.alo = a.take<u64>(eqhalf);
+    w.ahi = a.take<u64>(eqhalf);
+    w.blo = a.take<u64>(eqhalf);
+    w.bhi = a.take<u64>(eqhalf);
     w.llo = a.take<u64>(c->line_lo);
     w.lhl = a.take<u64>(c->line_hl);
     w.lhh = a.take<u64>(c->line_hh);
-    w.rowpool = a.take<u64>(std::max<u64>(ps.rows, 1));
+    w.rowpool = rt.take<u64>(std::max<u64>(ps.rows, 1));
     w.frec = a.take<u64>(std::max<u64>(ps.recs, 1));
     w.d_items = a.take<FinItem>(std::max<u64>(ps.items, 1));
     w.d_top = a.take<TopLayer>(c->L);
@@ -860,10 +871,10 @@ static void carve(const gkr_circuit *c, Arena &a, Arena &h, Workspace &w, const 
         const u64 N = 1ull << c->spmax;
         w.tA0 = rt.take<u64>(N);
         w.tC0 = rt.take<u64>(N);
-        w.tA[0] = rt.take<u64>(std::max<u64>(N / 2, 2));
-        w.tA[1] = rt.take<u64>(std::max<u64>(N / 2, 2));
-        w.tC[0] = rt.take<u64>(std::max<u64>(N / 2, 2));
-        w.tC[1] = rt.take<u64>(std::max<u64>(N / 2, 2));
+        w.tA[0] = rt.take<u64>(level(c->spmax, 3));
+        w.tA[1] = rt.take<u64>(level(c->spmax, 6));
+        w.tC[0] = rt.take<u64>(level(c->spmax, 3));
+        w.tC[1] = rt.take<u64>(level(c->spmax, 6));
         w.partA = rt.take<u64>(c->nch_max);
         w.partC = rt.take<u64>(c->nch_max);
     }
@@ -956,7 +967,7 @@ struct Planner {
         s.reduces = 1;
         s.K = K;
         const u64 n = units.back();
-        const u64 most = n ? std::min<u64>(CAP_MAX, std::max<u64>(1, (n + SBLOCK - 1) / SBLOCK)) : s.nblocks;
+        const u64 most = n ? std::min<u64>(cap_max(s.kind), std::max<u64>(1, (n + SBLOCK - 1) / SBLOCK)) : s.nblocks;
         s.rows = w ? w->rowpool + rows_used : nullptr;
         rows_used += std::max<u64>(most, s.nblocks) * std::max<u32>(K, ROW_STRIDE);
     }
@@ -1271,7 +1282,7 @@ struct Planner {
                 mods.back() = 6.0 * (1ull << sp) + 2.0 * sp * (sp - 1) * lwg;
                 e.fin = f;
                 lrows = w ? w->rowpool + rows_used : nullptr;
-                rows_used += (u64)LFOLD_CHUNKS * lwg * ROW_STRIDE;
+                rows_used += (u64)((sp - 1 + ROW_STRIDE - 1) / ROW_STRIDE) * lwg * ROW_STRIDE;
                 e.u.lfold = LfoldArgs{sp, ltb, co + s, co + s + sp, V(i + 1), lrows, chals};
             };
             const u64 ntab = sp >= 2 ? (u64)(sp - 1) * ((1ull << Ll) + (1ull << M) + (1ull << H)) : 1;

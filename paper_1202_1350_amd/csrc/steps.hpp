@@ -251,13 +251,13 @@ constexpr u32 lfold_wg_live(u32 sp, u64 n) {
     const u64 need = (n + (1ull << (lfold_tb(sp) + 9)) - 1) >> (lfold_tb(sp) + 9);
     return need < 1 ? 1u : need > lfold_wg(sp) ? lfold_wg(sp) : (u32)need;
 }
-constexpr u32 LFOLD_CHUNKS = 2;  // rows a workgroup: h(2..s'), s' - 1 <= 2 ROW_STRIDE values
+constexpr u32 LFOLD_CHUNKS = 2;  // most rows a workgroup: h(2..s'), s' - 1 <= 2 ROW_STRIDE values
 static_assert(LFOLD_MAX - 1 <= LFOLD_CHUNKS * ROW_STRIDE, "h(2..s') fits a workgroup's rows");
 static_assert(LFOLD_MAX <= 32, "b*_k and c*_k - b*_k of the line sit in 32 words of LDS each");
 struct LfoldArgs {
     u32 sp, tb, bbase, cbase;  // coordinates; 2^tb entries a thread; challenge indices of b* and c*
     const u64 *V;              // V_{i+1}
-    u64 *rows;                 // LFOLD_CHUNKS x nwg rows of ROW_STRIDE words
+    u64 *rows;                 // nwg rows of ROW_STRIDE words for every ROW_STRIDE values
     const u64 *chals;
 };
 struct SgeArgs {

@@ -149,3 +149,30 @@ def test_server_admits_over_budget_proofs_out_of_core():
             assert np.array_equal(out[rid], O.prove(circ, W.f2_inputs(1 << 16, k), 40 + k)[0])
     finally:
         srv.close()
+
+
+# Device bytes each placement (resident, per layer, per message) took when a
+# step summed two rounds: budgets chosen by those figures keep their meaning.
+TWO_ROUNDS = [
+    ("F0", 100003, 1, (784981248, 41148672, 16976128)),
+    ("F0", 100003, 0, (354652672, 135179776, 119396352)),
+    ("F2", 1 << 21, 1, (462301696, 210067456, 8739840)),
+    ("PM", 100003, 1, (220199680, 103307264, 6620672)),
+    ("MatMult", 128, 1, (360798208, 192094208, 7543808)),
+]
+
+
+@pytest.mark.parametrize("kind,n,algo,bytes_then", TWO_ROUNDS)
+def test_budgets_of_the_two_round_steps_still_hold(kind, n, algo, bytes_then):
+    circ = {"F0": W.f0_circuit, "F2": W.f2_circuit, "PM": W.pm_circuit, "MatMult": W.matmult_circuit}[kind](n)
+    x = {"F0": W.f0_inputs, "F2": W.f2_inputs, "MatMult": W.matmult_inputs,
+         "PM": lambda m, seed: W.pm_inputs(m, seed)[0]}[kind](n, 9)
+    gc = G().Circuit.from_workload(circ, omega_algo=algo)
+    need = [gc.memory_need(m)[0] for m in (0, 1, 2)]
+    say("needs", kind, n, "algo", algo, need)
+    assert all(now <= then for now, then in zip(need, bytes_then)), (need, bytes_then)
+    want, _ = G().gkr_prove(gc, x, 3)
+    for mode in (1, 2):
+        assert gc.set_memory(mode, bytes_then[mode]) == mode
+        say("proof in placement", mode, "of", kind, n)
+        assert np.array_equal(G().gkr_prove(gc, x, 3)[0], want)
