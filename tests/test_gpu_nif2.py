@@ -112,3 +112,26 @@ def test_row_lengths_and_tile_edges(n, h):
     got = G().nif2_prove(device_tensor(a), h)
     bad = np.nonzero(got != want)[0]
     assert len(bad) == 0, f"first differing values {bad[:5]} of {2 * h}"
+
+
+@pytest.mark.parametrize("n,h", [(5005 * 2 + 1, 5005), (315 * 256, 315), (315 * 257 - 3, 315), (315 * 512 + 1, 315),
+                                 (45 * 100 + 7, 45), (45 * 2049, 45), (9 * 8192, 9), (9 * 8193 + 4, 9),
+                                 (9 * 65537 - 1, 9), (63 * 16385 + 2, 63), (99 * 8193 - 5, 99), (225 * 4097 + 1, 225),
+                                 (693 * 1025, 693), (1287 * 513 - 1, 1287)])
+def test_tile_heights_by_row_count(n, h):
+    """The height of a tile follows the number of rows: one row, the changes to
+    two and to four, the lowest of short rows and the one after it, and the
+    full height of every row length with the last tile partly filled.  Exact."""
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, P, n).astype(np.uint64)
+    a[:2] = a[-2:] = P - 1
+    say("nif2 tile heights", "n", n, "h", h)
+    O.set_threads(oracle_threads())
+    want = O.nif2_prove(a, h)
+    got = G().nif2_prove(device_tensor(a), h)
+    bad = np.nonzero(got != want)[0]
+    assert len(bad) == 0, f"first differing values {bad[:5]} of {2 * h}"
+    a[n // 2] = P
+    with pytest.raises(G().GkrError) as e:
+        G().nif2_prove(device_tensor(a), h)
+    assert e.value.code == G().GKR_ERR_RANGE
