@@ -2732,8 +2732,11 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
     u64 tab_words = 0;
     u32 eq_blocks = 0, gate_blocks = 0;
     std::vector<WireLayer> wl;
+    const auto on_host = [&](u32 i) { return closed && c->form[i] != GKR_WIRING_GATES; };  // (below)
+    u64 wanted = 0;
+    for (u32 i = 0; i < d; i++) wanted += on_host(i) ? 0 : wire_blocks_wanted(c->S[i]);
     for (u32 i = 0; i < d; i++) {
-        if (closed && c->form[i] != GKR_WIRING_GATES) continue;  // on the host below
+        if (on_host(i)) continue;
         const u32 s = c->s[i], sp = c->s[i + 1];
         WireLayer w;
         memset(&w, 0, sizeof w);
@@ -2751,7 +2754,7 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
         w.in2 = c->in2[i];
         w.tab = (u64 *)tab_words;  // (its offset, for now)
         eq_blocks += wire_eq_blocks(s, sp);
-        gate_blocks += wire_gate_blocks(c->S[i]);
+        gate_blocks += wire_gate_blocks(c->S[i], wanted);
         tab_words += wire_table_words(s, sp) + BLOCK;  // (the last workgroup's threads past the tables write nothing)
         gl.push_back(i);
         wl.push_back(w);
@@ -2843,7 +2846,7 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
         l.v2 = msgs[mi++];
         l.beta = 1;
         for (u32 k = 0; k < s; k++) l.beta = mul(l.beta, eq(z[i][k], r[k]));
-        if (closed && c->form[i] != GKR_WIRING_GATES)
+        if (on_host(i))
             l.w = wiring_closed(c->form[i], c->S[i], s, sp, r, r + s, r + s + sp);
         l.line = sp != 0 || l.v1 == l.v2;
         u64 y[33];  // (s_{i+1} <= 31)
@@ -2857,7 +2860,7 @@ extern "C" int gkr_verify(const gkr_circuit *c, const uint64_t *inputs, int inpu
     for (u32 i = 0, q = 0; i < upto; i++) {
         const Layer &l = lv[i];
         u64 addv = 0, mulv = 0;
-        if (closed && c->form[i] != GKR_WIRING_GATES) {
+        if (on_host(i)) {
             (c->kind[i] == KIND_ADD ? addv : mulv) = l.w;
         } else {
             for (u32 b = wl[q].block0; b < wl[q + 1].block0; b++) {

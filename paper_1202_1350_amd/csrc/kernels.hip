@@ -121,9 +121,14 @@ u64 wire_table_words(u32 s, u32 sp) {
     return (1ull << (s / 2)) + (1ull << (s - s / 2)) + 2 * ((1ull << (sp / 2)) + (1ull << (sp - sp / 2)));
 }
 u32 wire_eq_blocks(u32 s, u32 sp) { return (u32)((wire_table_words(s, sp) + BLOCK - 1) / BLOCK); }
-u32 wire_gate_blocks(u32 S) {
-    // two gates a thread before another workgroup starts, at most 256 a layer
-    return std::max<u32>(1, std::min<u32>(256, (S + 2 * BLOCK - 1) / (2 * BLOCK)));
+u32 wire_gate_blocks(u32 S, u64 blocks_all) {
+    // The layers of a launch share WIRE_BLOCKS workgroups (eight a CU, all the
+    // chip holds at once) by gates: a thread's gates are a chain of dependent
+    // gathers, so one wide layer needs them all (2^24 gates: 218 us a
+    // verification, 302 with 256 workgroups a layer), and many layers no more
+    // (78 layers of F0 on 100003 values 117 us, 147 with two gates a thread).
+    const u64 b = wire_blocks_wanted(S);
+    return (u32)(blocks_all <= WIRE_BLOCKS ? b : std::max<u64>(1, b * WIRE_BLOCKS / blocks_all));
 }
 
 hipError_t launch_wiring(hipStream_t st, const WireLayer *L, u32 n, u32 eq_blocks, u32 gate_blocks, const u64 *pts,

@@ -4,6 +4,8 @@
 // them synchronises.  Device pointers only.  Reductions write one row of
 // partial sums per workgroup; the host adds the rows.
 #pragma once
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -48,7 +50,12 @@ struct WireLayer {
 };
 u64 wire_table_words(u32 s, u32 sp);
 u32 wire_eq_blocks(u32 s, u32 sp);
-u32 wire_gate_blocks(u32 S);
+// Workgroups of a layer of S gates: two gates a thread before another starts,
+// a share of WIRE_BLOCKS when the launch's layers want more in all
+// (blocks_all, the sum of what they want), at least one.
+constexpr u64 WIRE_BLOCKS = 2048;
+inline u64 wire_blocks_wanted(u32 S) { return std::max<u64>(1, ((u64)S + 2 * BLOCK - 1) / (2 * BLOCK)); }
+u32 wire_gate_blocks(u32 S, u64 blocks_all);
 // L: n descriptors on the device, then one whose eq0 and block0 are the totals.
 // out[2b], out[2b+1]: workgroup b's sums over ADD and MUL gates.
 hipError_t launch_wiring(hipStream_t st, const WireLayer *L, u32 n, u32 eq_blocks, u32 gate_blocks, const u64 *pts,

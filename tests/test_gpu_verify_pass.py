@@ -4,7 +4,8 @@ exact: the honest transcript is accepted, one changed input is rejected."""
 import numpy as np
 import pytest
 
-from gpu_util import say, device_tensor
+from gpu_util import say, device_tensor, oracle_threads
+from oracle import oracle as O
 import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +69,33 @@ def test_rows(n, h):
     with pytest.raises(G().GkrError) as e:
         G().nif2_verify(device_tensor(a), h, 3, m)
     assert e.value.code == G().GKR_ERR_RANGE
+
+
+@pytest.mark.parametrize("sizes", [[5, 524288, 64], [5, 700001, 3, 1100003, 257], [2, 1048576, 1048577, 9]])
+def test_layers_share_the_workgroups_of_one_pass(sizes):
+    """Layers without a closed form whose gates want just the workgroups a pass
+    has, or more (then shared by gates, one at least for the small ones): a
+    changed v1 of each layer is found in that layer, as the oracle finds it."""
+    rng = np.random.default_rng(sum(sizes))
+    types, in1, in2 = [], [], []
+    for s, below in zip(sizes, sizes[1:]):
+        types.append(rng.integers(0, 2, s, np.uint8))
+        in1.append(rng.integers(0, below, s, np.uint32))
+        in2.append(rng.integers(0, below, s, np.uint32))
+    circ = W.circuits.Circuit(list(sizes), types, in1, in2, name=f"shares {sizes}")
+    x = W.splitmix64(3, 1, sizes[-1]) % np.uint64(P)
+    say("verify shares", sizes)
+    O.set_threads(oracle_threads())
+    c, t = G().Circuit.from_workload(circ), device_tensor(x)
+    msgs, _ = G().gkr_prove(c, t, 8)
+    assert G().gkr_verify(c, t, 8, msgs) == (True, -1, -1, 0) == O.verify(circ, x, 8, msgs)
+    at = sizes[0]
+    for i, (s, below) in enumerate(zip(sizes, sizes[1:])):
+        a, b = (s - 1).bit_length(), (below - 1).bit_length()
+        v1 = at + 3 * (a + 2 * b)
+        at = v1 + 2 + max(b - 1, 0)
+        bad = msgs.copy()
+        bad[v1] = (int(bad[v1]) + 1) % P
+        got = G().gkr_verify(c, t, 8, bad)
+        assert got == O.verify(circ, x, 8, bad) and got[:2] == (False, i)
+    assert at == len(msgs)
