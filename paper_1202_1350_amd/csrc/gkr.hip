@@ -3708,9 +3708,11 @@ extern "C" int nif2_verify(const uint64_t *a, uint64_t n, uint32_t h, int on_dev
     LAUNCH(PC_NIF2, n * 8.0 + 5.0 * h * 8, launch_nif2_verify(st, src, n, v, h, w, xi, r, b.L, hmsgs, out, (u32 *)hflag));
     HIP_TRY(hipStreamSynchronize(st));
     if (*(const u32 *)hflag) return fail(GKR_ERR_RANGE, "input value not below p");
-    u64 rows = 0;
-    for (u32 k = 1; k < nb; k++) rows = fp::add(rows, out[k]);
-    *accepted = rows == out[0];
+    const u32 pb = nif2_proof_blocks(h);
+    u64 rows = 0, at_r = 0;
+    for (u32 k = 0; k < pb; k++) at_r = fp::add(at_r, out[k]);
+    for (u32 k = pb; k < nb; k++) rows = fp::add(rows, out[k]);
+    *accepted = rows == at_r;
     if (f2) {
         u64 s = 0;
         for (u64 j = 0; j < h; j++) s = fp::add(s, msgs[2 * j]);

@@ -659,25 +659,37 @@ __global__ void k_nif2_bases(u64 w, u64 xi, u64 h, u64 r, u64 rh1, u64 r2h1, u64
         L[t] = mul(mul(wj, rN1), fp::inv(mul(N % P, sub(r, wj))));
 }
 
-// Verifier's pass over the grid: out[1 + b] = the sum over workgroup b's rows
-// y of (sum_j a(j, y) L[j])^2, and out[0] = sum_k msgs[k] L[h + k] (workgroup
-// 0).  RW adjacent rows at a time, RB / RW threads a row taking every
+// Verifier's pass over the grid: out[pb + b] = the sum over workgroup pb + b's
+// rows y of (sum_j a(j, y) L[j])^2, and out[0 .. pb) add up to sum_k msgs[k]
+// L[h + k], PROOF_WORDS of the proof a workgroup, all its loads in flight: the
+// proof is in host memory, and one workgroup for all of it waited a trip over
+// the link for every 512 words (a verification of 5 10^4 values at h = 225225
+// 1497 us, now 736; at h = 5005 60, now 56).  RW adjacent rows at a time, RB / RW threads a row taking every
 // (RB / RW)-th column, eight loads in flight; values are checked against p as
 // they pass.  One read of the grid: 200 MB in 37 us at h = 585 (a range check,
 // a pass of 32-column parts and their squares before: 72 us in three).
+constexpr u32 PROOF_WORDS = 4 * RB;
+static_assert((2 * NIF2_MAX_H + PROOF_WORDS - 1) / PROOF_WORDS < NIF2_ROW_BLOCKS, "workgroups left for the rows");
 template <int RW>
 __global__ void __launch_bounds__(RB) k_nif2_rowsum(const u64 *__restrict__ a, u32 h, u32 full, u64 rem, u64 v,
-                                                    const u64 *__restrict__ L, const u64 *__restrict__ msgs, u64 *out,
-                                                    u32 *flag) {
+                                                    const u64 *__restrict__ L, const u64 *__restrict__ msgs, u32 pb,
+                                                    u64 *out, u32 *flag) {
     constexpr u32 G = RB / RW, U = 8;
     __shared__ u64 sm[G][RW];
     const u32 tid = threadIdx.x, y = tid % RW, g = tid / RW;
     u64 s = 0;
-    if (blockIdx.x == 0) {
-        for (u32 k = tid; k < 2 * h; k += RB) s = add(s, mul(msgs[k], L[h + k]));
+    if (blockIdx.x < pb) {
+        constexpr u32 W = PROOF_WORDS / RB;
+        const u32 k0 = blockIdx.x * PROOF_WORDS + tid;
+        u64 m[W];
+#pragma unroll
+        for (u32 i = 0; i < W; i++) m[i] = k0 + i * RB < 2 * h ? msgs[k0 + i * RB] : 0;
+#pragma unroll
+        for (u32 i = 0; i < W; i++)
+            if (k0 + i * RB < 2 * h) s = add(s, mul(m[i], L[h + k0 + i * RB]));
     } else {
         u64 bad = 0;
-        for (u64 y0 = (u64)(blockIdx.x - 1) * RW; y0 < v; y0 += (u64)(gridDim.x - 1) * RW) {
+        for (u64 y0 = (u64)(blockIdx.x - pb) * RW; y0 < v; y0 += (u64)(gridDim.x - pb) * RW) {
             const u64 row = y0 + y;
             const u32 cols = row < v ? full + (row < rem ? 1u : 0u) : 0u;
             u64 t = 0;
@@ -720,9 +732,10 @@ __global__ void __launch_bounds__(RB) k_nif2_rowsum(const u64 *__restrict__ a, u
 // Rows a workgroup takes at a time: 512, a thread a row, where rows are short;
 // else 64 while they fill the chip.
 static u64 rowsum_rows(u32 h, u64 v) { return v < 64 * 512 ? 16 : h > 64 ? 64 : 512; }
+u32 nif2_proof_blocks(u32 h) { return (2 * h + PROOF_WORDS - 1) / PROOF_WORDS; }
 u32 nif2_rowsum_blocks(u32 h, u64 v) {
     const u64 rw = rowsum_rows(h, v), b = (v + rw - 1) / rw;
-    return 1 + (u32)std::min<u64>(b, NIF2_ROW_BLOCKS - 1);
+    return nif2_proof_blocks(h) + (u32)std::min<u64>(b, NIF2_ROW_BLOCKS - nif2_proof_blocks(h));
 }
 
 hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, u64 w, u64 xi, u64 r, u64 *L,
@@ -732,14 +745,14 @@ hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h,
                        sub(mul(rh, rh), 1), L, flag);
     const dim3 g(nif2_rowsum_blocks(h, v));
     const u64 rw = rowsum_rows(h, v);
-    const u32 full = (u32)(n / v);
+    const u32 full = (u32)(n / v), pb = nif2_proof_blocks(h);
     const u64 rem = n % v;
     if (rw == 512)
-        hipLaunchKernelGGL(k_nif2_rowsum<512>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
+        hipLaunchKernelGGL(k_nif2_rowsum<512>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, pb, out, flag);
     else if (rw == 64)
-        hipLaunchKernelGGL(k_nif2_rowsum<64>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
+        hipLaunchKernelGGL(k_nif2_rowsum<64>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, pb, out, flag);
     else
-        hipLaunchKernelGGL(k_nif2_rowsum<16>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, out, flag);
+        hipLaunchKernelGGL(k_nif2_rowsum<16>, g, dim3(RB), 0, st, a, h, full, rem, v, L, msgs, pb, out, flag);
     return hipGetLastError();
 }
 

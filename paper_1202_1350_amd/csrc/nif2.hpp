@@ -46,11 +46,14 @@ hipError_t launch_nif2_colsum(hipStream_t st, const PfaPlan &pl, const u64 *a, u
                               const u64 *W, u64 *part, u64 *msgs);
 // tw[k] = xi^k / h, k < h.
 hipError_t launch_nif2_twist(hipStream_t st, u32 h, u64 xi, u64 *tw);
-// The verifier at the secret r: out[0] = the value at r of the polynomial
-// through the 2h proof values msgs (device-visible), and out[1 ..
-// nif2_rowsum_blocks(h, v)) add up to sum_y f_y(r)^2; *flag = 1 if some a_i >= p
-// (cleared first).  L: 3h scratch words.
+// The verifier at the secret r: out[0 .. nif2_proof_blocks(h)) add up to the
+// value at r of the polynomial through the 2h proof values msgs
+// (device-visible), out[nif2_proof_blocks(h) .. nif2_rowsum_blocks(h, v)) to
+// sum_y f_y(r)^2; *flag = 1 if some a_i >= p (cleared first).  L: 3h scratch
+// words.
 constexpr u32 NIF2_ROW_BLOCKS = 1024;
+constexpr u32 NIF2_MAX_H = 9 * 25 * 7 * 11 * 13;  // the longest row of the supported factors
+u32 nif2_proof_blocks(u32 h);
 u32 nif2_rowsum_blocks(u32 h, u64 v);
 hipError_t launch_nif2_verify(hipStream_t st, const u64 *a, u64 n, u64 v, u32 h, u64 w, u64 xi, u64 r, u64 *L,
                               const u64 *msgs, u64 *out, u32 *flag);
