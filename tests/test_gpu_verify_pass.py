@@ -99,3 +99,50 @@ def test_layers_share_the_workgroups_of_one_pass(sizes):
         got = G().gkr_verify(c, t, 8, bad)
         assert got == O.verify(circ, x, 8, bad) and got[:2] == (False, i)
     assert at == len(msgs)
+
+
+@pytest.mark.parametrize("n,h", [(64 * 512 * 9 - 9, 9), (64 * 512 * 9, 9), (64 * 512 * 99 - 99, 99), (64 * 512 * 99 + 40, 99),
+                                 (32833 * 65 - 7, 65)])
+def test_rows_a_workgroup_takes(n, h):
+    """Grids of 16, 512 and 64 rows a workgroup at the changes between them
+    (32768 rows; rows of more than 64 values), the last group and the last
+    column partly filled.  The verdicts are the oracle's; a changed value and one
+    out of range are found in the last group and in the last column."""
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, P, n).astype(np.uint64)
+    a[0] = a[-1] = P - 1
+    v = -(-n // h)
+    say("verify rows a workgroup, n", n, "h", h, "rows", v)
+    t = device_tensor(a)
+    m = G().nif2_prove(t, h)
+    f2 = sum(int(m[2 * j]) for j in range(h)) % P
+    O.set_threads(oracle_threads())
+    assert G().nif2_verify(t, h, 3, m) == (True, f2) == O.nif2_verify(a, h, 3, m)
+    for k in (v - 1, n // 2, n - 1):
+        b = a.copy()
+        b[k] = (int(b[k]) + 1) % P
+        assert G().nif2_verify(device_tensor(b), h, 3, m) == (False, f2) == O.nif2_verify(b, h, 3, m)
+        b[k] = P
+        with pytest.raises(G().GkrError) as e:
+            G().nif2_verify(device_tensor(b), h, 3, m)
+        assert e.value.code == G().GKR_ERR_RANGE
+
+
+@pytest.mark.parametrize("h", [1001, 1287, 5005, 225225])
+def test_long_proofs(h):
+    """Proofs of one to 220 workgroups' words, the last one partly filled: every
+    changed word is found, as the oracle finds it."""
+    rng = np.random.default_rng(h)
+    a = rng.integers(0, P, 3 * h + 1).astype(np.uint64)
+    say("verify long proof h", h)
+    t = device_tensor(a)
+    m = G().nif2_prove(t, h)
+    O.set_threads(oracle_threads())
+    want = O.nif2_verify(a, h, 5, m)
+    assert want[0] and G().nif2_verify(t, h, 5, m) == want
+    for k in (0, 511, 2 * h // 2048 * 2048 - 1, 2 * h // 2048 * 2048, 2 * h - 1):
+        if not 0 <= k < 2 * h:
+            continue
+        bad = m.copy()
+        bad[k] = (int(bad[k]) + 1) % P
+        assert not G().nif2_verify(t, h, 5, bad)[0], k
