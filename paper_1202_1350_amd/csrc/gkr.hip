@@ -59,6 +59,8 @@ namespace {
 
 // Profiling classes: one per step kind (the kernel k_step_one<kind, ...>),
 // then the verifier's and the F2 sum-check's kernels.
+// (Nothing is timed under PC_TABLES and PC_MISC any more; they keep their
+// places in the list that gkr_profile_read reports.)
 enum ProfClass {
     PC_STEP = 0,  // + StepKind
     PC_WIRING = 21, PC_MLE, PC_TABLES, PC_F2SC, PC_FINAL, PC_MISC, PC_BATCH, PC_NIF2, PC_SERVE, PC_COUNT

@@ -213,10 +213,13 @@ __device__ __forceinline__ void mac(Sums &a, Half x, Half y) {
     a.mm += (u64)x.h * y.l;
     a.hh += (u64)x.h * y.h;
 }
-// The value of N <= 7 terms' sums plus x0 (below 2^62 + 32), below 2^61 + 8:
+// The value of N <= 7 terms' sums plus x0, below 2^61 + 8:
 // ll + mm 2^31 + 2 hh with 2^31 mm = (mm >> 30) + (mm mod 2^30) 2^31.  Before
-// the last fold: ll folded 2^61, x0 2^62, 2^34, 2^61 and 2 hh 2^63 for four
-// terms (folded first for more), below 2^64 together.
+// the last fold ll is folded (2^61), mm's parts are 2^34 and 2^61, and 2 hh is
+// 2^61 a term (for more than four terms hh is folded first: 2^62).  With four
+// terms x0 is below 2^61 + 8: 7 2^61 and less than 2^36 in all, below 2^64.
+// Where F = 9 moves one of its four terms into x0 (below 2^62 + 32 then) three
+// are left: 7 2^61 and less than 2^36 again.
 template <int N>
 __device__ __forceinline__ u64 total(const Sums &a, u64 x0 = 0) {
     const u64 t = fold(a.ll) + x0 + (a.mm >> 30) + (u64)((u32)a.mm & 0x3fffffffu) * 0x80000000u;

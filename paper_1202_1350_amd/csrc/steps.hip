@@ -344,6 +344,9 @@ struct Gram {
     i32x16 acc[2][2];  // by tile of A's and F's digits
     u64 c;             // sum of the lane's C entries, below 2^61 + 8
 };
+// (A last turn that some waves lack stays with oct_add as well: 786,500 wires,
+// just above three a thread, prove in 437 us so and in 425 with oct_add, 900,001
+// in 448 and 441, 1,040,001 in 473 and 467; 2^20, four a thread, in 472.)
 __device__ __forceinline__ bool gram_fits(u64 n, u64 stride) {  // (uniform)
     return n >= 4 * stride && n <= (stride << 13);               // at most 2^16 octs a wave
 }
@@ -477,9 +480,9 @@ __device__ __forceinline__ void t_message(const u64 *E, u32 k, const u64 *r, u64
     if (lane < 3) msg[lane] = lane == 0 ? q0 : (lane == 1 ? q1 : sub(add(add(q1, q1), add(q2, q2)), q0));
 }
 
-// One item of ST_FINISH: a round's rows into its message, lanes t < 3 (and
-// 3..5 for a second message) writing one value each; operands that do not
-// depend on the rows are loaded before the row sums.
+// One item of ST_FINISH: the rows of one round (FIN_W), of the rounds a step
+// summed (FIN_P, FIN_T: the columns are added up, then a wave forms each
+// message) or of a chunk of line values into the transcript.
 __device__ __forceinline__ void step_finish(const FinishArgs &a, const Ctx &c) {
     const FinItem &it = a.items[c.lb];
     const u32 tid = threadIdx.x;
@@ -1826,7 +1829,7 @@ __device__ __forceinline__ void step_lfold(const LfoldArgs &a, const Ctx &c, i32
 // omega phases leave V_{i+1} as level 0 of F, which is the next layer's
 // V_i, so global memory is read only for each V_{i+1} and the wiring and
 // written only for messages, challenges and RNG states.  LDS areas (TAIL_TAB
-// entries each): X holds B (p-phase), A (omega phases) and the line's point
+// entries each): X holds the p-phase's sums, A (omega phases) and the line's point
 // tables; Y holds C and, in its last 128 entries, the eq halves of a* and
 // b* while the level-0 tables are formed; Z holds V_i, then F.
 

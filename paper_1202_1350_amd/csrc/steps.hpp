@@ -41,17 +41,17 @@ constexpr int ROW_STRIDE = 16;   // u64 per partial-sum row
 enum StepKind : u32 {
     ST_EVAL = 0,   // V_i[g] = V_{i+1}[in1] op V_{i+1}[in2]
     ST_START,      // outputs into the transcript, z_0 drawn
-    ST_EQ,         // eq half tables of a point (z_i suffix, a*, or b*)
-    ST_P,          // one p-phase round (a-variables)
-    ST_W,          // one omega round (b- or c-variables)
+    ST_EQ,         // eq half tables of a point (a* or b*)
+    ST_P,          // p-phase, three to seven rounds (a-variables)
+    ST_W,          // one omega round (b- or c-variables), gate by gate
     ST_FOLD,       // fold of V_{i+1}'s table by the last challenge
     ST_LT,         // eq tables of the line points
     ST_LINE,       // line sums h(t), t = 2..s'
     ST_SGE,        // next layer has one gate: v1 = v2 = V_{i+1}[0]
     ST_END,        // nothing but the prologue
     ST_WAGG,       // omega phase, tables: per-gate weights summed by bound wire
-    ST_WT0,        // omega phase, tables: level-0 tables and round 0
-    ST_WT,         // omega phase, tables: round k >= 1 (fold, then sum)
+    ST_WT0,        // omega phase, tables: level-0 tables and rounds 0 to 2
+    ST_WT,         // omega phase, tables: rounds k to k + 2 (fold, then sum)
     ST_WTAIL,      // omega phase, tables: remaining rounds in one workgroup
     ST_PTAIL,      // p-phase: remaining rounds in one workgroup
     ST_LOAD,       // inputs (pointer in state[3]) into V_d, range check
