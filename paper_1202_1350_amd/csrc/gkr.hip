@@ -293,8 +293,8 @@ void line_shape(u32 sp, u32 *L, u32 *M, u32 *H) {
 // log2 q (bits 0-1) and log2 cap - 8 (bits 2-3): 16 candidates.
 // Steps that leave an oct's sums take at most SMAX_BLOCKS workgroups whatever
 // the shape says: their rows are twice as long as the others', every row is
-// kept until the proof ends, and no tuning of theirs chose more (the caps of
-// 2048 it lists are of classes with fewer workgroups).
+// kept until the proof ends, and a tuning free to choose more of them did not
+// (larger caps in a table stand for the same grids).
 constexpr u32 CAP_MAX = 2048;
 constexpr u32 cap_max(u32 kind) {
     return kind == ST_WA0 || kind == ST_WT0 || kind == ST_WT ? (u32)SMAX_BLOCKS : CAP_MAX;

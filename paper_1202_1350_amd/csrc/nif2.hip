@@ -337,13 +337,7 @@ __device__ __forceinline__ void square_sums(const u64 *W, u32 h, u32 logty, u64 
         const u32 p = threadIdx.x + c * RB;
         if (p < h) {
             u64 t = acc[c];
-            if (logty < 2) {  // (uniform) a tile of one row or two
-                Sums s;
-                square(s, W[p << logty]);
-                if (logty) square(s, W[(p << 1) + 1]);
-                t = fold(t + total<4>(s));
-            }
-            for (u32 y = 0; y + 4 <= (1u << logty); y += 4) {
+            for (u32 y = 0; y < (1u << logty); y += 4) {
                 Sums s;
 #pragma unroll
                 for (u32 i = 0; i < 4; i++) square(s, W[(p << logty) + y + i]);
@@ -353,8 +347,8 @@ __device__ __forceinline__ void square_sums(const u64 *W, u32 h, u32 logty, u64 
         }
     }
 }
-// Short rows: a row a lane (a thread a position would leave most threads
-// idle), summed over the lanes of a position into s_acc, LDS.
+// Short rows, and one row or two: a row a lane (a thread a position would leave
+// most threads idle), summed over the lanes of a position into s_acc, LDS.
 __device__ __forceinline__ void square_lanes(const u64 *W, u32 h, u32 logty, u64 *s_acc) {
     const u32 lane = threadIdx.x & 63, w = threadIdx.x >> 6, lw = logty < 6 ? logty : 6;  // log2 lanes a position
     const u32 y0 = lane & ((1u << lw) - 1), per = 64 >> lw;
@@ -489,22 +483,24 @@ __global__ void __launch_bounds__(1024) k_nif2_parts(const PfaPlan pl, const u64
 // accumulate over lanes in LDS with up to 512 a tile, longer ones over threads'
 // positions with up to 64: 24 million values at h = 9 take 190 us so (820 with
 // a thread a position), at h = 99 302 us (400 over lanes), at 225 373 (491).
-// Fewer rows than fill the chip so are cut into lower tiles, down to one row,
-// while half the height makes at most one tile a CU and leaves half the
-// threads a value: 5 10^4 values took 130 us in 3 tiles of 4 rows at h = 5005
-// and take 81 in 10 of one, 52 -> 40 at h = 45 (9 tiles -> 139), 5 10^5 values
-// 131 -> 86 at 5005, 70 -> 50 at 585 (54 -> 214).  More tiles than CUs gain
-// nothing: 5 10^5 values at h = 225 take 52 us in 139, 56 in 278, 62 in 556.
-static bool over_lanes(u32 h) { return h < 64; }
-static u64 tile_bytes(u32 h, u32 l) { return 8ull * h * ((1ull << l) + (over_lanes(h) ? 2 : 0)); }
+// Fewer rows than fill the chip so are cut into lower tiles, down to one row
+// (below four over lanes: the squares of a position come in fours), while half
+// the height makes at most one tile a CU and leaves half the threads a value:
+// 5 10^4 values took 130 us in 3 tiles of 4 rows at h = 5005 and take 85 in
+// 10 of one, 52 -> 40 at h = 45 (9 tiles -> 139), 5 10^5 values 131 -> 91 at
+// 5005, 70 -> 50 at 585 (54 -> 214).  More tiles than CUs gain nothing: 5 10^5
+// values at h = 225 take 52 us in 139, 56 in 278, 62 in 556.
+static bool over_lanes(u32 h, u32 l) { return h < 64 || l < 2; }
+static u64 tile_bytes(u32 h, u32 l) { return 8ull * h * ((1ull << l) + (over_lanes(h, l) ? 2 : 0)); }
 static u64 tile_count(u64 v, u32 l) { return (v + (1ull << l) - 1) >> l; }
 static u32 tile_log(u32 h, u64 v) {
-    const u32 most = over_lanes(h) ? 9 : 6;
     u32 l = 2;
+    const u32 most = over_lanes(h, l) ? 9 : 6;
     while (l < most && tile_bytes(h, l + 1) <= 80 * 1024) l++;
     while (l > 0 && tile_count(v, l - 1) <= 256 && (h << (l - 1)) >= RB / 2) l--;
     return l;
 }
+static_assert(8ull * NIF2_LDS_H * 4 <= 160 * 1024, "two rows and their sums fit LDS");
 u32 nif2_lds_groups(u32 h, u64 v) {
     const u32 l = tile_log(h, v);
     const u64 tiles = tile_count(v, l), most = 256 * std::min<u64>(4, 160 * 1024 / tile_bytes(h, l));
@@ -547,7 +543,7 @@ hipError_t launch_nif2_rows_lds(hipStream_t st, const PfaPlan &pl, const u64 *a,
     hipLaunchKernelGGL(k_nif2_tables, dim3((pl.h + NT - 1) / NT), dim3(NT), 0, st, pl, xi, fp::inv(pl.h), pos, tw);
     const u32 nc = (pl.h + RB - 1) / RB;
 #define RK(N) hipLaunchKernelGGL(k_nif2_rows_lds<N>, dim3(nwg), dim3(RB), lds, st, r)
-    if (over_lanes(pl.h)) RK(0);
+    if (over_lanes(pl.h, r.logty)) RK(0);
     else if (nc <= 1) RK(1);
     else if (nc <= 3) RK(3);
     else if (nc <= 5) RK(5);
