@@ -86,3 +86,21 @@ def test_batch_of_long_and_short_transcripts(words):
     got = G().gkr_batch_prove([G().Circuit.from_workload(c) for c in cs], [device_tensor(x) for x in xs], [4, 5, 6])
     for c, x, seed, msgs in zip(cs, xs, [4, 5, 6], got):
         assert np.array_equal(msgs, O.prove(c, x, seed)[0])
+
+
+@pytest.mark.parametrize("kind", [None, 0, 1])
+@pytest.mark.parametrize("sizes", [[9000, 8192], [5000, 40960], [700, 40896]])
+def test_four_entries_in_every_thread_or_not(sizes, kind):
+    """At four entries a thread the matrix cores take a step whose wires are a
+    multiple of 2048, over several workgroups; one that lacks the last 64 stays
+    with the sums over lanes."""
+    g = G()
+    g.gkr_tune_set(None)
+    blob = bytearray(g.gkr_tune_get())
+    shapes = 17 * 48  # step kinds by size classes, at the table's end
+    blob[-shapes:] = bytes([2]) * shapes
+    try:
+        g.gkr_tune_set(bytes(blob))
+        check(sizes, kind, 4 + sum(sizes))
+    finally:
+        g.gkr_tune_set(None)
